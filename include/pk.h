@@ -101,7 +101,7 @@ typedef struct {
  * (not a strategy of the case table; set only in instance descriptions) */
 #define PK_MFMA_SINGLE 1
 #define PK_MFMA_GROUPED 2
-#define PK_MFMA_ELEMENT 4 /* internal: the twin of a program that reads rows element by element */
+#define PK_MFMA_ELEMENT 4 /* internal: the twin of a program that reads rows at element alignment */
 #define PK_MFMA_MIXED 8   /* internal: a grouped kernel running a different tile program per product */
 #define PK_MFMA_SPLIT 16  /* internal: the form of a program that runs shares of K (pk_params.ks > 1) */
 
@@ -258,8 +258,8 @@ int pk_select_operands(const pk_table *tbl, pk_dtype dtype, const void *A, int64
  * Runs on a private stream and synchronizes.  *n receives the number
  * of candidates; arrays must hold cap >= *n entries (else
  * PK_ERR_BUFFER_TOO_SMALL).  MFMA candidates are timed on the given
- * operands as they are: rows not aligned for 16-byte loads are read element
- * by element.
+ * operands as they are: rows not aligned for 16-byte loads are read at element
+ * alignment.
  * Errors: PK_ERR_INVALID_ARG, PK_ERR_NO_FEASIBLE_BRANCH, PK_ERR_HIP. */
 int pk_measure(const pk_table *tbl, pk_dtype dtype, const void *A, int64_t lda, const void *B, int64_t ldb, void *C,
                int64_t ldc, int64_t M, int64_t N, int64_t K, pk_params *params_out, double *seconds_out, int cap,
@@ -278,8 +278,8 @@ int pk_measure(const pk_table *tbl, pk_dtype dtype, const void *A, int64_t lda, 
  * M == 0 or N == 0 is a no-op; K == 0 writes zeros (or leaves C unchanged
  * when accumulating).  MFMA programs load 16 bytes at a time along rows that
  * are aligned for it (A and B 16-byte aligned; lda and ldb multiples of 4
- * for f32, of 8 for bf16) and element by element otherwise -- the same
- * arithmetic in the same order, so the result does not depend on the
+ * for f32, of 8 for bf16), and at element alignment or element by element
+ * otherwise -- the same arithmetic in the same order, so the result does not depend on the
  * alignment.  One program
  * has no element-load form (the bfloat16 256 x 256 x 64 tile, whose
  * element-load kernel would spill); given it with operands whose rows are not
@@ -322,7 +322,7 @@ int pk_matmul(const pk_table *tbl, const pk_params *params_or_null, pk_dtype dty
  *     persistent one.
  * The tiles of a launch are ordered by estimated cost, most expensive first,
  * and cut into 8 ranges of equal estimated cost, one per XCD.  Rows that are
- * not aligned for the 16-byte loads are read with element loads.  The plan
+ * not aligned for the 16-byte loads are read at element alignment.  The plan
  * copies its descriptors to the device when created (allocating and
  * synchronizing then); running it allocates nothing and does not
  * synchronize, so it may be captured in a HIP graph.  Pointers must stay

@@ -28,15 +28,22 @@
 // so a lane's operands are contiguous in LDS.  The set of products summed is
 // unchanged.
 //
-// Global loads are 16 bytes wide, so the leading dimensions must keep rows
-// aligned (lda, ldb multiples of 4 floats / 8 bfloat16 and 16-byte aligned
-// bases); the host checks this and otherwise launches the element-load twin.
-// Tiles crossing the matrix edge
-// keep the wide loads: they clamp the rows of A and the column chunks of B
-// they read to the last chunk in range (results outside C are never stored),
-// zero the elements of A at k >= K, read the rows of B at k >= K from a block
-// of zeros, and guard their stores.  Edge loads choose an address, never a
-// loaded value, so they carry no branches and stay in flight together.
+// Global loads are 16 bytes wide in two kernels of every program: the wide one
+// for rows aligned for them (lda, ldb multiples of 4 floats / 8 bfloat16 and
+// 16-byte aligned bases), and its twin for all others, which reads the same
+// chunks at element alignment.  Row reads are bound by the loads in flight, so
+// 16 bytes a load pays whatever the alignment: the twins once loaded element
+// by element and took 1.4 (float32) and 3.5 (bfloat16) times the wide
+// programs' time; in chunks they take 1.00-1.03 and 1.05-1.25 times
+// (1024^3 to 4096^3; bfloat16 1021 x 3001 x 2047: 152 -> 40 us).
+// Tiles crossing the matrix edge keep the 16-byte loads in the twins and the
+// grouped kernels: they clamp the rows of A and the column chunks of B they
+// read to the last in range (results outside C are never stored), read the
+// rows of B at k >= K from a block of zeros, and guard their stores; the
+// elements of A at k >= K become zeros, and chunks across the end of an
+// unaligned row (read ending at its last element) are shifted into place,
+// when the chunks go to LDS.  Edge loads choose an address, never a loaded
+// value, so they carry no branches and stay in flight together.
 //
 // Workgroup -> tile map: workgroups are dispatched round-robin over the 8 XCDs
 // (each with its own L2); blocks b and b+8 land on the same XCD, so the map
@@ -63,6 +70,24 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 // space and would emit flat accesses (which also wait on the LDS counter).
 template <class T> using gptr = const __attribute__((address_space(1))) T *;
 template <class T> using gmut = __attribute__((address_space(1))) T *;
+
+// 16 bytes of a row: at a 16-byte boundary (rows aligned), or at any element
+// of EB bytes (one global load of 16 bytes either way: gfx950 reads global
+// memory at any byte address, a chunk that crosses a cache line as two).
+template <int EB, bool ALIGNED> struct ChunkAt { typedef u32x4 type; };
+template <> struct ChunkAt<4, false> { typedef unsigned int type __attribute__((ext_vector_type(4), aligned(4))); };
+template <> struct ChunkAt<2, false> { typedef unsigned int type __attribute__((ext_vector_type(4), aligned(2))); };
+
+// The elements of a chunk from element `s` on, zeros behind them (EB bytes an
+// element; s is uniform over the workgroup, 0 <= s < 16 / EB).
+template <int EB> __device__ __forceinline__ u32x4 chunk_from(u32x4 v, int s) {
+    const int d = EB == 4 ? s : s >> 1;
+    if (d & 1) v = u32x4{v[1], v[2], v[3], 0u};
+    if (d & 2) v = u32x4{v[2], v[3], 0u, 0u};
+    if (EB == 2 && (s & 1))
+        v = u32x4{v[0] >> 16 | v[1] << 16, v[1] >> 16 | v[2] << 16, v[2] >> 16 | v[3] << 16, v[3] >> 16};
+    return v;
+}
 
 // the source of every element at k >= K (read only)
 static __device__ __attribute__((aligned(16))) unsigned int kZeroBlock[4] = {0u, 0u, 0u, 0u};
@@ -96,15 +121,15 @@ template <int BM, int BN, int BK, int STAGES> struct F32Lds {
 
 // One BM x BN output tile at (row0, col0) over the K steps [kt0, kt1) (of
 // BK each), its A tiles at As0 (STAGES x F32Lds::A floats) and its B tiles
-// at Bs0 (STAGES x F32Lds::B floats) in LDS.  `vec`: the rows
-// of A and B are 16-byte aligned, so interior tiles may use 16-byte loads.
+// at Bs0 (STAGES x F32Lds::B floats) in LDS.  WIDE: the rows
+// of A and B are 16-byte aligned (else chunks are read at element alignment).
 // With a.splits > 1 the tile's sum over its K steps is added to C atomically
 // (C holds zeros or the sums of the other shares of K); otherwise it is
 // stored (added to C with a.accumulate).  The caller synchronises the
 // workgroup before reusing the LDS for another tile.
 
-template <int BM, int BN, int BK, int WM, int WN, int STAGES, bool EDGE_ADDR>
-__device__ __forceinline__ void mfma_f32_tile(const MmArgs &a, const int row0, const int col0, const bool vec,
+template <int BM, int BN, int BK, int WM, int WN, int STAGES, bool WIDE, bool EDGE_ADDR>
+__device__ __forceinline__ void mfma_f32_tile(const MmArgs &a, const int row0, const int col0,
                                               float *const As0, float *const Bs0, const int kt0,
                                               const int kt1) {
     constexpr int NT = 64 * WM * WN;
@@ -125,6 +150,7 @@ __device__ __forceinline__ void mfma_f32_tile(const MmArgs &a, const int row0, c
     // and guards serve a whole product and a share of one)
     const gptr<float> __restrict__ A = (gptr<float>)a.A + kt0 * BK;
     const gptr<float> __restrict__ B = (gptr<float>)a.B + (int64_t)kt0 * BK * a.ldb;
+    const gptr<uint32_t> Aw = (gptr<uint32_t>)A, Bw = (gptr<uint32_t>)B;  // the same words, as bits
     const gmut<float> __restrict__ C = (gmut<float>)a.C;
     const int M = a.M, N = a.N, K = a.K - kt0 * BK;
     const int tid = threadIdx.x;
@@ -147,37 +173,45 @@ __device__ __forceinline__ void mfma_f32_tile(const MmArgs &a, const int row0, c
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 
-    f32x4 ra[A4], rb[B4];
-    // a K step that lies wholly inside aligned operands: no guards, so the
-    // loads issue back to back (guarded loads branch per load, and the
-    // compiler then waits for each load before the next)
+    u32x4 ra[A4], rb[B4];
+    typedef typename ChunkAt<4, WIDE>::type chunk;
+    // a K step that lies wholly inside the operands: no guards, so the loads
+    // issue back to back (guarded loads branch per load, and the compiler
+    // then waits for each load before the next)
     auto gload_fast = [&](int k0) {
 #pragma unroll
         for (int u = 0; u < A4; ++u) {
             const int f = tid + u * NT;
             const int rr = f / (BK / 4), c4 = (f % (BK / 4)) * 4;
-            ra[u] = *reinterpret_cast<gptr<f32x4>>(A + (int64_t)(row0 + rr) * a.lda + k0 + c4);
+            ra[u] = *reinterpret_cast<gptr<chunk>>(A + (int64_t)(row0 + rr) * a.lda + k0 + c4);
         }
 #pragma unroll
         for (int u = 0; u < B4; ++u) {
             const int f = tid + u * NT;
             const int rr = f / (BN / 4), c4 = (f % (BN / 4)) * 4;
-            rb[u] = *reinterpret_cast<gptr<f32x4>>(B + (int64_t)(k0 + rr) * a.ldb + col0 + c4);
+            rb[u] = *reinterpret_cast<gptr<chunk>>(B + (int64_t)(k0 + rr) * a.ldb + col0 + c4);
         }
     };
     // Any K step, edge tiles included.  Without EDGE_ADDR: guarded loads
     // (16 bytes where the chunk is wholly inside the matrix, else element by
     // element), which hold fewer registers where edge steps are rare.
-    // EDGE_ADDR, for programs whose steps are mostly edge steps (many small
-    // products): every load goes to a chosen address.  Aligned rows (vec):
-    // 16-byte loads at addresses clamped into the matrix.
-    // Rows of A past M read row M - 1 and columns of B past N read the chunk
-    // holding column N - 1 (their results are never stored); in a step past
-    // the end of K, A's chunks past k = K - 1 read the chunk holding it and
-    // the elements at k >= K become zeros, and the rows of B at k >= K read a
-    // block of zeros.  Every chunk read holds an element of the matrix, so it
-    // lies inside its aligned row.
-    // Unaligned rows: element loads.
+    // EDGE_ADDR: every load is a 16-byte chunk at a chosen address, and what
+    // the chunk has to be changed into happens when it goes to LDS (sstore),
+    // so these loads stay in flight during the products too.  Rows of A past
+    // M read row M - 1 and columns of B past N a chunk inside N (their
+    // results are never stored); rows of B at k >= K read a block of zeros.
+    // Aligned rows: a chunk across k = K or column N is read whole (it holds
+    // an element of the matrix, so it lies inside its aligned row).
+    // Unaligned rows: such a chunk is read ending at the row's last element
+    // and shifted down by sk (A) or sn (B) elements later.  Unaligned rows
+    // shorter than a chunk (tiny): element loads.
+    // CHUNKS false: the float32 twins of the large single-stage tiles keep
+    // element loads, since the wide form of their guards would spill at their
+    // register cap.
+    constexpr bool CHUNKS = WIDE || EDGE_ADDR || WM * WN >= 16;
+    const bool tiny = !WIDE && (a.K < 4 || N < 4);
+    const int sk = WIDE ? 0 : (4 - (K & 3)) & 3, sn = WIDE ? 0 : (4 - (N & 3)) & 3;
+    const int klast = WIDE ? (K - 1) & ~3 : K - 4, nlast = WIDE ? (N - 1) & ~3 : N - 4;
     auto gload = [&](int k0) {
         if constexpr (!EDGE_ADDR) {
             const bool kfull = (k0 + BK <= K);
@@ -186,12 +220,12 @@ __device__ __forceinline__ void mfma_f32_tile(const MmArgs &a, const int row0, c
                 const int f = tid + u * NT;
                 const int rr = f / (BK / 4), c4 = (f % (BK / 4)) * 4;
                 const int gr = row0 + rr, gc = k0 + c4;
-                if (vec && kfull && gr < M) {
-                    ra[u] = *reinterpret_cast<gptr<f32x4>>(A + (int64_t)gr * a.lda + gc);
+                if (CHUNKS && kfull && gr < M) {
+                    ra[u] = *reinterpret_cast<gptr<chunk>>(A + (int64_t)gr * a.lda + gc);
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        ra[u][e] = (gr < M && gc + e < K) ? A[(int64_t)gr * a.lda + gc + e] : 0.0f;
+                        ra[u][e] = (gr < M && gc + e < K) ? Aw[(int64_t)gr * a.lda + gc + e] : 0u;
                 }
             }
 #pragma unroll
@@ -199,53 +233,40 @@ __device__ __forceinline__ void mfma_f32_tile(const MmArgs &a, const int row0, c
                 const int f = tid + u * NT;
                 const int rr = f / (BN / 4), c4 = (f % (BN / 4)) * 4;
                 const int gr = k0 + rr, gc = col0 + c4;
-                if (vec && gr < K && gc + 4 <= N) {
-                    rb[u] = *reinterpret_cast<gptr<f32x4>>(B + (int64_t)gr * a.ldb + gc);
+                if (CHUNKS && gr < K && gc + 4 <= N) {
+                    rb[u] = *reinterpret_cast<gptr<chunk>>(B + (int64_t)gr * a.ldb + gc);
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        rb[u][e] = (gr < K && gc + e < N) ? B[(int64_t)gr * a.ldb + gc + e] : 0.0f;
+                        rb[u][e] = (gr < K && gc + e < N) ? Bw[(int64_t)gr * a.ldb + gc + e] : 0u;
                 }
             }
             return;
         }
-        const gptr<float> zero = (gptr<float>)(const void *)kZeroBlock;
-        if (vec) {
-            const int klast = (K - 1) & ~3, nlast = (N - 1) & ~3;
-            if (k0 + BK <= K) {
+        if (!tiny) {
 #pragma unroll
-                for (int u = 0; u < A4; ++u) {
-                    const int f = tid + u * NT;
-                    const int rr = f / (BK / 4), c4 = (f % (BK / 4)) * 4;
-                    ra[u] = *reinterpret_cast<gptr<f32x4>>(A + (int64_t)min(row0 + rr, M - 1) * a.lda + k0 + c4);
-                }
-            } else {
-#pragma unroll
-                for (int u = 0; u < A4; ++u) {
-                    const int f = tid + u * NT;
-                    const int rr = f / (BK / 4), c4 = (f % (BK / 4)) * 4;
-                    const int k = k0 + c4;
-                    f32x4 v = *reinterpret_cast<gptr<f32x4>>(A + (int64_t)min(row0 + rr, M - 1) * a.lda +
-                                                             min(k, klast));
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = k + e < K ? v[e] : 0.0f;
-                    ra[u] = v;
-                }
+            for (int u = 0; u < A4; ++u) {
+                const int f = tid + u * NT;
+                const int rr = f / (BK / 4), c4 = (f % (BK / 4)) * 4;
+                ra[u] = *reinterpret_cast<gptr<chunk>>(A + (int64_t)min(row0 + rr, M - 1) * a.lda +
+                                                       min(k0 + c4, klast));
             }
 #pragma unroll
             for (int u = 0; u < B4; ++u) {
                 const int f = tid + u * NT;
                 const int rr = f / (BN / 4), c4 = (f % (BN / 4)) * 4;
                 const int k = k0 + rr;
-                rb[u] = *reinterpret_cast<gptr<f32x4>>(k < K ? B + (int64_t)k * a.ldb + min(col0 + c4, nlast) : zero);
+                rb[u] = *(k < K ? reinterpret_cast<gptr<chunk>>(B + (int64_t)k * a.ldb + min(col0 + c4, nlast))
+                                : (gptr<chunk>)(const void *)kZeroBlock);
             }
             return;
         }
+        const gptr<uint32_t> zero = (gptr<uint32_t>)(const void *)kZeroBlock;
 #pragma unroll
         for (int u = 0; u < A4; ++u) {
             const int f = tid + u * NT;
             const int rr = f / (BK / 4), c4 = (f % (BK / 4)) * 4;
-            const gptr<float> row = A + (int64_t)min(row0 + rr, M - 1) * a.lda;
+            const gptr<uint32_t> row = Aw + (int64_t)min(row0 + rr, M - 1) * a.lda;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int k = k0 + c4 + e;
@@ -257,9 +278,37 @@ __device__ __forceinline__ void mfma_f32_tile(const MmArgs &a, const int row0, c
             const int f = tid + u * NT;
             const int rr = f / (BN / 4), c4 = (f % (BN / 4)) * 4;
             const int k = k0 + rr;
-            const gptr<float> row = k < K ? B + (int64_t)k * a.ldb : nullptr;
+            const gptr<uint32_t> row = k < K ? Bw + (int64_t)k * a.ldb : nullptr;
 #pragma unroll
             for (int e = 0; e < 4; ++e) rb[u][e] = *(row ? row + min(col0 + c4 + e, N - 1) : zero);
+        }
+    };
+    // what the chunks of an edge step at k0 become before they go to LDS
+    auto fixup = [&](int k0) {
+        if constexpr (!EDGE_ADDR) return;
+        if (tiny) return;
+        if (k0 + BK > K) {
+#pragma unroll
+            for (int u = 0; u < A4; ++u) {
+                const int k = k0 + ((tid + u * NT) % (BK / 4)) * 4;
+                if constexpr (WIDE) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) ra[u][e] = k + e < K ? ra[u][e] : 0u;
+                } else {
+                    const u32x4 t = chunk_from<4>(ra[u], sk);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) ra[u][e] = k + 4 <= K ? ra[u][e] : k < K ? t[e] : 0u;
+                }
+            }
+        }
+        if (!WIDE && sn && col0 + BN > N) {
+#pragma unroll
+            for (int u = 0; u < B4; ++u) {
+                const u32x4 t = chunk_from<4>(rb[u], sn);
+                const bool whole = col0 + ((tid + u * NT) % (BN / 4)) * 4 + 4 <= N;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) rb[u][e] = whole ? rb[u][e] : t[e];
+            }
         }
     };
     auto sstore = [&](int st) {
@@ -267,13 +316,13 @@ __device__ __forceinline__ void mfma_f32_tile(const MmArgs &a, const int row0, c
         for (int u = 0; u < A4; ++u) {
             const int f = tid + u * NT;
             const int rr = f / (BK / 4), c4 = (f % (BK / 4)) * 4;
-            *reinterpret_cast<f32x4 *>(&As0[st * L::A + rr * LDA_S + c4]) = ra[u];
+            *reinterpret_cast<u32x4 *>(&As0[st * L::A + rr * LDA_S + c4]) = ra[u];
         }
 #pragma unroll
         for (int u = 0; u < B4; ++u) {
             const int f = tid + u * NT;
             const int rr = f / (BN / 4), c4 = (f % (BN / 4)) * 4;
-            *reinterpret_cast<f32x4 *>(&Bs0[st * L::B + rr * LDB_S + c4]) = rb[u];
+            *reinterpret_cast<u32x4 *>(&Bs0[st * L::B + rr * LDB_S + c4]) = rb[u];
         }
     };
     auto compute = [&](int st) {
@@ -303,13 +352,15 @@ __device__ __forceinline__ void mfma_f32_tile(const MmArgs &a, const int row0, c
     // along K).  Leading steps that need no guards: all of them for an
     // interior tile on aligned rows, except a partial last one.
     const int KT = kt1 - kt0;
-    const int KF = (vec && interior) ? min(K / BK, KT) : 0;
+    const int KF = CHUNKS && interior ? min(K / BK, KT) : 0;
     if (STAGES == 2) {
         if (KT > 0) {
-            if (KF > 0)
+            if (KF > 0) {
                 gload_fast(0);
-            else
+            } else {
                 gload(0);
+                fixup(0);
+            }
             sstore(0);
         }
         __syncthreads();
@@ -329,7 +380,10 @@ __device__ __forceinline__ void mfma_f32_tile(const MmArgs &a, const int row0, c
             if (kt + 1 < KT) gload((kt + 1) * BK);
             if constexpr (PIN) __builtin_amdgcn_sched_barrier(0);
             if (!idle) compute(cur);
-            if (kt + 1 < KT) sstore(cur ^ 1);
+            if (kt + 1 < KT) {
+                fixup((kt + 1) * BK);
+                sstore(cur ^ 1);
+            }
             __syncthreads();
         }
     } else {
@@ -351,6 +405,7 @@ __device__ __forceinline__ void mfma_f32_tile(const MmArgs &a, const int row0, c
             compute(0);
         }
         for (; kt < KT; ++kt) {
+            if (kt >= KF) fixup(kt * BK);
             __syncthreads();
             sstore(0);
             __syncthreads();
@@ -403,9 +458,9 @@ __device__ __forceinline__ s16x4 lds_read_tr16(const unsigned short *p) {
 }
 
 // bfloat16 tile, its A tiles at As0 (STAGES x Bf16Lds::A elements) and its B
-// tiles at Bs0 (STAGES x Bf16Lds::B); `vec`: A and B rows 16-byte aligned.
-template <int BM, int BN, int BK, int WM, int WN, int STAGES, bool EDGE_ADDR>
-__device__ __forceinline__ void mfma_bf16_tile(const MmArgs &a, const int row0, const int col0, const bool vec,
+// tiles at Bs0 (STAGES x Bf16Lds::B); WIDE: A and B rows 16-byte aligned.
+template <int BM, int BN, int BK, int WM, int WN, int STAGES, bool WIDE, bool EDGE_ADDR>
+__device__ __forceinline__ void mfma_bf16_tile(const MmArgs &a, const int row0, const int col0,
                                                unsigned short *const As0, unsigned short *const Bs0,
                                                const int kt0, const int kt1) {
     constexpr int NT = 64 * WM * WN;
@@ -450,22 +505,27 @@ __device__ __forceinline__ void mfma_bf16_tile(const MmArgs &a, const int row0, 
     // work-item f of the workgroup's u-th load: A row f / (BK / 8), its k
     // chunk (f % (BK / 8)) * 8; B row (k) f / (BN / 8), its column chunk
     // (f % (BN / 8)) * 8
-    u16x8 ra[A8], rb[B8];
+    u32x4 ra[A8], rb[B8];
+    typedef typename ChunkAt<2, WIDE>::type chunk;
     auto gload_fast = [&](int k0) {  // unguarded, as in the float32 tile
 #pragma unroll
         for (int u = 0; u < A8; ++u) {
             const int f = tid + u * NT;
             const int rr = f / (BK / 8), c8 = (f % (BK / 8)) * 8;
-            ra[u] = *reinterpret_cast<gptr<u16x8>>(A + (int64_t)(row0 + rr) * a.lda + k0 + c8);
+            ra[u] = *reinterpret_cast<gptr<chunk>>(A + (int64_t)(row0 + rr) * a.lda + k0 + c8);
         }
 #pragma unroll
         for (int u = 0; u < B8; ++u) {
             const int f = tid + u * NT;
             const int rr = f / (BN / 8), c8 = (f % (BN / 8)) * 8;
-            rb[u] = *reinterpret_cast<gptr<u16x8>>(B + (int64_t)(k0 + rr) * a.ldb + col0 + c8);
+            rb[u] = *reinterpret_cast<gptr<chunk>>(B + (int64_t)(k0 + rr) * a.ldb + col0 + c8);
         }
     };
-    auto gload = [&](int k0) {  // any K step: as in the float32 tile
+    // any K step, and the chunks of edge steps: as in the float32 tile
+    const bool tiny = !WIDE && (a.K < 8 || N < 8);
+    const int sk = WIDE ? 0 : (8 - (K & 7)) & 7, sn = WIDE ? 0 : (8 - (N & 7)) & 7;
+    const int klast = WIDE ? (K - 1) & ~7 : K - 8, nlast = WIDE ? (N - 1) & ~7 : N - 8;
+    auto gload = [&](int k0) {
         if constexpr (!EDGE_ADDR) {
             const bool kfull = (k0 + BK <= K);
 #pragma unroll
@@ -473,12 +533,14 @@ __device__ __forceinline__ void mfma_bf16_tile(const MmArgs &a, const int row0, 
                 const int f = tid + u * NT;
                 const int rr = f / (BK / 8), c8 = (f % (BK / 8)) * 8;
                 const int gr = row0 + rr, gc = k0 + c8;
-                if (vec && kfull && gr < M) {
-                    ra[u] = *reinterpret_cast<gptr<u16x8>>(A + (int64_t)gr * a.lda + gc);
+                if (kfull && gr < M) {
+                    ra[u] = *reinterpret_cast<gptr<chunk>>(A + (int64_t)gr * a.lda + gc);
                 } else {
+                    u16x8 v;
 #pragma unroll
                     for (int e = 0; e < 8; ++e)
-                        ra[u][e] = (gr < M && gc + e < K) ? A[(int64_t)gr * a.lda + gc + e] : (unsigned short)0;
+                        v[e] = (gr < M && gc + e < K) ? A[(int64_t)gr * a.lda + gc + e] : (unsigned short)0;
+                    ra[u] = __builtin_bit_cast(u32x4, v);
                 }
             }
 #pragma unroll
@@ -486,65 +548,49 @@ __device__ __forceinline__ void mfma_bf16_tile(const MmArgs &a, const int row0, 
                 const int f = tid + u * NT;
                 const int rr = f / (BN / 8), c8 = (f % (BN / 8)) * 8;
                 const int gr = k0 + rr, gc = col0 + c8;
-                if (vec && gr < K && gc + 8 <= N) {
-                    rb[u] = *reinterpret_cast<gptr<u16x8>>(B + (int64_t)gr * a.ldb + gc);
+                if (gr < K && gc + 8 <= N) {
+                    rb[u] = *reinterpret_cast<gptr<chunk>>(B + (int64_t)gr * a.ldb + gc);
                 } else {
+                    u16x8 v;
 #pragma unroll
                     for (int e = 0; e < 8; ++e)
-                        rb[u][e] = (gr < K && gc + e < N) ? B[(int64_t)gr * a.ldb + gc + e] : (unsigned short)0;
+                        v[e] = (gr < K && gc + e < N) ? B[(int64_t)gr * a.ldb + gc + e] : (unsigned short)0;
+                    rb[u] = __builtin_bit_cast(u32x4, v);
                 }
             }
             return;
         }
-        const gptr<unsigned short> zero = (gptr<unsigned short>)(const void *)kZeroBlock;
-        if (vec) {
-            // aligned rows: 16-byte chunks at chosen addresses.  A rows past M
-            // repeat row M - 1 and B chunks past N the row's last chunk (their
-            // products land outside C); B rows past K read the zero block; the
-            // chunk holding A's k tail is masked
-            const int klast = (K - 1) & ~7, nlast = (N - 1) & ~7;
-            if (k0 + BK <= K) {
+        if (!tiny) {
 #pragma unroll
-                for (int u = 0; u < A8; ++u) {
-                    const int f = tid + u * NT;
-                    const int rr = f / (BK / 8), c8 = (f % (BK / 8)) * 8;
-                    ra[u] = *reinterpret_cast<gptr<u16x8>>(A + (int64_t)min(row0 + rr, M - 1) * a.lda + k0 + c8);
-                }
-            } else {
-#pragma unroll
-                for (int u = 0; u < A8; ++u) {
-                    const int f = tid + u * NT;
-                    const int rr = f / (BK / 8), c8 = (f % (BK / 8)) * 8;
-                    const int k = k0 + c8;
-                    u32x4 v = *reinterpret_cast<gptr<u32x4>>(A + (int64_t)min(row0 + rr, M - 1) * a.lda +
-                                                             min(k, klast));
-                    // word w holds k + 2w (low half) and k + 2w + 1 (high half)
-#pragma unroll
-                    for (int w = 0; w < 4; ++w)
-                        v[w] &= k + 2 * w + 1 < K ? 0xffffffffu : (k + 2 * w < K ? 0x0000ffffu : 0u);
-                    ra[u] = __builtin_bit_cast(u16x8, v);
-                }
+            for (int u = 0; u < A8; ++u) {
+                const int f = tid + u * NT;
+                const int rr = f / (BK / 8), c8 = (f % (BK / 8)) * 8;
+                ra[u] = *reinterpret_cast<gptr<chunk>>(A + (int64_t)min(row0 + rr, M - 1) * a.lda +
+                                                       min(k0 + c8, klast));
             }
 #pragma unroll
             for (int u = 0; u < B8; ++u) {
                 const int f = tid + u * NT;
                 const int rr = f / (BN / 8), c8 = (f % (BN / 8)) * 8;
                 const int k = k0 + rr;
-                rb[u] = *(k < K ? reinterpret_cast<gptr<u16x8>>(B + (int64_t)k * a.ldb + min(col0 + c8, nlast))
-                                : (gptr<u16x8>)(const void *)kZeroBlock);
+                rb[u] = *(k < K ? reinterpret_cast<gptr<chunk>>(B + (int64_t)k * a.ldb + min(col0 + c8, nlast))
+                                : (gptr<chunk>)(const void *)kZeroBlock);
             }
             return;
         }
+        const gptr<unsigned short> zero = (gptr<unsigned short>)(const void *)kZeroBlock;
 #pragma unroll
         for (int u = 0; u < A8; ++u) {
             const int f = tid + u * NT;
             const int rr = f / (BK / 8), c8 = (f % (BK / 8)) * 8;
             const gptr<unsigned short> row = A + (int64_t)min(row0 + rr, M - 1) * a.lda;
+            u16x8 v;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const int k = k0 + c8 + e;
-                ra[u][e] = *(k < K ? row + k : zero);
+                v[e] = *(k < K ? row + k : zero);
             }
+            ra[u] = __builtin_bit_cast(u32x4, v);
         }
 #pragma unroll
         for (int u = 0; u < B8; ++u) {
@@ -552,8 +598,39 @@ __device__ __forceinline__ void mfma_bf16_tile(const MmArgs &a, const int row0, 
             const int rr = f / (BN / 8), c8 = (f % (BN / 8)) * 8;
             const int k = k0 + rr;
             const gptr<unsigned short> row = k < K ? B + (int64_t)k * a.ldb : nullptr;
+            u16x8 v;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) rb[u][e] = *(row ? row + min(col0 + c8 + e, N - 1) : zero);
+            for (int e = 0; e < 8; ++e) v[e] = *(row ? row + min(col0 + c8 + e, N - 1) : zero);
+            rb[u] = __builtin_bit_cast(u32x4, v);
+        }
+    };
+    // what the chunks of an edge step at k0 become before they go to LDS
+    auto fixup = [&](int k0) {
+        if constexpr (!EDGE_ADDR) return;
+        if (tiny) return;
+        if (k0 + BK > K) {
+#pragma unroll
+            for (int u = 0; u < A8; ++u) {
+                const int k = k0 + ((tid + u * NT) % (BK / 8)) * 8;
+                if constexpr (WIDE) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)  // word e holds k + 2e (low half) and k + 2e + 1 (high half)
+                        ra[u][e] &= k + 2 * e + 1 < K ? 0xffffffffu : (k + 2 * e < K ? 0x0000ffffu : 0u);
+                } else {
+                    const u32x4 t = chunk_from<2>(ra[u], sk);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) ra[u][e] = k + 8 <= K ? ra[u][e] : k < K ? t[e] : 0u;
+                }
+            }
+        }
+        if (!WIDE && sn && col0 + BN > N) {
+#pragma unroll
+            for (int u = 0; u < B8; ++u) {
+                const u32x4 t = chunk_from<2>(rb[u], sn);
+                const bool whole = col0 + ((tid + u * NT) % (BN / 8)) * 8 + 8 <= N;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) rb[u][e] = whole ? rb[u][e] : t[e];
+            }
         }
     };
     auto sstore = [&](int st) {
@@ -561,13 +638,13 @@ __device__ __forceinline__ void mfma_bf16_tile(const MmArgs &a, const int row0, 
         for (int u = 0; u < A8; ++u) {
             const int f = tid + u * NT;
             const int rr = f / (BK / 8), c8 = (f % (BK / 8)) * 8;
-            *reinterpret_cast<u16x8 *>(&As0[st * L::A + rr * LD_S + c8]) = ra[u];
+            *reinterpret_cast<u32x4 *>(&As0[st * L::A + rr * LD_S + c8]) = ra[u];
         }
 #pragma unroll
         for (int u = 0; u < B8; ++u) {
             const int f = tid + u * NT;
             const int rr = f / (BN / 8), c8 = (f % (BN / 8)) * 8;
-            *reinterpret_cast<u16x8 *>(&Bs0[st * L::B + rr * LDB_S + c8]) = rb[u];
+            *reinterpret_cast<u32x4 *>(&Bs0[st * L::B + rr * LDB_S + c8]) = rb[u];
         }
     };
     // lane (r, h) multiplies A row r and B column r over k = h BK/2 + kc + t,
@@ -603,13 +680,15 @@ __device__ __forceinline__ void mfma_bf16_tile(const MmArgs &a, const int row0, 
     // along K).  Leading steps that need no guards: all of them for an
     // interior tile on aligned rows, except a partial last one.
     const int KT = kt1 - kt0;
-    const int KF = (vec && interior) ? min(K / BK, KT) : 0;
+    const int KF = interior ? min(K / BK, KT) : 0;
     if (STAGES == 2) {
         if (KT > 0) {
-            if (KF > 0)
+            if (KF > 0) {
                 gload_fast(0);
-            else
+            } else {
                 gload(0);
+                fixup(0);
+            }
             sstore(0);
         }
         __syncthreads();
@@ -629,7 +708,10 @@ __device__ __forceinline__ void mfma_bf16_tile(const MmArgs &a, const int row0, 
             if (kt + 1 < KT) gload((kt + 1) * BK);
             if constexpr (PIN) __builtin_amdgcn_sched_barrier(0);
             if (!idle) compute(cur);
-            if (kt + 1 < KT) sstore(cur ^ 1);
+            if (kt + 1 < KT) {
+                fixup((kt + 1) * BK);
+                sstore(cur ^ 1);
+            }
             __syncthreads();
         }
     } else {
@@ -651,6 +733,7 @@ __device__ __forceinline__ void mfma_bf16_tile(const MmArgs &a, const int row0, 
             compute(0);
         }
         for (; kt < KT; ++kt) {
+            if (kt >= KF) fixup(kt * BK);
             __syncthreads();
             sstore(0);
             __syncthreads();
@@ -699,9 +782,10 @@ __device__ __forceinline__ void k_share(const MmArgs &a, int64_t tiles, int64_t 
 }
 
 // WIDE: 16-byte loads along aligned rows; the element-load twin (WIDE =
-// false) is a kernel of its own, so neither carries the other's load path.
-// The twins of workgroups up to 256 work-items load at chosen addresses (all
-// their steps take the edge path).  SPLIT: the kernel runs shares of K
+// false: 16-byte loads at element alignment) is a kernel of its own, so
+// neither carries the other's load path.  The twins load edge chunks at chosen
+// addresses, but for float32 tiles whose fixups would spill at their register
+// cap.  SPLIT: the kernel runs shares of K
 // (a.splits > 1); the wide program's split form is a kernel of its own too,
 // so the whole-product kernel carries none of it (the element-load twins,
 // already off the fast path, split in place).
@@ -717,7 +801,9 @@ __device__ __forceinline__ void mfma_f32(const MmArgs &a0) {
     int kt0, kt1;
     k_share<BK>(a, (int64_t)((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN), &b, &kt0, &kt1);
     tile_of(b, (a.M + BM - 1) / BM, (a.N + BN - 1) / BN, &tm, &tn);
-    mfma_f32_tile<BM, BN, BK, WM, WN, STAGES, !WIDE && WM * WN < 8>(a, tm * BM, tn * BN, WIDE, As, Bs, kt0, kt1);
+    mfma_f32_tile<BM, BN, BK, WM, WN, STAGES, WIDE,
+                  !WIDE && WM * WN < 16 && (STAGES == 2 || BM * BN * BK <= 128 * 256 * 16)>(a, tm * BM, tn * BN, As, Bs, kt0,
+                                                                                            kt1);
 }
 
 template <int BM, int BN, int BK, int WM, int WN, int STAGES, bool WIDE = true, bool SPLIT = !WIDE>
@@ -732,7 +818,7 @@ __device__ __forceinline__ void mfma_bf16(const MmArgs &a0) {
     int kt0, kt1;
     k_share<BK>(a, (int64_t)((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN), &b, &kt0, &kt1);
     tile_of(b, (a.M + BM - 1) / BM, (a.N + BN - 1) / BN, &tm, &tn);
-    mfma_bf16_tile<BM, BN, BK, WM, WN, STAGES, !WIDE && WM * WN < 8>(a, tm * BM, tn * BN, WIDE, As, Bs, kt0, kt1);
+    mfma_bf16_tile<BM, BN, BK, WM, WN, STAGES, WIDE, !WIDE>(a, tm * BM, tn * BN, As, Bs, kt0, kt1);
 }
 
 // ------------------------------------------------------------------ grouped (persistent)
@@ -816,7 +902,7 @@ __device__ __forceinline__ void grouped_f32(const GroupArgs &g) {
     walk_tiles(g, [&](const GroupDesc &d, int local) {
         const int tm = local / d.tiles_n, tn = local % d.tiles_n;
         const MmArgs a{d.A, d.B, d.C, d.lda, d.ldb, d.ldc, d.M, d.N, d.K, g.accumulate, WIDE};
-        mfma_f32_tile<BM, BN, BK, WM, WN, STAGES, true>(a, tm * BM, tn * BN, WIDE, As, Bs, 0, (d.K + BK - 1) / BK);
+        mfma_f32_tile<BM, BN, BK, WM, WN, STAGES, WIDE, true>(a, tm * BM, tn * BN, As, Bs, 0, (d.K + BK - 1) / BK);
     });
 }
 
@@ -828,7 +914,7 @@ __device__ __forceinline__ void grouped_bf16(const GroupArgs &g) {
     walk_tiles(g, [&](const GroupDesc &d, int local) {
         const int tm = local / d.tiles_n, tn = local % d.tiles_n;
         const MmArgs a{d.A, d.B, d.C, d.lda, d.ldb, d.ldc, d.M, d.N, d.K, g.accumulate, WIDE};
-        mfma_bf16_tile<BM, BN, BK, WM, WN, STAGES, true>(a, tm * BM, tn * BN, WIDE, As, Bs, 0, (d.K + BK - 1) / BK);
+        mfma_bf16_tile<BM, BN, BK, WM, WN, STAGES, WIDE, true>(a, tm * BM, tn * BN, As, Bs, 0, (d.K + BK - 1) / BK);
     });
 }
 
@@ -854,7 +940,7 @@ __device__ __forceinline__ void mixed_f32_tile(const MmArgs &a, int local, int t
     constexpr int BM = kMixedTile[P][0], BN = kMixedTile[P][1];
     const int tm = local / tiles_n, tn = local % tiles_n;
     using L = F32Lds<BM, BN, kMixedBk[0], STAGES>;
-    mfma_f32_tile<BM, BN, kMixedBk[0], 2, 2, STAGES, true>(a, tm * BM, tn * BN, WIDE, lds,
+    mfma_f32_tile<BM, BN, kMixedBk[0], 2, 2, STAGES, WIDE, true>(a, tm * BM, tn * BN, lds,
                                                            lds + STAGES * L::A, 0,
                                                            (a.K + kMixedBk[0] - 1) / kMixedBk[0]);
 }
@@ -864,7 +950,7 @@ __device__ __forceinline__ void mixed_bf16_tile(const MmArgs &a, int local, int 
     constexpr int BM = kMixedTile[P][0], BN = kMixedTile[P][1];
     const int tm = local / tiles_n, tn = local % tiles_n;
     using L = Bf16Lds<BM, BN, kMixedBk[2], STAGES>;
-    mfma_bf16_tile<BM, BN, kMixedBk[2], 2, 2, STAGES, true>(a, tm * BM, tn * BN, WIDE, lds,
+    mfma_bf16_tile<BM, BN, kMixedBk[2], 2, 2, STAGES, WIDE, true>(a, tm * BM, tn * BN, lds,
                                                             lds + STAGES * L::A, 0,
                                                             (a.K + kMixedBk[2] - 1) / kMixedBk[2]);
 }
