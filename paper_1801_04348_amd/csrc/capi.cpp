@@ -51,10 +51,9 @@ int resolve(const pk_table *tbl, const pk_params *pin, int dtype, pk_params *pou
     int variant = pin->variant;
     if (leaf >= 0) {
         if (leaf >= (int)part->solved.leaves.size()) return fail(PK_ERR_INVALID_ARG, "leaf index out of range");
-        const Leaf &L = part->solved.leaves[leaf];
-        if (!system_holds(part->fam, L.C, pt, part->mvals))
+        if (!part->holds[(size_t)leaf * part->fam.points.size() + idx])
             return fail(PK_ERR_NO_FEASIBLE_BRANCH, "the leaf's system does not hold at these parameters");
-        variant = (int)L.applied;
+        variant = (int)part->solved.leaves[leaf].applied;
     } else if (variant >= 0) {
         if (!variant_fits(part->fam, (uint32_t)variant, pt, part->mvals))
             return fail(PK_ERR_NO_FEASIBLE_BRANCH, "the variant does not fit the machine at these parameters");
@@ -63,7 +62,9 @@ int resolve(const pk_table *tbl, const pk_params *pin, int dtype, pk_params *pou
         if (leaf < 0) return fail(PK_ERR_NO_FEASIBLE_BRANCH, "no leaf of the case table holds at these parameters");
         variant = (int)part->solved.leaves[leaf].applied;
     }
-    const KernelEntry *e = find_instance(pin->family, variant, dtype, pt);
+    const auto &prog = part->programs[idx];
+    const KernelEntry *e = prog.entry && prog.variant == variant ? prog.entry
+                                                                 : find_instance(pin->family, variant, dtype, pt);
     if (!e) return fail(PK_ERR_NOT_INSTANTIATED, "no compiled instance for these parameters");
     if (pin->ks < 0 || pin->ks > kMaxSplits || (pin->ks > 1 && !split_twin(*e)))
         return fail(PK_ERR_INVALID_ARG, "ks: shares of K are 0 or 1 (none), or up to " + std::to_string(kMaxSplits) +
@@ -84,7 +85,7 @@ int resolve(const pk_table *tbl, const pk_params *pin, int dtype, pk_params *pou
 // more than max_threads_cu / max_threads_block, a figure that only describes
 // full-size workgroups (one HIP runtime reports 2 for gfx950, another 32).
 int64_t blocks_per_cu(const pk_machine &m, const KernelEntry &e) {
-    const KernelResources *r = resources_of(e.name);
+    const KernelResources *r = resources_of(e);
     const int64_t wave = m.wave > 0 ? m.wave : 64;
     const int64_t waves = (e.threads + wave - 1) / wave;
     int64_t b = m.max_threads_cu > 0 ? std::max<int64_t>(1, m.max_threads_cu / wave) / waves : 32;
@@ -188,6 +189,13 @@ int launch(const pk_machine &m, const KernelEntry &e0, const MmArgs &args, hipSt
 
 using namespace pk;
 
+// pk_matmul's CASE choices in the table's cache: first key component by
+// element type and row alignment, beside pk_select's (the element type), the
+// other families' (100 ..), and at most this many entries in all: a program
+// that meets new sizes without end chooses anew (about 10 us) beyond it
+constexpr int kCaseWide = 1000, kCaseNarrow = 1010;
+constexpr size_t kMaxCachedCase = 1 << 16;
+
 // ------------------------------------------------------------------ table
 const pk_table::Part *pk_table::part(int family, int dtype) const {
     for (const auto &p : parts)
@@ -272,13 +280,27 @@ int pk_case_table_build(int device, const pk_machine *override_or_null, pk_table
                     part.fam = matmul_family(family, dtype);
                     part.solved = comprehensive_optimization(part.fam);
                     part.mvals = machine_values(part.fam, m);
-                    part.first_leaf.assign(part.fam.points.size(), -1);
-                    for (size_t i = 0; i < part.fam.points.size(); ++i)
-                        for (size_t l = 0; l < part.solved.leaves.size(); ++l)
+                    const size_t np = part.fam.points.size(), nl = part.solved.leaves.size();
+                    part.first_leaf.assign(np, -1);
+                    part.programs.assign(np, {});
+                    part.holds.assign(np * nl, 0);
+                    for (size_t i = 0; i < np; ++i) {
+                        for (size_t l = nl; l-- > 0;)
                             if (system_holds(part.fam, part.solved.leaves[l].C, part.fam.points[i], part.mvals)) {
+                                part.holds[l * np + i] = 1;
                                 part.first_leaf[i] = (int)l;
-                                break;
                             }
+                        if (part.first_leaf[i] < 0) continue;
+                        auto &p = part.programs[i];
+                        p.variant = (int)part.solved.leaves[part.first_leaf[i]].applied;
+                        p.entry = find_instance(family, p.variant, dtype, part.fam.points[i]);
+                        if (!p.entry) continue;
+                        p.resident = blocks_per_cu(m, *p.entry);
+                        p.rate = product_rate(m, *p.entry, dtype);
+                        if (family != PK_FAMILY_MFMA) continue;
+                        p.twin = element_twin(*p.entry);
+                        p.split = split_twin(*p.entry);
+                    }
                 }
                 t->parts.push_back(std::move(part));
             }
@@ -485,8 +507,17 @@ int pk_matmul(const pk_table *tbl, const pk_params *params_or_null, pk_dtype dty
     try {
         pk_params sel;
         if (!params_or_null) {
-            int rc = select_params(tbl, (int)dtype, M, N, K, PK_POLICY_CASE, false, &sel, A, lda, B, ldb);
-            if (rc != PK_OK) return rc;
+            // the CASE choice for these operands (it depends on their sizes
+            // and on whether their rows are aligned): cached like pk_select's
+            const bool wide = K > 0 && wide_rows((int)dtype, A, lda, B, ldb);
+            const auto key = std::make_tuple(wide ? (int)dtype + kCaseWide : (int)dtype + kCaseNarrow, M, N, K,
+                                             (int)PK_POLICY_CASE);
+            if (!tbl->cached(key, &sel)) {
+                int rc = select_params(tbl, (int)dtype, M, N, K, PK_POLICY_CASE, false, &sel, A, lda, B, ldb);
+                if (rc != PK_OK) return rc;
+                std::lock_guard<std::mutex> g(tbl->cache_mu);
+                if (tbl->cache.size() < kMaxCachedCase) tbl->cache[key] = sel;
+            }
             params_or_null = &sel;
         }
         if (params_or_null->family != PK_FAMILY_VALU && params_or_null->family != PK_FAMILY_VALU2 &&

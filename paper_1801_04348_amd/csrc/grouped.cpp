@@ -92,7 +92,7 @@ const KernelEntry *mixed_entry(int dtype, int stage) {
 // The kernel's own resources fit one workgroup of the bound machine.
 bool entry_fits(const pk_machine &m, const KernelEntry &e) {
     if (e.threads > m.max_threads_block || e.lds_bytes > m.lds_block) return false;
-    const KernelResources *r = resources_of(e.name);
+    const KernelResources *r = resources_of(e);
     return r && regs_per_block(*r, e.threads, m.wave > 0 ? m.wave : 64) <= m.regs_block;
 }
 

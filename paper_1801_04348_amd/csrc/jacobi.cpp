@@ -40,7 +40,7 @@ const KernelEntry *find_fused(const pk_machine &m, int dtype, int64_t B, int64_t
         if (e.family != PK_FAMILY_JACOBI || e.variant != PK_JACOBI_FUSED || e.dtype != dtype || e.bx != B || e.s != S)
             continue;
         if (e.lds_bytes > m.lds_block || e.threads > m.max_threads_block) return nullptr;
-        const KernelResources *r = resources_of(e.name);
+        const KernelResources *r = resources_of(e);
         if (!r || regs_per_block(*r, e.threads, m.wave > 0 ? m.wave : 64) > m.regs_block) return nullptr;
         return &e;
     }
@@ -128,6 +128,8 @@ int pk_select_jacobi1d(const pk_table *tbl, pk_dtype dtype, int64_t N, int64_t s
     const pk_table::Part *part = tbl->part(PK_FAMILY_JACOBI, (int)dtype);
     if (!part || !part->supported) return fail(PK_ERR_UNSUPPORTED_DTYPE, "no 1D Jacobi table");
     try {
+        auto key = std::make_tuple(300 + (int)dtype, N, nsteps, (int64_t)0, policy);
+        if (tbl->cached(key, out)) return PK_OK;
         struct C {
             int point, leaf, variant;
             const KernelEntry *e;
@@ -135,10 +137,8 @@ int pk_select_jacobi1d(const pk_table *tbl, pk_dtype dtype, int64_t N, int64_t s
         };
         std::vector<C> c;
         for (size_t i = 0; i < part->fam.points.size(); ++i) {
-            const int leaf = part->first_leaf[i];
-            if (leaf < 0) continue;
-            const int variant = (int)part->solved.leaves[leaf].applied;
-            const KernelEntry *e = find_instance(PK_FAMILY_JACOBI, variant, (int)dtype, part->fam.points[i]);
+            const int leaf = part->first_leaf[i], variant = part->programs[i].variant;
+            const KernelEntry *e = part->programs[i].entry;
             if (e) c.push_back(C{(int)i, leaf, variant, e, (double)nsteps * estimate_ja(tbl->machine, *e, N)});
         }
         for (size_t i = 0; i < part->fam.points.size(); ++i) {
@@ -146,15 +146,6 @@ int pk_select_jacobi1d(const pk_table *tbl, pk_dtype dtype, int64_t N, int64_t s
             if (e) c.push_back(C{(int)i, -1, PK_JACOBI_FUSED, e, estimate_fused(tbl->machine, *e, N, nsteps)});
         }
         if (c.empty()) return fail(PK_ERR_NO_FEASIBLE_BRANCH, "no 1D Jacobi leaf holds");
-        auto key = std::make_tuple(300 + (int)dtype, N, nsteps, (int64_t)0, policy);
-        {
-            std::lock_guard<std::mutex> g(tbl->cache_mu);
-            auto it = tbl->cache.find(key);
-            if (it != tbl->cache.end()) {
-                *out = it->second;
-                return PK_OK;
-            }
-        }
         int pick = 0;
         if (policy == PK_POLICY_EXHAUSTIVE && N > 2) {
             if (tbl->device < 0) return fail(PK_ERR_INVALID_ARG, "timing needs a table bound to a device");

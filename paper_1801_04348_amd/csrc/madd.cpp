@@ -50,6 +50,8 @@ int pk_select_madd(const pk_table *tbl, pk_dtype dtype, int64_t M, int64_t N, in
     const pk_table::Part *part = tbl->part(PK_FAMILY_MADD, (int)dtype);
     if (!part || !part->supported) return fail(PK_ERR_UNSUPPORTED_DTYPE, "no matrix-addition table");
     try {
+        auto key = std::make_tuple(200 + (int)dtype, M, N, (int64_t)0, policy);
+        if (tbl->cached(key, out)) return PK_OK;
         struct C {
             int point, leaf, variant;
             const KernelEntry *e;
@@ -57,22 +59,11 @@ int pk_select_madd(const pk_table *tbl, pk_dtype dtype, int64_t M, int64_t N, in
         };
         std::vector<C> c;
         for (size_t i = 0; i < part->fam.points.size(); ++i) {
-            const int leaf = part->first_leaf[i];
-            if (leaf < 0) continue;
-            const int variant = (int)part->solved.leaves[leaf].applied;
-            const KernelEntry *e = find_instance(PK_FAMILY_MADD, variant, (int)dtype, part->fam.points[i]);
+            const int leaf = part->first_leaf[i], variant = part->programs[i].variant;
+            const KernelEntry *e = part->programs[i].entry;
             if (e) c.push_back(C{(int)i, leaf, variant, e, estimate_ma(tbl->machine, *e, M, N)});
         }
         if (c.empty()) return fail(PK_ERR_NO_FEASIBLE_BRANCH, "no matrix-addition leaf holds");
-        auto key = std::make_tuple(200 + (int)dtype, M, N, (int64_t)0, policy);
-        {
-            std::lock_guard<std::mutex> g(tbl->cache_mu);
-            auto it = tbl->cache.find(key);
-            if (it != tbl->cache.end()) {
-                *out = it->second;
-                return PK_OK;
-            }
-        }
         int pick = 0;
         if (policy == PK_POLICY_EXHAUSTIVE && M > 0 && N > 0) {
             if (tbl->device < 0) return fail(PK_ERR_INVALID_ARG, "timing needs a table bound to a device");

@@ -142,6 +142,8 @@ struct KernelResources {
 
 const std::vector<KernelEntry> &registry();
 const KernelResources *resources_of(const char *name);
+// of a registry entry (or a copy of one): its own record, without the lookup by name
+const KernelResources *resources_of(const KernelEntry &e);
 // registers one workgroup of `threads` work-items allocates on gfx950
 // (unified VGPR file: arch VGPRs rounded to 4 plus AGPRs, granule 8, per lane)
 int64_t regs_per_block(const KernelResources &r, int threads, int wave);
@@ -197,9 +199,30 @@ struct pk_table {
         pk::SolveResult solved;
         std::vector<int64_t> mvals;                 // machine values by symbol id
         std::vector<int> first_leaf;                // per point: first satisfied leaf or -1
+        // what choosing and launching need of each point and do not change
+        // after binding, so that a call neither searches the registry nor
+        // evaluates a system
+        struct Program {
+            const pk::KernelEntry *entry = nullptr;  // the first leaf's program; null: none
+            const pk::KernelEntry *twin = nullptr;   // its element-load twin
+            const pk::KernelEntry *split = nullptr;  // its split-along-K form
+            int variant = 0;                         // the leaf's strategy bits
+            int64_t resident = 1;                    // workgroups per compute unit (the model's count)
+            double rate = 0.0;                       // product families: flop per clock and compute unit
+        };
+        std::vector<Program> programs;              // per point
+        std::vector<char> holds;                    // [leaf * points + point]: the leaf's system holds
     };
     std::vector<Part> parts;  // PK_NUM_FAMILIES x 3 dtypes
     const Part *part(int family, int dtype) const;
     mutable std::mutex cache_mu;
     mutable std::map<std::tuple<int, int64_t, int64_t, int64_t, int>, pk_params> cache;
+    // a cached choice, if there is one
+    bool cached(const std::tuple<int, int64_t, int64_t, int64_t, int> &key, pk_params *out) const {
+        std::lock_guard<std::mutex> g(cache_mu);
+        auto it = cache.find(key);
+        if (it == cache.end()) return false;
+        *out = it->second;
+        return true;
+    }
 };

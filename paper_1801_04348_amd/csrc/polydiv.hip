@@ -53,7 +53,7 @@ const KernelEntry *find_fused(const pk_machine &m, int64_t B, int64_t S, int64_t
     for (const auto &e : registry()) {
         if (e.family != PK_FAMILY_POLYDIV || e.variant != variant || e.bx != B || e.s != S) continue;
         if (e.lds_bytes > m.lds_block || e.threads > m.max_threads_block) return nullptr;
-        const KernelResources *r = resources_of(e.name);
+        const KernelResources *r = resources_of(e);
         if (!r || regs_per_block(*r, e.threads, m.wave > 0 ? m.wave : 64) > m.regs_block) return nullptr;
         return &e;
     }
@@ -124,6 +124,8 @@ int pk_select_polydiv(const pk_table *tbl, int64_t N, int64_t M, int policy, pk_
     const pk_table::Part *part = tbl->part(PK_FAMILY_POLYDIV, PK_I32);
     if (!part || !part->supported) return fail(PK_ERR_UNSUPPORTED_DTYPE, "no polynomial-division table");
     try {
+        auto key = std::make_tuple(400, N, M, (int64_t)0, policy);
+        if (tbl->cached(key, out)) return PK_OK;
         struct C {
             int point, leaf, variant;
             const KernelEntry *e;
@@ -131,10 +133,8 @@ int pk_select_polydiv(const pk_table *tbl, int64_t N, int64_t M, int policy, pk_
         };
         std::vector<C> c;
         for (size_t i = 0; i < part->fam.points.size(); ++i) {
-            const int leaf = part->first_leaf[i];
-            if (leaf < 0) continue;
-            const int variant = (int)part->solved.leaves[leaf].applied;
-            const KernelEntry *e = find_instance(PK_FAMILY_POLYDIV, variant, PK_I32, part->fam.points[i]);
+            const int leaf = part->first_leaf[i], variant = part->programs[i].variant;
+            const KernelEntry *e = part->programs[i].entry;
             if (e) c.push_back(C{(int)i, leaf, variant, e, estimate_pd(tbl->machine, *e, N, M)});
         }
         for (size_t i = 0; i < part->fam.points.size(); ++i) {
@@ -143,15 +143,6 @@ int pk_select_polydiv(const pk_table *tbl, int64_t N, int64_t M, int policy, pk_
             if (e) c.push_back(C{(int)i, -1, PK_POLYDIV_FUSED, e, estimate_fused(tbl->machine, *e, N, M)});
         }
         if (c.empty()) return fail(PK_ERR_NO_FEASIBLE_BRANCH, "no polynomial-division leaf holds");
-        auto key = std::make_tuple(400, N, M, (int64_t)0, policy);
-        {
-            std::lock_guard<std::mutex> g(tbl->cache_mu);
-            auto it = tbl->cache.find(key);
-            if (it != tbl->cache.end()) {
-                *out = it->second;
-                return PK_OK;
-            }
-        }
         int pick = 0;
         if (policy == PK_POLICY_EXHAUSTIVE && N > M) {
             if (tbl->device < 0) return fail(PK_ERR_INVALID_ARG, "timing needs a table bound to a device");

@@ -2,6 +2,7 @@
 // instance lists and the resource figures (taken from the compiler's
 // kernel-resource-usage report at build time) are generated by build.py.
 #include <cstring>
+#include <functional>
 #include <string>
 #include <unordered_map>
 
@@ -36,6 +37,18 @@ const KernelResources *resources_of(const char *name) {
     }();
     auto it = res.find(name);
     return it == res.end() ? nullptr : &it->second;
+}
+
+const KernelResources *resources_of(const KernelEntry &e) {
+    static const std::vector<const KernelResources *> by_index = [] {
+        std::vector<const KernelResources *> v;
+        for (const auto &x : registry()) v.push_back(resources_of(x.name));
+        return v;
+    }();
+    const auto &reg = registry();
+    const std::less<const KernelEntry *> before;
+    if (!reg.empty() && !before(&e, reg.data()) && before(&e, reg.data() + reg.size())) return by_index[&e - reg.data()];
+    return resources_of(e.name);  // a copy
 }
 
 }  // namespace pk

@@ -42,8 +42,9 @@ constexpr double kAtomicAddsPerSecond = 4e11;  // float atomic additions to C, w
 
 int elem_bytes(int dtype) { return dtype == PK_BF16 ? 2 : 4; }
 
-// multiply-accumulate throughput of one compute unit, flop per clock
-double cu_rate(const pk_machine &m, const KernelEntry &e, int dtype) {
+}  // namespace
+
+double product_rate(const pk_machine &m, const KernelEntry &e, int dtype) {
     const int threads = e.threads;
     const int wave = m.wave > 0 ? m.wave : 64;
     const double lanes = (double)threads / (double)(wave * ((threads + wave - 1) / wave));
@@ -77,7 +78,6 @@ double cu_rate(const pk_machine &m, const KernelEntry &e, int dtype) {
         mads = std::min(mads, 24.0 * std::pow(s / (1.0 + s), 0.25));
     return 2.0 * mads * lanes;
 }
-}  // namespace
 
 double streaming_seconds(const pk_machine &m, const KernelEntry &e, double bytes, int64_t tiles,
                          double inflight_bytes_per_tile, double segment_bytes) {
@@ -99,18 +99,12 @@ double streaming_seconds(const pk_machine &m, const KernelEntry &e, double bytes
     return bytes * (tiles >= ncu ? imbalance : 1.0) / bw + 0.5e-6 * rounds + 3e-6;
 }
 
-std::vector<int> k_splits(const pk_machine &m, const KernelEntry &e, int64_t M, int64_t N, int64_t K) {
-    std::vector<int> out;
-    if (e.family != PK_FAMILY_MFMA || e.bk <= 0 || !split_twin(e)) return out;
-    const int64_t tiles = ((M + e.tile_m - 1) / e.tile_m) * ((N + e.tile_n - 1) / e.tile_n);
-    const int64_t ksteps = (K + e.bk - 1) / e.bk;
-    const int64_t ncu = std::max<int32_t>(m.cu_count, 1);
-    for (int ks = 2; ks <= kMaxSplits && 2 * ks <= ksteps && tiles * (ks / 2) < 2 * ncu; ks *= 2) out.push_back(ks);
-    return out;
-}
+namespace {
 
-double estimate_seconds(const pk_machine &m, const KernelEntry &e, int dtype, int64_t M, int64_t N, int64_t K,
-                        bool wide, int ks) {
+// estimate_seconds with the program's residency and rate given (the bound
+// table holds them per point)
+double estimate_program(const pk_machine &m, const KernelEntry &e, int64_t resident, double prate, int dtype,
+                        int64_t M, int64_t N, int64_t K, bool wide, int ks) {
     // Per compute unit: the busiest one holds ceil(tiles / NCU) tiles, `res`
     // of them resident at once; each K step of a round costs the larger of
     // the resident tiles' arithmetic at the unit's rate and one step's
@@ -125,7 +119,7 @@ double estimate_seconds(const pk_machine &m, const KernelEntry &e, int dtype, in
     // a product split along K runs ks workgroups per tile, each over its share
     const int64_t tiles = std::max<int64_t>(tm * tn, 1) * ks;
     const int64_t per_cu = (tiles + ncu - 1) / ncu;
-    const int64_t res = std::min(blocks_per_cu(m, e), per_cu);
+    const int64_t res = std::min(resident, per_cu);
     const int64_t rounds = (per_cu + res - 1) / res;
     const int bk = e.bk > 0 ? e.bk : 1;
     const double ksteps = std::ceil((double)((std::max<int64_t>(K, 1) + bk - 1) / bk) / ks);
@@ -133,12 +127,13 @@ double estimate_seconds(const pk_machine &m, const KernelEntry &e, int dtype, in
     const double waves_per_simd = (double)res * ((e.threads + wave - 1) / wave) / 4.0;
     const bool mfma = e.family == PK_FAMILY_MFMA;
     const bool vi32 = !mfma && dtype == PK_I32;  // int32 VALU: its own fitted barrier cost
-    const double occupancy = std::min(1.0, std::pow(waves_per_simd / 3.0, mfma ? 0.4 : 0.25));
+    const double occupancy =
+        waves_per_simd >= 3.0 ? 1.0 : std::min(1.0, std::pow(waves_per_simd / 3.0, mfma ? 0.4 : 0.25));
     // MFMA: the tile's LDS words per output; VALU: workgroups of fewer than
     // 256 work-items lose in proportion
     const double eff = mfma ? 0.85 / (1.0 + 6.0 * (1.0 / e.tile_m + 1.0 / e.tile_n))
                             : std::min(1.0, e.threads / 256.0);
-    const double rate = cu_rate(m, e, dtype) * clock * eff * occupancy;
+    const double rate = prate * clock * eff * occupancy;
     const double latency = mfma ? ((e.variant & PK_MFMA_SINGLE) ? 0.4e-6 : 0.3e-6) : 0.1e-6;
     // VALU K steps also pay their two barriers per resident workgroup
     const double overhead = mfma ? 0.0 : (vi32 ? 0.1e-6 : 0.4e-6) * (double)res;
@@ -160,6 +155,13 @@ double estimate_seconds(const pk_machine &m, const KernelEntry &e, int dtype, in
     return std::max(compute, std::max(tile_bytes / kHbmBytesPerSecond, hbm)) + split + kLaunchSeconds;
 }
 
+}  // namespace
+
+double estimate_seconds(const pk_machine &m, const KernelEntry &e, int dtype, int64_t M, int64_t N, int64_t K,
+                        bool wide, int ks) {
+    return estimate_program(m, e, blocks_per_cu(m, e), product_rate(m, e, dtype), dtype, M, N, K, wide, ks);
+}
+
 double tile_work_seconds(const pk_machine &m, const KernelEntry &e, int dtype, int64_t M, int64_t N, int64_t K) {
     // compute-unit seconds of the product's tiles when the unit is kept full
     // of this program's workgroups: a unit advances its resident tiles by one
@@ -176,7 +178,7 @@ double tile_work_seconds(const pk_machine &m, const KernelEntry &e, int dtype, i
     const bool mfma = e.family == PK_FAMILY_MFMA;
     const double eff = mfma ? 0.85 / (1.0 + 6.0 * (1.0 / e.tile_m + 1.0 / e.tile_n))
                             : std::min(1.0, e.threads / 256.0);
-    const double rate = cu_rate(m, e, dtype) * clock * eff * occupancy;
+    const double rate = product_rate(m, e, dtype) * clock * eff * occupancy;
     const double latency = mfma ? ((e.variant & PK_MFMA_SINGLE) ? 0.4e-6 : 0.3e-6) : 0.1e-6;
     const double step = std::max((double)res * flops_step / rate, latency);
     return (double)tiles * ksteps * step / (double)res;
@@ -193,27 +195,35 @@ void fill_params(const pk_table *tbl, const Candidate &c, int dtype, pk_params *
 std::vector<Candidate> feasible(const pk_table *tbl, int dtype, int64_t M, int64_t N, int64_t K, const void *A,
                                 int64_t lda, const void *B, int64_t ldb) {
     std::vector<Candidate> out;
+    out.reserve(192);
     for (int family : {PK_FAMILY_VALU, PK_FAMILY_VALU2, PK_FAMILY_MFMA}) {  // the product families
         const pk_table::Part *part = tbl->part(family, dtype);
         if (!part || !part->supported) continue;
         // MFMA programs read unaligned rows element by element: feasible, slower
         const bool wide = !A || family != PK_FAMILY_MFMA || wide_rows(dtype, A, lda, B, ldb);
-        for (size_t i = 0; i < part->fam.points.size(); ++i) {
-            const int leaf = part->first_leaf[i];
-            if (leaf < 0) continue;
+        const int64_t ncu = std::max<int32_t>(tbl->machine.cu_count, 1);
+        for (size_t i = 0; i < part->programs.size(); ++i) {
+            const auto &p = part->programs[i];
+            if (!p.entry || (!wide && !p.twin)) continue;
             Candidate c;
             c.family = family;
             c.point = (int)i;
-            c.leaf = leaf;
-            c.variant = (int)part->solved.leaves[leaf].applied;
-            c.entry = find_instance(family, c.variant, dtype, part->fam.points[i]);
-            if (!c.entry || (!wide && !element_twin(*c.entry))) continue;
-            c.estimate = estimate_seconds(tbl->machine, *c.entry, dtype, M, N, K, wide);
+            c.leaf = part->first_leaf[i];
+            c.variant = p.variant;
+            c.entry = p.entry;
+            c.estimate = estimate_program(tbl->machine, *p.entry, p.resident, p.rate, dtype, M, N, K, wide, 1);
             out.push_back(c);
-            for (int ks : k_splits(tbl->machine, *c.entry, M, N, K)) {  // the same program split along K
+            if (!p.split) continue;
+            // the same program split along K: shares 2, 4, ... while the
+            // product has fewer tiles than two per compute unit at the
+            // previous count and every share keeps at least two K steps
+            const KernelEntry &e = *p.entry;
+            const int64_t tiles = ((M + e.tile_m - 1) / e.tile_m) * ((N + e.tile_n - 1) / e.tile_n);
+            const int64_t ksteps = (K + e.bk - 1) / e.bk;
+            for (int ks = 2; ks <= kMaxSplits && 2 * ks <= ksteps && tiles * (ks / 2) < 2 * ncu; ks *= 2) {
                 Candidate d = c;
                 d.ks = ks;
-                d.estimate = estimate_seconds(tbl->machine, *c.entry, dtype, M, N, K, wide, ks);
+                d.estimate = estimate_program(tbl->machine, e, p.resident, p.rate, dtype, M, N, K, wide, ks);
                 out.push_back(d);
             }
         }
@@ -342,18 +352,11 @@ int time_candidates(const pk_table *tbl, int dtype, int64_t M, int64_t N, int64_
 
 int select_params(const pk_table *tbl, int dtype, int64_t M, int64_t N, int64_t K, int policy, bool cache,
                   pk_params *out, const void *A, int64_t lda, const void *B, int64_t ldb) {
-    std::vector<Candidate> cands = feasible(tbl, dtype, M, N, K, A, lda, B, ldb);
-    if (cands.empty()) return fail(PK_ERR_NO_FEASIBLE_BRANCH, "no leaf of the case table holds for this dtype");
     const bool aligned_any = A == nullptr;
     auto key = std::make_tuple(dtype, M, N, K, policy);
-    if (cache && aligned_any) {
-        std::lock_guard<std::mutex> g(tbl->cache_mu);
-        auto it = tbl->cache.find(key);
-        if (it != tbl->cache.end()) {
-            *out = it->second;
-            return PK_OK;
-        }
-    }
+    if (cache && aligned_any && tbl->cached(key, out)) return PK_OK;
+    std::vector<Candidate> cands = feasible(tbl, dtype, M, N, K, A, lda, B, ldb);
+    if (cands.empty()) return fail(PK_ERR_NO_FEASIBLE_BRANCH, "no leaf of the case table holds for this dtype");
     int pick = 0;
     const pk_costmodel *model = (dtype >= 0 && dtype < 3) ? tbl->costmodel[dtype].get() : nullptr;
     if (policy == PK_POLICY_LEARNED && model) {

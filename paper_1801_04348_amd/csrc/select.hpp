@@ -30,11 +30,6 @@ std::vector<Candidate> feasible(const pk_table *tbl, int dtype, int64_t M, int64
 double estimate_seconds(const pk_machine &m, const KernelEntry &e, int dtype, int64_t M, int64_t N, int64_t K,
                         bool wide = true, int ks = 1);
 
-// Shares of K worth trying for an MFMA program at (M, N, K): 2, 4, ... while
-// the product has fewer tiles than two per compute unit at the previous
-// share count and every share keeps at least two K steps.
-std::vector<int> k_splits(const pk_machine &m, const KernelEntry &e, int64_t M, int64_t N, int64_t K);
-
 // Compute-unit seconds of a product's tiles under a program when every
 // compute unit is kept full of its workgroups (the work a persistent grouped
 // launch spends on the product).
@@ -76,6 +71,8 @@ int zero_matrix(const pk_machine &m, void *C, int64_t ldc, int64_t M, int64_t N,
 
 // helpers shared with capi.cpp
 int64_t blocks_per_cu(const pk_machine &m, const KernelEntry &e);
+// multiply-accumulate throughput of one compute unit running a product's program, flop per clock
+double product_rate(const pk_machine &m, const KernelEntry &e, int dtype);
 int64_t grid_of(const pk_machine &m, const KernelEntry &e, int64_t M, int64_t N);
 // the same for a launch: residency from the runtime's occupancy calculator
 int64_t live_blocks_per_cu(const pk_machine &m, const KernelEntry &e);

@@ -48,12 +48,9 @@ std::vector<TrCand> tr_feasible(const pk_table *tbl, int dtype, int64_t M, int64
     const pk_table::Part *part = tbl->part(PK_FAMILY_TRANSPOSE, dtype);
     if (!part || !part->supported) return out;
     for (size_t i = 0; i < part->fam.points.size(); ++i) {
-        const int leaf = part->first_leaf[i];
-        if (leaf < 0) continue;
-        const int variant = (int)part->solved.leaves[leaf].applied;
-        const KernelEntry *e = find_instance(PK_FAMILY_TRANSPOSE, variant, dtype, part->fam.points[i]);
-        if (!e) continue;
-        out.push_back(TrCand{(int)i, leaf, variant, e, estimate_tr(tbl->machine, *e, M, N)});
+        const auto &p = part->programs[i];
+        if (!p.entry) continue;
+        out.push_back(TrCand{(int)i, part->first_leaf[i], p.variant, p.entry, estimate_tr(tbl->machine, *p.entry, M, N)});
     }
     return out;
 }
@@ -71,17 +68,10 @@ int pk_select_transpose(const pk_table *tbl, pk_dtype dtype, int64_t M, int64_t 
     if (dtype != PK_F32 && dtype != PK_I32) return fail(PK_ERR_UNSUPPORTED_DTYPE, "transposition: 4-byte elements");
     if (M < 0 || N < 0) return fail(PK_ERR_INVALID_ARG, "negative dimension");
     try {
+        auto key = std::make_tuple(100 + (int)dtype, M, N, (int64_t)0, policy);
+        if (tbl->cached(key, out)) return PK_OK;
         std::vector<TrCand> c = tr_feasible(tbl, (int)dtype, M, N);
         if (c.empty()) return fail(PK_ERR_NO_FEASIBLE_BRANCH, "no transposition leaf holds");
-        auto key = std::make_tuple(100 + (int)dtype, M, N, (int64_t)0, policy);
-        {
-            std::lock_guard<std::mutex> g(tbl->cache_mu);
-            auto it = tbl->cache.find(key);
-            if (it != tbl->cache.end()) {
-                *out = it->second;
-                return PK_OK;
-            }
-        }
         int pick = 0;
         if (policy == PK_POLICY_EXHAUSTIVE && M > 0 && N > 0) {
             if (tbl->device < 0) return fail(PK_ERR_INVALID_ARG, "timing needs a table bound to a device");

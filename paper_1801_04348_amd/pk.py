@@ -415,16 +415,18 @@ def _ptr_ld(t, esize=None, what="matrix", device=True):
     only row read, at least its column count)."""
     if t.dim() != 2:
         raise ValueError("%s must be 2-D, got %d dimensions" % (what, t.dim()))
-    rows, cols = int(t.shape[0]), int(t.shape[1])
-    if cols > 1 and t.stride(1) != 1:
+    rows, cols = t.shape
+    ld, step = t.stride()
+    if cols > 1 and step != 1:
         raise ValueError("%s must have unit column stride (stride %s)" % (what, tuple(t.stride())))
-    if rows > 1 and t.stride(0) < cols:
-        raise ValueError("%s rows overlap: row stride %d < %d columns" % (what, t.stride(0), cols))
+    if ld < cols:
+        if rows > 1:
+            raise ValueError("%s rows overlap: row stride %d < %d columns" % (what, ld, cols))
+        ld = cols
     if esize is not None and t.element_size() != esize:
         raise ValueError("%s has %d-byte elements, the dtype needs %d" % (what, t.element_size(), esize))
     if device and not t.is_cuda:
         raise ValueError("%s must be a GPU tensor (got device %s)" % (what, t.device))
-    ld = t.stride(0) if rows > 1 else max(t.stride(0), cols)
     return ctypes.c_void_p(t.data_ptr()), ld
 
 
@@ -432,9 +434,11 @@ def _operands(*specs):
     """[(pointer, ld)] for (tensor, element bytes, name) triples: every
     layout is checked before any device, so a malformed operand is reported
     as such whatever the others are."""
+    out = [_ptr_ld(t, es, what, device=False) for t, es, what in specs]
     for t, es, what in specs:
-        _ptr_ld(t, es, what, device=False)
-    return [_ptr_ld(t, es, what) for t, es, what in specs]
+        if not t.is_cuda:
+            raise ValueError("%s must be a GPU tensor (got device %s)" % (what, t.device))
+    return out
 
 
 def _in_bytes(dtype) -> int:

@@ -81,3 +81,24 @@ def test_grouped_rows_packed(table, dtype):
     torch.cuda.synchronize()
     for (a, b), C, d in zip(ops, Cs, dims):
         assert np.array_equal(C.cpu().numpy().astype(np.float64), om.matmul(a[0], b[0], dtype)), d
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "i32"])
+def test_choice_of_one_size_on_both_alignments(table, dtype):
+    # pk_matmul's own choice is kept per size and alignment: calls of one size
+    # on aligned and unaligned rows in turn each compute the product
+    M, N, K = 256, 512, 264
+    a = inputs.small_int_i32((M, K), seed=41)
+    b = inputs.small_int_i32((K, N), seed=42)
+    ref = om.matmul(a, b, "i32").astype(np.float64)
+    dt = {"f32": torch.float32, "bf16": torch.bfloat16, "i32": torch.int32}[dtype]
+    for lead in (0, 1, 0, 1):
+        views = []
+        for x in (a, b):
+            buf = torch.zeros((x.shape[0], x.shape[1] + 8), dtype=dt, device="cuda")
+            buf[:, lead:lead + x.shape[1]] = x.to(dt).cuda()
+            views.append(buf[:, lead:lead + x.shape[1]])
+        C = torch.full((M, N), -1, dtype=torch.int32 if dtype == "i32" else torch.float32, device="cuda")
+        pk.pk_matmul(table, None, dtype, views[0], views[1], C)
+        torch.cuda.synchronize()
+        assert np.array_equal(C.cpu().numpy().astype(np.float64), ref), lead
