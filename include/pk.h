@@ -155,7 +155,7 @@ typedef struct {
  *   resources are checked against the machine when it is chosen). */
 #define PK_POLYDIV_FUSED 4
 #define PK_JACOBI_FUSED 4
-#define PK_POLYDIV_WIDE 8 /* internal: the instance holding up to 1024 quotient coefficients */
+#define PK_POLYDIV_WIDE 8 /* accepted beside PK_POLYDIV_FUSED, without effect */
 typedef struct {
     int32_t family;
     int32_t leaf;

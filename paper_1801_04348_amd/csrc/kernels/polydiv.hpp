@@ -105,14 +105,25 @@ namespace pkk {
 //     r[x] = a[x] - sum_{0 <= j < K} q_j b[x - (K-1) + j]   (terms with a
 //     b index below 0 vanish),
 // K products per coefficient, no dependence between coefficients.
-// Phase 1 runs in the first wavefront of every workgroup (redundantly, so no
-// grid-wide synchronisation is needed): lane l keeps top[l + 64 r], r < R, in
-// registers, the coefficient q_k is broadcast from its owner with a lane
-// read, and b[M-1-i] is staged in LDS.  Phase 2: each workgroup stages the b
-// window of its tile of S * B remainder coefficients and reads the quotient
-// from LDS.  Needs K <= 64 * R <= 1024 and B >= 64.  LDS bytes:
-// 4 * (2 * 1024 + S * B + 1024).  a[M .. n-1] are left for the host to clear.
+// Phase 1 (redundantly in every workgroup, so no grid-wide synchronisation is
+// needed) is bound by the latency of the recurrence: it goes in blocks of 64
+// quotient coefficients.  Within a block the first wavefront holds one
+// coefficient per lane and takes a step per coefficient: a lane read, one
+// product reduced by Shoup's method (the quotient estimated by the high word
+// of x w', w' = floor(2^32 w / P) precomputed per divisor coefficient: three
+// 32-bit multiplies instead of the six of a 64-bit Barrett reduction, two of
+// them in the chain), a subtraction.  Then all wavefronts apply the block's
+// 64 steps to the coefficients behind it, as one sum of products each.
+// Sums of products (there and in phase 2) are kept whole: four products of
+// residues below 2^31 fit 64 bits, and their 32-bit halves are summed apart
+// and reduced once at the end, about 2 instructions a product instead of 16.
+// Divisions modulo 2^31 - 1, M = 2^15: K = 100 33 -> 10.5 us (two launches'
+// worth), K = 1000 71 us with 1024 work-items.
+// Phase 2: each workgroup stages the b window of its tile of S * B remainder
+// coefficients and reads the quotient from LDS.  Needs K <= 1024 and B >= 64.  LDS bytes: 4 * (2 * 1024 + S * B + 1024).  a[M .. n-1] are left
+// for the host to clear.
 constexpr int kPdMaxK = 1024;
+constexpr int kPdBlock = 64;  // quotient coefficients per block: one per lane
 
 __device__ __forceinline__ uint32_t barrett(uint64_t t, uint32_t P, uint64_t mu) {
     const uint64_t q = __umul64hi(t, mu);
@@ -121,58 +132,98 @@ __device__ __forceinline__ uint32_t barrett(uint64_t t, uint32_t P, uint64_t mu)
     return (uint32_t)r;
 }
 
-template <int B, int S, int R>
+// sum_{0 <= j < n} x[j] y[j] mod P over residues (n <= kPdMaxK): y[j] at
+// y[j * DIR]
+template <int DIR>
+__device__ __forceinline__ uint32_t dot_mod(const uint32_t *x, const uint32_t *y, int n, uint32_t P, uint64_t mu) {
+    uint64_t lo = 0, hi = 0;
+    int j = 0;
+    for (; j + 4 <= n; j += 4) {
+        uint64_t t = 0;  // 4 (2^31 - 2)^2 < 2^64
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t += (uint64_t)x[j + e] * y[(j + e) * DIR];
+        lo += (uint32_t)t;
+        hi += t >> 32;
+    }
+    uint64_t t = 0;
+    for (; j < n; ++j) t += (uint64_t)x[j] * y[j * DIR];
+    lo += (uint32_t)t;
+    hi += t >> 32;
+    // lo, hi < 2^41: hi mod P < 2^31, so the last sum stays below 2^64
+    return barrett(((uint64_t)barrett(hi, P, mu) << 32) + lo, P, mu);
+}
+
+template <int B, int S>
 __device__ __forceinline__ void polydiv_fused(const PdArgs &g) {
-    static_assert(B % 64 == 0 && R * 64 <= kPdMaxK, "fused division: whole wavefronts, K <= 1024");
+    static_assert(B % 64 == 0, "fused division: whole wavefronts");
     constexpr int TW = S * B;
-    __shared__ uint32_t qs[kPdMaxK];
-    __shared__ uint32_t bt[kPdMaxK];          // bt[i] = b[M-1-i]
-    __shared__ uint32_t bw[TW + kPdMaxK];     // b window of a remainder tile
+    __shared__ uint32_t qs[kPdMaxK];              // top[j], turning into q_j
+    __shared__ __attribute__((aligned(16))) uint32_t work[2 * kPdMaxK + TW];   // phase 1: divisor coefficients; phase 2: the b window
+    // phase 1: bt[d - 1] = b[M - d] (zeros past the divisor's end and, 64 of
+    // them, before d = 1), and the first 64 of them as (w, w') pairs, with 64
+    // zero pairs before
+    uint32_t *const bt = work + kPdBlock;
+    uint2 *const pairs = reinterpret_cast<uint2 *>(work + 2 * kPdBlock + kPdMaxK);
+    static_assert(2 * kPdBlock + kPdMaxK + 4 * kPdBlock <= 2 * kPdMaxK, "phase 1 fits the window's space");
     const int M = g.M, n = g.n, K = n - M;
     const uint32_t P = g.P;
     const uint64_t mu = g.mu;
-    const int t = threadIdx.x, lane = t & 63;
-    const int nb = min(K, M);
-    for (int i = t; i < nb; i += B) bt[i] = g.b[M - 1 - i];
-    __syncthreads();
-    if (t < 64) {
-        uint32_t top[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int j = lane + 64 * r;
-            top[r] = j < K ? g.a[n - 1 - j] : 0u;
+    const int t = threadIdx.x;
+    for (int i = t; i < K; i += B) qs[i] = g.a[n - 1 - i];
+    for (int i = t - kPdBlock; i < K; i += B) bt[i] = i >= 0 && i < M ? g.b[M - 1 - i] : 0u;
+    for (int i = t; i < 2 * kPdBlock; i += B) {
+        const int d = i - kPdBlock;
+        uint32_t w = 0, ws = 0;
+        if (d >= 0 && d < M) {
+            w = g.b[M - 1 - d];
+            const uint64_t x = (uint64_t)w << 32;
+            uint64_t q = __umul64hi(x, mu);
+            if (x - q * P >= P) ++q;
+            ws = (uint32_t)q;
         }
-        for (int k = 0; k < K; ++k) {
-            uint32_t mine = top[0];
-#pragma unroll
-            for (int r = 1; r < R; ++r)
-                if (r == (k >> 6)) mine = top[r];
-            const uint32_t q = (uint32_t)__builtin_amdgcn_readlane((int)mine, k & 63);
-            if (lane == 0) qs[k] = q;
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const int d = lane + 64 * r - k;  // top[k + d] receives q b[M - d]
-                if (d >= 1 && d <= nb && k + d < K) top[r] = submod(top[r], barrett((uint64_t)q * bt[d - 1], P, mu), P);
-            }
-        }
+        pairs[i] = make_uint2(w, ws);
     }
     __syncthreads();
+    for (int kb = 0; kb < K; kb += kPdBlock) {
+        const int kn = min(kPdBlock, K - kb);
+        if (t < 64) {
+            uint32_t top = t < kn ? qs[kb + t] : 0u;
+            const uint2 *const pl = pairs + t;  // step i: d = t - i, pair d - 1 + 64
+#pragma unroll
+            for (int i0 = 0; i0 < kPdBlock; i0 += 16) {
+                if (i0 >= kn) break;  // (lanes past kn hold zeros: steps past kn - 1 subtract nothing)
+                uint2 w[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) w[i] = pl[kPdBlock - 1 - i0 - i];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const uint32_t q = (uint32_t)__builtin_amdgcn_readlane((int)top, i0 + i);
+                    uint32_t r = q * w[i].x - __umulhi(q, w[i].y) * P;  // in [0, 2P)
+                    r = min(r, r - P);
+                    top -= r;
+                    top = min(top, top + P);
+                }
+            }
+            if (t < kn) qs[kb + t] = top;
+        }
+        __syncthreads();
+        if (kb + kPdBlock >= K) break;
+        for (int j = kb + kPdBlock + t; j < K; j += B)
+            qs[j] = submod(qs[j], dot_mod<-1>(qs + kb, bt + (j - kb - 1), kPdBlock, P, mu), P);
+        __syncthreads();
+    }
     const int tiles = (M + TW - 1) / TW;
     for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
         const int x0 = tile * TW;
         for (int i = t; i < TW + K - 1; i += B) {
             const int p = x0 - (K - 1) + i;
-            bw[i] = (p >= 0 && p < M) ? g.b[p] : 0u;
+            work[i] = (p >= 0 && p < M) ? g.b[p] : 0u;
         }
         __syncthreads();
 #pragma unroll
         for (int s = 0; s < S; ++s) {
             const int xl = t + s * B, x = x0 + xl;
-            if (x < M) {
-                uint64_t acc = 0;
-                for (int j = 0; j < K; ++j) acc += barrett((uint64_t)qs[j] * bw[xl + j], P, mu);
-                g.a[x] = submod(g.a[x], barrett(acc, P, mu), P);
-            }
+            if (x < M) g.a[x] = submod(g.a[x], dot_mod<1>(qs, work + xl, K, P, mu), P);
         }
         __syncthreads();
     }

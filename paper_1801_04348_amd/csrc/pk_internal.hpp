@@ -177,7 +177,7 @@ int noalloc_setup(int device);
 const KernelEntry *find_jacobi_fused(int dtype, int64_t bx, int64_t s);
 
 // The one-launch polynomial-division instance named by a variant
-// (PK_POLYDIV_FUSED, with or without PK_POLYDIV_WIDE) and (bx, s), or null.
+// (PK_POLYDIV_FUSED) and (bx, s), or null.
 const KernelEntry *find_polydiv_fused(int variant, int64_t bx, int64_t s);
 
 }  // namespace pk

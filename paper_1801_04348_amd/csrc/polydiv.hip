@@ -45,13 +45,11 @@ int run_division(const pk_machine &m, const KernelEntry &e, uint32_t *a, int64_t
 }
 
 // The one-launch program (kernels/polydiv.hpp, polydiv_fused) for a B x S
-// point and K = N - M quotient coefficients: the instance whose register
-// slots hold K, if it exists and fits the machine.
+// point and K = N - M quotient coefficients, if it exists and fits the machine.
 const KernelEntry *find_fused(const pk_machine &m, int64_t B, int64_t S, int64_t K) {
     if (K < 1 || K > pkk::kPdMaxK) return nullptr;
-    const int variant = PK_POLYDIV_FUSED | (K > 128 ? PK_POLYDIV_WIDE : 0);
     for (const auto &e : registry()) {
-        if (e.family != PK_FAMILY_POLYDIV || e.variant != variant || e.bx != B || e.s != S) continue;
+        if (e.family != PK_FAMILY_POLYDIV || e.variant != PK_POLYDIV_FUSED || e.bx != B || e.s != S) continue;
         if (e.lds_bytes > m.lds_block || e.threads > m.max_threads_block) return nullptr;
         const KernelResources *r = resources_of(e);
         if (!r || regs_per_block(*r, e.threads, m.wave > 0 ? m.wave : 64) > m.regs_block) return nullptr;
@@ -80,17 +78,21 @@ int run_fused(const pk_machine &m, const KernelEntry &e, uint32_t *a, int64_t N,
 double estimate_fused(const pk_machine &m, const KernelEntry &e, int64_t N, int64_t M) {
     const double K = (double)(N - M);
     const double clock = m.clock_khz > 0 ? m.clock_khz * 1e3 : 2.4e9;
-    // phase 1: a dependent chain of K steps, each a lane read, a product
-    // reduction and the register-slot updates of one wavefront
-    const double slots = (e.variant & PK_POLYDIV_WIDE) ? 16.0 : 2.0;
-    const double phase1 = K * (160.0 + 60.0 * slots) / clock;
-    // phase 2: K reduced products per remainder coefficient, about 16 VALU
-    // instructions each, over the resident lanes
+    const double ncu = std::max(m.cu_count, 1);
+    // Phase 1: a dependent chain of K steps of one wavefront, then, behind
+    // each block, its products with the coefficients behind it over the
+    // workgroup's lanes.  Phase 2: K products per remainder coefficient.  A
+    // product takes a wavefront about 34 cycles alone and 11.5 of a full
+    // SIMD.  (Divisors of 512 to 2^20 coefficients: K = 1000, M = 2^15 takes
+    // 189 us with 64 work-items and 71 with 1024; K = 100, M = 2^20, where
+    // phase 2 counts, 38 and 19; at K <= 100 and M <= 2^16 all take 10-12.)
+    const double behind = std::max(K - (double)pkk::kPdBlock, 0.0);
+    const double phase1 = K * 120.0 + 0.5 * behind * behind / e.threads * 34.0;
     const int64_t tiles = (M + e.tile_n - 1) / e.tile_n;
-    const double lanes = (double)std::min<int64_t>(tiles, (int64_t)m.cu_count * blocks_per_cu(m, e)) * e.threads;
-    const double lane_rate = std::min(lanes, (double)m.cu_count * 64.0 * 4.0) * clock / 4.0;
-    const double phase2 = (double)M * K * 16.0 / std::max(lane_rate, 1.0);
-    return phase1 + phase2 + 6e-6;
+    const double waves = (double)std::min<int64_t>(tiles, (int64_t)ncu * blocks_per_cu(m, e)) * (e.threads / 64);
+    const double rounds = std::ceil((double)tiles * (e.threads / 64) / waves) * e.s;  // coefficients per lane
+    const double phase2 = rounds * K * std::max(34.0, 11.5 * waves / (4.0 * ncu));
+    return (phase1 + phase2) / clock + 6e-6;
 }
 
 double estimate_pd(const pk_machine &m, const KernelEntry &e, int64_t N, int64_t M) {

@@ -145,3 +145,19 @@ def test_one_launch_refusals(table):
         run(table, fused(32, 1), a, b, 7)
     p = pk.pk_select_polydiv(table, 2 ** 15 + 100, 2 ** 15)
     say("polydiv M=2^15 case pick", p, pk.pk_kernel_name(table, p, "i32"))
+
+
+@pytest.mark.parametrize("K", [1, 63, 64, 65, 127, 128, 129, 191, 1023, 1024])
+@pytest.mark.parametrize("P", [2, 3, 65536, 2147483646, P31])
+def test_one_launch_block_edges(table, K, P):
+    # quotients around the blocks of 64 the recurrence runs in and the groups
+    # of four the product sums run in, even and odd moduli, the largest
+    # residues in every place (the largest products and sums)
+    for M in (1, 62, 64, 65, 300):
+        a, b = residues(M + K, P, M + K), residues(M, P, M + K + 1)
+        if K % 2:
+            a[::3] = P - 1
+            b[::2] = P - 1
+        ref = oracle(a, b, P)
+        for bx, s in ((64, 1), (128, 8), (1024, 1)):
+            assert np.array_equal(run(table, fused(bx, s), a, b, P), ref), (M, bx, s)
