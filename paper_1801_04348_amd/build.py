@@ -88,7 +88,7 @@ def valu2_lds(bx, by, sx, sy, bk):
     return 4 * (by * sy * (bk + 4) + bk * bx * sx)
 
 
-def mfma_reg_cap(dt, threads, stages, kind, bm=0, bn=0):
+def mfma_reg_cap(dt, threads, stages, kind, bm=0, bn=0, lds=0):
     """At most 65536 / threads registers a lane, so that the workgroup fits a
     block register budget of 65536 (the smaller figure HIP runtimes report for
     gfx950), where the compiler's own choice would exceed it and the capped
@@ -96,6 +96,12 @@ def mfma_reg_cap(dt, threads, stages, kind, bm=0, bn=0):
     of 256 work-items (256 registers; their loads at chosen addresses hold
     more), programs of 256 work-items with tiles larger than 128 x 128 (256),
     and single-stage float32 programs of 512 (128)."""
+    if kind == "wide" and threads == 256 and bm * bn <= 128 * 128:
+        # direct loads to LDS hold few registers: as many wavefronts a SIMD
+        # as the LDS of their workgroups allows, up to what compiles without
+        # spilling; left alone the compiler spreads the operands over AGPRs
+        return "__attribute__((amdgpu_waves_per_eu(%d)))" % min({64 * 64: 4, 64 * 128: 3}.get(bm * bn, 2),
+                                                               163840 // lds)
     if (dt == F32 and threads == 512 and stages == 1) or (kind != "wide" and threads == 256) or \
             (threads == 256 and bm * bn > 128 * 128):
         return "__attribute__((amdgpu_waves_per_eu(%d)))" % (threads // 128)
@@ -156,7 +162,7 @@ def instances():
                 entry = dict(family=FAM_MFMA, variant=0 if stages == 2 else MFMA_SINGLE, dtype=dt,
                              bx=0, by=0, s=0, bk=bk, bm=bm, bn=bn, wm=wm, wn=wn, threads=64 * wm * wn,
                              lds=mfma_lds(dt, bm, bn, bk, stages), tile_m=bm, tile_n=bn)
-                entry["attrs"] = mfma_reg_cap(dt, 64 * wm * wn, stages, "wide", bm, bn)
+                entry["attrs"] = mfma_reg_cap(dt, 64 * wm * wn, stages, "wide", bm, bn, entry["lds"])
                 out.append(("mfma_%s_%d" % (DT_NAME[dt], bm * 1000 + bn), name, body, entry))
                 # the split-along-K form of the wide program (workgroups of up
                 # to 512 work-items; not the single-stage float32 programs of

@@ -152,11 +152,34 @@ static bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 
 // Rows aligned for the MFMA programs' wide loads: 16-byte loads along the
 // rows of A and B (leading dimensions multiples of 4 f32 / 8 bf16 elements,
-// 16-byte aligned bases).  Otherwise the programs read element by element
-// (same arithmetic, same summation order).
+// 16-byte aligned bases), short enough for a tile's offsets to fit the loads'
+// 32 bits.  Otherwise the programs read at element alignment (same arithmetic,
+// same summation order).
 bool wide_rows(int dtype, const void *A, int64_t lda, const void *B, int64_t ldb) {
     const int64_t vec = dtype == PK_BF16 ? 8 : 4;
+    if (dtype != PK_I32 && std::max(lda, ldb) * (16 / vec) > pkk::kMaxDmaRowBytes) return false;
     return aligned16(A) && lda % vec == 0 && aligned16(B) && ldb % vec == 0;
+}
+
+// Buffers of K steps a wide MFMA kernel cycles through, and the LDS the
+// launch adds for them (`extra`): what its LDS budget holds (two), and more
+// where a compute unit's LDS has room beside the workgroups it holds at a time
+// -- `resident`, what registers, wavefronts and the budget admit, or fewer
+// where the launch has no more.  A launch parameter like the grid: the
+// program, its counters and its residency stay what the case table says.
+int dma_depth(const pk_machine &m, const KernelEntry &e, int64_t resident, int64_t ksteps, int *extra) {
+    *extra = 0;
+    if (e.family != PK_FAMILY_MFMA || e.dtype == PK_I32 || (e.variant & PK_MFMA_ELEMENT) || e.threads >= 1024) return 2;
+    const int es = e.dtype == PK_BF16 ? 2 : 4;
+    const int sbk = (e.variant & PK_MFMA_SINGLE) ? e.bk / 2 : e.bk;
+    const int64_t bytes = (int64_t)(e.tile_m + e.tile_n) * sbk * es;
+    if (2 * bytes > e.lds_bytes) return 2;  // (the single-stage programs that load through registers)
+    // LDS is allocated in units of up to 1280 bytes
+    const int64_t room = std::min<int64_t>(m.lds_cu / std::max<int64_t>(resident, 1), m.lds_block) / 1280 * 1280;
+    const int64_t steps = std::max<int64_t>(2, (e.variant & PK_MFMA_SINGLE) ? 2 * ksteps : ksteps);
+    const int64_t depth = std::min<int64_t>({pkk::max_depth(es == 4, e.bm, e.bn, e.wm, e.wn), steps, std::max(room, (int64_t)e.lds_bytes) / bytes});
+    *extra = (int)std::max<int64_t>(0, depth * bytes - e.lds_bytes);
+    return (int)depth;
 }
 
 int launch(const pk_machine &m, const KernelEntry &e0, const MmArgs &args, hipStream_t stream) {
@@ -178,8 +201,15 @@ int launch(const pk_machine &m, const KernelEntry &e0, const MmArgs &args, hipSt
         int rc = zero_matrix(m, a.C, a.ldc, a.M, a.N, stream);
         if (rc != PK_OK) return rc;
     }
+    int extra = 0;
+    if (e.family == PK_FAMILY_MFMA) {
+        const int64_t ncu = std::max<int32_t>(m.cu_count, 1), per_cu = (grid + ncu - 1) / ncu;
+        const int64_t ksteps = ((int64_t)a.K + e.bk - 1) / std::max(e.bk, 1) / std::max(a.splits, 1);
+        a.depth = dma_depth(m, e, std::min(live_blocks_per_cu(m, e), per_cu), ksteps, &extra);
+    }
     void *kargs[] = {&a};
-    hipError_t err = hipLaunchKernel(e.fn, dim3((unsigned)grid), dim3((unsigned)e.threads), kargs, 0, stream);
+    hipError_t err =
+        hipLaunchKernel(e.fn, dim3((unsigned)grid), dim3((unsigned)e.threads), kargs, (size_t)extra, stream);
     if (err != hipSuccess)
         return fail(PK_ERR_HIP, std::string("hipLaunchKernel(") + e.name + "): " + hipGetErrorString(err));
     return PK_OK;

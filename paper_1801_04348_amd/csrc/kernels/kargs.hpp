@@ -17,11 +17,23 @@ struct MmArgs {
     int32_t accumulate;
     int32_t vec;     // MFMA programs: rows aligned for 16-byte loads (else element loads)
     int32_t splits;  // MFMA programs: shares of K (> 1: each adds its sum to C atomically), else 0
-    int32_t pad;
+    int32_t depth;   // MFMA programs that load straight to LDS: buffers of K steps (2 .. max_depth)
 };
+
+// Most buffers of K steps a wide MFMA kernel cycles through (grouped kernels:
+// two).  float32 steps multiply for thousands of cycles, more than memory
+// latency: two.  bfloat16: the wavefronts of the largest tiles have registers
+// for the code of three (or, holding more rows than columns, of two).
+constexpr int max_depth(bool f32, int bm, int bn, int wm, int wn) {
+    return f32 ? 2 : bm * bn >= 128 * 256 && wm * wn <= 4 ? (bm / wm <= bn / wn ? 3 : 2) : 4;
+}
 
 // Largest workgroup of an MFMA program that runs a product split along K.
 constexpr int kSplittableThreads = 512;
+
+// Longest row (leading dimension in bytes) the wide MFMA kernels read: the
+// offsets of a tile's up to 256 rows stay below 2^31.
+constexpr int64_t kMaxDmaRowBytes = (int64_t(1) << 23) - 1024;
 
 // One product of a grouped launch.
 struct GroupDesc {

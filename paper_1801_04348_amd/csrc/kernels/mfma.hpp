@@ -3,47 +3,49 @@
 // Same contract as the VALU family (C = [C +] A B, row-major, any M, N, K),
 // used where the product is a dense contraction in float32 or bfloat16:
 //   float32:  v_mfma_f32_32x32x2_f32   (A 32x2, B 2x32, C 32x32 per wavefront)
-//   bfloat16: v_mfma_f32_32x32x16_bf16 (A 32x16, B 16x32, float32 accumulate)
+//   bfloat16: v_mfma_f32_16x16x32_bf16 (A 16x32, B 32x16, float32 accumulate)
 //
 // Decomposition: a workgroup of WM x WN wavefronts owns a BM x BN output tile;
-// each wavefront owns (BM/WM) x (BN/WN), i.e. TM x TN blocks of 32x32
-// accumulators (16 per lane each).  K advances in steps of BK through LDS:
-//   float32:  As[BM][BK+4]   (k contiguous),   Bs[BK][BN+4]   (n contiguous)
-//   bfloat16: As[BM][BK+8]   (k contiguous),   Bs[BK][BN+32]  (n contiguous;
-//             each lane gathers its 8 k values of a column with two of
-//             gfx950's transposing LDS reads)
-// STAGES = 2 double-buffers the tiles (one barrier per K step: the next tile is
-// fetched from global memory into registers while the current one is
-// consumed); STAGES = 1 keeps one buffer and two barriers per step, as in the
-// paper's kernel, with the next step's loads in flight in registers while the
-// current step multiplies out of LDS.  LDS bytes = STAGES * (A tile + B tile).
-// Left to itself, the compiler's scheduler sinks those loads to the end of the
-// step (shortening their registers' lives) and the step then waits out a whole
-// global-memory latency; a scheduling barrier keeps them ahead of the products
-// in programs whose wavefronts hold at least a 64 x 64 tile (few wavefronts per
-// SIMD to hide the latency otherwise) and in every single-stage program.
+// each wavefront owns (BM/WM) x (BN/WN) of it, in blocks of 32 x 32 (float32) or
+// 16 x 16 (bfloat16) accumulators.  K advances in steps through LDS.
 //
-// The order in which k enters each 32x32 block's sum is permuted: lanes 0-31
-// consume k in the first half of the LDS tile and lanes 32-63 the second half,
-// so a lane's operands are contiguous in LDS.  The set of products summed is
-// unchanged.
+// LDS holds a step's tiles as they lie in memory, A row by row (k contiguous)
+// and B row by row (n contiguous), in chunks of 16 bytes without padding; the
+// chunks of a row are permuted (a_swz, b_swz) so that the reads that feed the
+// matrix unit fall in distinct banks.
 //
-// Global loads are 16 bytes wide in two kernels of every program: the wide one
-// for rows aligned for them (lda, ldb multiples of 4 floats / 8 bfloat16 and
-// 16-byte aligned bases), and its twin for all others, which reads the same
-// chunks at element alignment.  Row reads are bound by the loads in flight, so
-// 16 bytes a load pays whatever the alignment: the twins once loaded element
-// by element and took 1.4 (float32) and 3.5 (bfloat16) times the wide
-// programs' time; in chunks they take 1.00-1.03 and 1.05-1.25 times
-// (1024^3 to 4096^3; bfloat16 1021 x 3001 x 2047: 152 -> 40 us).
-// Tiles crossing the matrix edge keep the 16-byte loads in the twins and the
-// grouped kernels: they clamp the rows of A and the column chunks of B they
-// read to the last in range (results outside C are never stored), read the
-// rows of B at k >= K from a block of zeros, and guard their stores; the
-// elements of A at k >= K become zeros, and chunks across the end of an
-// unaligned row (read ending at its last element) are shifted into place,
-// when the chunks go to LDS.  Edge loads choose an address, never a loaded
-// value, so they carry no branches and stay in flight together.
+// Two ways bring the tiles there:
+//   dma_tile   rows aligned for 16-byte loads: global_load_lds writes each
+//              lane's chunk to LDS directly, no registers between.  NBUF
+//              buffers; the loads of a step go out when its buffer's last
+//              reader has passed a barrier, a whole step ahead at two buffers,
+//              and no wait drains more than it must.  A program's LDS stage
+//              budget decides: STAGES = 2 holds two buffers of BK; STAGES = 1,
+//              the paper's one buffer, is cut into two of BK / 2.
+//   regs_tile  other rows (and the single-stage bfloat16 programs of K tile
+//              32, too small to cut): chunks at element alignment through
+//              registers, the next step's loads in flight while the current
+//              step multiplies, STAGES buffers of BK.
+// Against loads through registers with padded LDS (the earlier form of both),
+// bfloat16 with 16 x 16 x 32 products: a float32 8192 x 3000 x 4096 product
+// 1683 -> 1444 us (64 x 64 tiles), a bfloat16 product of order 4096 150 -> 122
+// us (1.13 PFLOP/s, operands from HBM), one of order 1024 14 -> 7.
+// The 16 x 16 x 32 form draws less power than 32 x 32 x 16 at the same rate
+// (half the accumulator traffic): a dense 4096^3 product runs at 2.2 GHz with
+// it and 1.95 GHz without.
+//
+// Order of the sum: float32 products take k and k + 4 of each group of eight
+// in one instruction (lanes 0-31 the first four k, 32-63 the last four),
+// bfloat16 ones 32 consecutive k, both in ascending groups -- the same for
+// every tile, step and way of loading, so results do not depend on alignment.
+//
+// Tiles crossing the matrix edge keep the 16-byte loads: they clamp the rows
+// of A and the column chunks of B they read to the last in range (results
+// outside C are never stored) and guard their stores.  In a step past the end
+// of K, elements of A and rows of B at k >= K become zeros: dma_tile reads
+// clamped addresses and zeroes its own chunks in LDS once they have arrived,
+// regs_tile masks (or, across the end of an unaligned row, shifts) its chunks
+// when they go to LDS.
 //
 // Workgroup -> tile map: workgroups are dispatched round-robin over the 8 XCDs
 // (each with its own L2); blocks b and b+8 land on the same XCD, so the map
@@ -55,14 +57,14 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "kargs.hpp"
 
 namespace pkk {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 // Pointers into global memory.  The grouped kernels read operand pointers
@@ -92,360 +94,31 @@ template <int EB> __device__ __forceinline__ u32x4 chunk_from(u32x4 v, int s) {
 // the source of every element at k >= K (read only)
 static __device__ __attribute__((aligned(16))) unsigned int kZeroBlock[4] = {0u, 0u, 0u, 0u};
 
+constexpr int cmax(int a, int b) { return a > b ? a : b; }
+constexpr int cmin(int a, int b) { return a < b ? a : b; }
+
 constexpr int XCDS = kXcds;
 constexpr int GROUP_M = 8;
 
-// tile (tm, tn) of linear workgroup b among tiles_m x tiles_n
-__device__ __forceinline__ void tile_of(int64_t b, int tiles_m, int tiles_n, int *tm, int *tn) {
-    const int64_t T = (int64_t)tiles_m * tiles_n;
-    const int64_t q = T / XCDS;
-    int64_t pid = b;
-    if (b < q * XCDS) pid = (b % XCDS) * q + b / XCDS;
-    const int64_t width = (int64_t)GROUP_M * tiles_n;
-    const int64_t group = pid / width;
-    const int first_m = (int)(group * GROUP_M);
-    const int gm = min(tiles_m - first_m, GROUP_M);
-    const int64_t in = pid % width;
-    *tm = first_m + (int)(in % gm);
+// tile (tm, tn) of linear workgroup b among tiles_m x tiles_n (below 2^31:
+// a grid's workgroups; 64-bit divisions here would cost each workgroup the
+// better part of a microsecond)
+__device__ __forceinline__ void tile_of(uint32_t b, uint32_t tiles_m, uint32_t tiles_n, int *tm, int *tn) {
+    const uint32_t q = tiles_m * tiles_n / XCDS;
+    const uint32_t pid = b < q * XCDS ? (b % XCDS) * q + b / XCDS : b;
+    const uint32_t group_rows = min(tiles_m, (uint32_t)GROUP_M);
+    const uint32_t group = pid / (group_rows * tiles_n), in = pid - group * (group_rows * tiles_n);
+    const uint32_t first_m = group * group_rows, gm = min(tiles_m - first_m, group_rows);
     *tn = (int)(in / gm);
+    *tm = (int)(first_m + in - *tn * gm);
 }
 
-// ------------------------------------------------------------------ float32
-// LDS floats of a float32 tile program: STAGES x (A tile BM x (BK + 4)),
-// then STAGES x (B tile BK x (BN + 4)); every part starts 16-byte aligned.
-template <int BM, int BN, int BK, int STAGES> struct F32Lds {
-    static constexpr int LDA_S = BK + 4, LDB_S = BN + 4;
-    static constexpr int A = BM * LDA_S, B = BK * LDB_S;
-    static constexpr int floats = STAGES * (A + B);
-};
-
-// One BM x BN output tile at (row0, col0) over the K steps [kt0, kt1) (of
-// BK each), its A tiles at As0 (STAGES x F32Lds::A floats) and its B tiles
-// at Bs0 (STAGES x F32Lds::B floats) in LDS.  WIDE: the rows
-// of A and B are 16-byte aligned (else chunks are read at element alignment).
-// With a.splits > 1 the tile's sum over its K steps is added to C atomically
-// (C holds zeros or the sums of the other shares of K); otherwise it is
-// stored (added to C with a.accumulate).  The caller synchronises the
-// workgroup before reusing the LDS for another tile.
-
-template <int BM, int BN, int BK, int WM, int WN, int STAGES, bool WIDE, bool EDGE_ADDR>
-__device__ __forceinline__ void mfma_f32_tile(const MmArgs &a, const int row0, const int col0,
-                                              float *const As0, float *const Bs0, const int kt0,
-                                              const int kt1) {
-    constexpr int NT = 64 * WM * WN;
-    constexpr int WTM = BM / WM, WTN = BN / WN;
-    constexpr int TM = WTM / 32, TN = WTN / 32;
-    using L = F32Lds<BM, BN, BK, STAGES>;
-    constexpr int LDA_S = L::LDA_S, LDB_S = L::LDB_S;
-    constexpr int A4 = BM * BK / 4 / NT;  // float4 loads per work-item per A tile
-    constexpr int B4 = BK * BN / 4 / NT;
-    static_assert(TM >= 1 && TN >= 1 && WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be 32x32 blocks");
-    static_assert(A4 >= 1 && B4 >= 1 && (BM * BK / 4) % NT == 0 && (BK * BN / 4) % NT == 0, "tile loads");
-    static_assert(BK % 8 == 0, "BK");
-    constexpr bool PIN = TM * TN >= 4;  // two stages: the next step's loads ahead of the products
-
-
-    // the operands from this workgroup's first K step on: its steps run from
-    // 0, and K counts what is left of the product from there (the same loops
-    // and guards serve a whole product and a share of one)
-    const gptr<float> __restrict__ A = (gptr<float>)a.A + kt0 * BK;
-    const gptr<float> __restrict__ B = (gptr<float>)a.B + (int64_t)kt0 * BK * a.ldb;
-    const gptr<uint32_t> Aw = (gptr<uint32_t>)A, Bw = (gptr<uint32_t>)B;  // the same words, as bits
-    const gmut<float> __restrict__ C = (gmut<float>)a.C;
-    const int M = a.M, N = a.N, K = a.K - kt0 * BK;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / WN, wn = wave % WN;
-    const int r = lane & 31, h = lane >> 5;
-
-    const bool interior = (row0 + BM <= M) && (col0 + BN <= N);
-    // a wavefront whose part of an edge tile lies wholly outside C has nothing
-    // to multiply (it still loads and stores its share of the operand tiles);
-    // skipping its products frees the matrix unit for the other wavefronts
-    // (not in programs of 1024 work-items, whose registers are at the limit)
-    const bool idle = NT <= 512 && ((row0 + wm * WTM >= M) || (col0 + wn * WTN >= N));
-
-    f32x16 acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-
-    u32x4 ra[A4], rb[B4];
-    typedef typename ChunkAt<4, WIDE>::type chunk;
-    // a K step that lies wholly inside the operands: no guards, so the loads
-    // issue back to back (guarded loads branch per load, and the compiler
-    // then waits for each load before the next)
-    auto gload_fast = [&](int k0) {
-#pragma unroll
-        for (int u = 0; u < A4; ++u) {
-            const int f = tid + u * NT;
-            const int rr = f / (BK / 4), c4 = (f % (BK / 4)) * 4;
-            ra[u] = *reinterpret_cast<gptr<chunk>>(A + (int64_t)(row0 + rr) * a.lda + k0 + c4);
-        }
-#pragma unroll
-        for (int u = 0; u < B4; ++u) {
-            const int f = tid + u * NT;
-            const int rr = f / (BN / 4), c4 = (f % (BN / 4)) * 4;
-            rb[u] = *reinterpret_cast<gptr<chunk>>(B + (int64_t)(k0 + rr) * a.ldb + col0 + c4);
-        }
-    };
-    // Any K step, edge tiles included.  Without EDGE_ADDR: guarded loads
-    // (16 bytes where the chunk is wholly inside the matrix, else element by
-    // element), which hold fewer registers where edge steps are rare.
-    // EDGE_ADDR: every load is a 16-byte chunk at a chosen address, and what
-    // the chunk has to be changed into happens when it goes to LDS (sstore),
-    // so these loads stay in flight during the products too.  Rows of A past
-    // M read row M - 1 and columns of B past N a chunk inside N (their
-    // results are never stored); rows of B at k >= K read a block of zeros.
-    // Aligned rows: a chunk across k = K or column N is read whole (it holds
-    // an element of the matrix, so it lies inside its aligned row).
-    // Unaligned rows: such a chunk is read ending at the row's last element
-    // and shifted down by sk (A) or sn (B) elements later.  Unaligned rows
-    // shorter than a chunk (tiny): element loads.
-    // CHUNKS false: the float32 twins of the large single-stage tiles keep
-    // element loads, since the wide form of their guards would spill at their
-    // register cap.
-    constexpr bool CHUNKS = WIDE || EDGE_ADDR || WM * WN >= 16;
-    const bool tiny = !WIDE && (a.K < 4 || N < 4);
-    const int sk = WIDE ? 0 : (4 - (K & 3)) & 3, sn = WIDE ? 0 : (4 - (N & 3)) & 3;
-    const int klast = WIDE ? (K - 1) & ~3 : K - 4, nlast = WIDE ? (N - 1) & ~3 : N - 4;
-    auto gload = [&](int k0) {
-        if constexpr (!EDGE_ADDR) {
-            const bool kfull = (k0 + BK <= K);
-#pragma unroll
-            for (int u = 0; u < A4; ++u) {
-                const int f = tid + u * NT;
-                const int rr = f / (BK / 4), c4 = (f % (BK / 4)) * 4;
-                const int gr = row0 + rr, gc = k0 + c4;
-                if (CHUNKS && kfull && gr < M) {
-                    ra[u] = *reinterpret_cast<gptr<chunk>>(A + (int64_t)gr * a.lda + gc);
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        ra[u][e] = (gr < M && gc + e < K) ? Aw[(int64_t)gr * a.lda + gc + e] : 0u;
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < B4; ++u) {
-                const int f = tid + u * NT;
-                const int rr = f / (BN / 4), c4 = (f % (BN / 4)) * 4;
-                const int gr = k0 + rr, gc = col0 + c4;
-                if (CHUNKS && gr < K && gc + 4 <= N) {
-                    rb[u] = *reinterpret_cast<gptr<chunk>>(B + (int64_t)gr * a.ldb + gc);
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        rb[u][e] = (gr < K && gc + e < N) ? Bw[(int64_t)gr * a.ldb + gc + e] : 0u;
-                }
-            }
-            return;
-        }
-        if (!tiny) {
-#pragma unroll
-            for (int u = 0; u < A4; ++u) {
-                const int f = tid + u * NT;
-                const int rr = f / (BK / 4), c4 = (f % (BK / 4)) * 4;
-                ra[u] = *reinterpret_cast<gptr<chunk>>(A + (int64_t)min(row0 + rr, M - 1) * a.lda +
-                                                       min(k0 + c4, klast));
-            }
-#pragma unroll
-            for (int u = 0; u < B4; ++u) {
-                const int f = tid + u * NT;
-                const int rr = f / (BN / 4), c4 = (f % (BN / 4)) * 4;
-                const int k = k0 + rr;
-                rb[u] = *(k < K ? reinterpret_cast<gptr<chunk>>(B + (int64_t)k * a.ldb + min(col0 + c4, nlast))
-                                : (gptr<chunk>)(const void *)kZeroBlock);
-            }
-            return;
-        }
-        const gptr<uint32_t> zero = (gptr<uint32_t>)(const void *)kZeroBlock;
-#pragma unroll
-        for (int u = 0; u < A4; ++u) {
-            const int f = tid + u * NT;
-            const int rr = f / (BK / 4), c4 = (f % (BK / 4)) * 4;
-            const gptr<uint32_t> row = Aw + (int64_t)min(row0 + rr, M - 1) * a.lda;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int k = k0 + c4 + e;
-                ra[u][e] = *(k < K ? row + k : zero);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < B4; ++u) {
-            const int f = tid + u * NT;
-            const int rr = f / (BN / 4), c4 = (f % (BN / 4)) * 4;
-            const int k = k0 + rr;
-            const gptr<uint32_t> row = k < K ? Bw + (int64_t)k * a.ldb : nullptr;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) rb[u][e] = *(row ? row + min(col0 + c4 + e, N - 1) : zero);
-        }
-    };
-    // what the chunks of an edge step at k0 become before they go to LDS
-    auto fixup = [&](int k0) {
-        if constexpr (!EDGE_ADDR) return;
-        if (tiny) return;
-        if (k0 + BK > K) {
-#pragma unroll
-            for (int u = 0; u < A4; ++u) {
-                const int k = k0 + ((tid + u * NT) % (BK / 4)) * 4;
-                if constexpr (WIDE) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) ra[u][e] = k + e < K ? ra[u][e] : 0u;
-                } else {
-                    const u32x4 t = chunk_from<4>(ra[u], sk);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) ra[u][e] = k + 4 <= K ? ra[u][e] : k < K ? t[e] : 0u;
-                }
-            }
-        }
-        if (!WIDE && sn && col0 + BN > N) {
-#pragma unroll
-            for (int u = 0; u < B4; ++u) {
-                const u32x4 t = chunk_from<4>(rb[u], sn);
-                const bool whole = col0 + ((tid + u * NT) % (BN / 4)) * 4 + 4 <= N;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) rb[u][e] = whole ? rb[u][e] : t[e];
-            }
-        }
-    };
-    auto sstore = [&](int st) {
-#pragma unroll
-        for (int u = 0; u < A4; ++u) {
-            const int f = tid + u * NT;
-            const int rr = f / (BK / 4), c4 = (f % (BK / 4)) * 4;
-            *reinterpret_cast<u32x4 *>(&As0[st * L::A + rr * LDA_S + c4]) = ra[u];
-        }
-#pragma unroll
-        for (int u = 0; u < B4; ++u) {
-            const int f = tid + u * NT;
-            const int rr = f / (BN / 4), c4 = (f % (BN / 4)) * 4;
-            *reinterpret_cast<u32x4 *>(&Bs0[st * L::B + rr * LDB_S + c4]) = rb[u];
-        }
-    };
-    auto compute = [&](int st) {
-        const float *as = &As0[st * L::A + (wm * WTM + r) * LDA_S + h * (BK / 2)];
-        const float *bs = &Bs0[st * L::B + (h * (BK / 2)) * LDB_S + wn * WTN + r];
-#pragma unroll
-        for (int kc = 0; kc < BK / 2; kc += 4) {
-            f32x4 af[TM];
-            float bf[TN][4];
-#pragma unroll
-            for (int i = 0; i < TM; ++i) af[i] = *reinterpret_cast<const f32x4 *>(as + i * 32 * LDA_S + kc);
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) bf[j][q] = bs[(kc + q) * LDB_S + j * 32];
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[i][q], bf[j][q], acc[i][j], 0, 0, 0);
-        }
-    };
-
-    // the workgroup's KT K steps (all of K, or its share of a product split
-    // along K).  Leading steps that need no guards: all of them for an
-    // interior tile on aligned rows, except a partial last one.
-    const int KT = kt1 - kt0;
-    const int KF = CHUNKS && interior ? min(K / BK, KT) : 0;
-    if (STAGES == 2) {
-        if (KT > 0) {
-            if (KF > 0) {
-                gload_fast(0);
-            } else {
-                gload(0);
-                fixup(0);
-            }
-            sstore(0);
-        }
-        __syncthreads();
-        int kt = 0;
-        // steps whose successor is unguarded too: a loop without branches, so
-        // the next step's loads stay in flight while this step multiplies
-        for (; kt + 1 < KF; ++kt) {
-            const int cur = kt & 1;
-            gload_fast((kt + 1) * BK);
-            if constexpr (PIN) __builtin_amdgcn_sched_barrier(0);
-            compute(cur);
-            sstore(cur ^ 1);
-            __syncthreads();
-        }
-        for (; kt < KT; ++kt) {
-            const int cur = kt & 1;
-            if (kt + 1 < KT) gload((kt + 1) * BK);
-            if constexpr (PIN) __builtin_amdgcn_sched_barrier(0);
-            if (!idle) compute(cur);
-            if (kt + 1 < KT) {
-                fixup((kt + 1) * BK);
-                sstore(cur ^ 1);
-            }
-            __syncthreads();
-        }
-    } else {
-        // one LDS buffer: step kt + 1's loads are in flight (in registers)
-        // while step kt multiplies out of LDS
-        if (KT > 0) {
-            if (KF > 0)
-                gload_fast(0);
-            else
-                gload(0);
-        }
-        int kt = 0;
-        for (; kt + 1 < KF; ++kt) {
-            __syncthreads();  // the previous step's LDS reads are done
-            sstore(0);
-            __syncthreads();
-            gload_fast((kt + 1) * BK);
-            __builtin_amdgcn_sched_barrier(0);
-            compute(0);
-        }
-        for (; kt < KT; ++kt) {
-            if (kt >= KF) fixup(kt * BK);
-            __syncthreads();
-            sstore(0);
-            __syncthreads();
-            if (kt + 1 < KT) gload((kt + 1) * BK);
-            __builtin_amdgcn_sched_barrier(0);
-            if (!idle) compute(0);
-        }
-    }
-
-    // epilogue: value v of block (i, j) is row 8*(v/4) + 4*h + v%4, column r
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int gc = col0 + wn * WTN + j * 32 + r;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int gr = row0 + wm * WTM + i * 32 + 8 * (v / 4) + 4 * h + (v % 4);
-                if (interior || (gr < M && gc < N)) {
-                    const gmut<float> p = C + (int64_t)gr * a.ldc + gc;
-                    if (a.splits > 1)  // a share of K: added to C, which holds the other shares' sums
-                        unsafeAtomicAdd((float *)p, acc[i][j][v]);
-                    else
-                        *p = a.accumulate ? *p + acc[i][j][v] : acc[i][j][v];
-                }
-            }
-        }
-}
-
-// ------------------------------------------------------------------ bfloat16
-// LDS elements (16-bit) of a bfloat16 tile program: STAGES x (A tile BM x
-// (BK + 8)), then STAGES x (B tile BK x (BN + 32), row-major as in memory).
-// A B row spans BN + 32 elements, 64 bytes past a multiple of 256 for every BN
-// here: the four rows one transposing read touches fall in four different
-// 64-byte quarters of the banks.
-template <int BM, int BN, int BK, int STAGES> struct Bf16Lds {
-    static constexpr int LD_S = BK + 8, LDB_S = BN + 32;
-    static constexpr int A = BM * LD_S, B = BK * LDB_S;
-    static constexpr int elems = STAGES * (A + B);
-};
+// ------------------------------------------------------------------ tiles in LDS
+// A BM x BK tile of A and a BK x BN tile of B (EB bytes an element) for WM x WN
+// wavefronts: chunks of 16 bytes, slots in LDS, the wavefront's operands and
+// products.
+constexpr int f32_lds(int bm, int bn, int bk, int stages) { return stages * 4 * (bm * (bk + 4) + bk * (bn + 4)); }
+constexpr int bf16_lds(int bm, int bn, int bk, int stages) { return stages * 2 * (bm * (bk + 8) + bk * (bn + 32)); }
 
 // The MFMA B operand of lanes [16g, 16g + 16) from a row-major tile in LDS:
 // gfx950's transposing read hands lane i of each group of 16 element i % 4 of
@@ -453,154 +126,483 @@ template <int BM, int BN, int BK, int STAGES> struct Bf16Lds {
 // group addressing row m / 4, columns 4 (m % 4) .. + 3, lane i receives
 // column i of four consecutive rows.
 typedef short s16x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ s16x4 lds_read_tr16(const unsigned short *p) {
+__device__ __forceinline__ s16x4 lds_read_tr16(const unsigned char *p) {
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)p);
 }
 
-// bfloat16 tile, its A tiles at As0 (STAGES x Bf16Lds::A elements) and its B
-// tiles at Bs0 (STAGES x Bf16Lds::B); WIDE: A and B rows 16-byte aligned.
-template <int BM, int BN, int BK, int WM, int WN, int STAGES, bool WIDE, bool EDGE_ADDR>
-__device__ __forceinline__ void mfma_bf16_tile(const MmArgs &a, const int row0, const int col0,
-                                               unsigned short *const As0, unsigned short *const Bs0,
-                                               const int kt0, const int kt1) {
-    constexpr int NT = 64 * WM * WN;
-    constexpr int WTM = BM / WM, WTN = BN / WN;
-    constexpr int TM = WTM / 32, TN = WTN / 32;
-    using L = Bf16Lds<BM, BN, BK, STAGES>;
-    constexpr int LD_S = L::LD_S;                // row stride (elements) of the A tiles
-    constexpr int LDB_S = L::LDB_S;              // row stride of the B tiles
-    constexpr int A8 = BM * BK / 8 / NT;         // 16-byte loads per work-item per A tile
-    constexpr int B8 = BK * BN / 8 / NT;         // 16-byte loads per work-item per B tile
-    static_assert(TM >= 1 && TN >= 1 && WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be 32x32 blocks");
-    static_assert(A8 >= 1 && B8 >= 1 && (BM * BK / 8) % NT == 0 && (BK * BN / 8) % NT == 0, "tile loads");
-    static_assert(BK % 32 == 0 && BN % 8 == 0, "BK, BN");
-    static_assert((LDB_S * 2) % 256 == 64 || (LDB_S * 2) % 256 == 192, "B rows one quarter of the banks apart");
-    constexpr bool PIN = true;  // two stages: the next step's loads ahead of the products
+template <int EB, int BM, int BN, int BK, int WM, int WN> struct Tile {
+    static constexpr bool F32 = EB == 4;
+    static constexpr int NT = 64 * WM * WN;
+    static constexpr int VE = 16 / EB;                        // elements per chunk
+    static constexpr int AC = BK / VE, BC = BN / VE;          // chunks per row
+    static constexpr int A_BYTES = BM * BK * EB, B_BYTES = BK * BN * EB;
+    static constexpr int BYTES = A_BYTES + B_BYTES;
+    // loads per work-item (a tile of fewer chunks than work-items is read by
+    // the first of them and again, to the same slots, by the rest)
+    static constexpr int AL = cmax(BM * AC / NT, 1), BL = cmax(BK * BC / NT, 1);
+    static constexpr int RB = F32 ? 32 : 16;                  // block edge
+    static constexpr int WTM = BM / WM, WTN = BN / WN;
+    static constexpr int TM = WTM / RB, TN = WTN / RB;        // blocks of a wavefront
+    static constexpr int KG = F32 ? 8 : 32;                   // k of one group of products
+    // Phases of a step: operands of one are read while the one before
+    // multiplies.  A phase is half a group: of its k (float32: two of the four
+    // pairs), or of the wavefront's columns (bfloat16) -- whole groups at once
+    // would hold up to 48 registers more.  A's operands are read for a group,
+    // in the two sets in turn (FLIP: a step ends on the other set).
+    static constexpr int P = 2 * (BK / KG);
+    static constexpr int FLIP = (BK / KG) & 1;
+    typedef float acc_t __attribute__((ext_vector_type(RB * RB / 64)));
+    static_assert(WTM % RB == 0 && WTN % RB == 0 && BK % KG == 0, "whole blocks and groups");
+    static_assert(F32 || TN % 2 == 0, "two halves of columns");
+    static_assert(AC == 2 || AC == 4 || AC == 8, "a_swz covers these row lengths");
+    static_assert(F32 || BC == 8 || BC >= 16, "b_swz stays within a row");
 
-    // from this workgroup's first K step on, as in the float32 tile
-    const gptr<unsigned short> __restrict__ A = (gptr<unsigned short>)a.A + kt0 * BK;
-    const gptr<unsigned short> __restrict__ B = (gptr<unsigned short>)a.B + (int64_t)kt0 * BK * a.ldb;
-    const gmut<float> __restrict__ C = (gmut<float>)a.C;
-    const int M = a.M, N = a.N, K = a.K - kt0 * BK;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / WN, wn = wave % WN;
-    const int r = lane & 31, h = lane >> 5;
+    // Chunk c of A row r lies in slot r AC + (c ^ a_swz(r)).  A read of one
+    // chunk by the lanes of a block's rows goes through in groups of lanes
+    // 0-3, 12-15, 20-27 and so on; 256 / (16 AC) rows share a bank cycle, so
+    // the permutation has to tell rows that far apart from each other.
+    static __device__ __forceinline__ int a_swz(int r) {
+        if (AC == 8) return (r >> 1) & 7;
+        if (AC == 4) return (((r >> 2) ^ (r >> 3)) & 1) << 1 | ((r >> 3) & 1);
+        return (r >> 3) & 1;
+    }
+    // Chunk c of B row k: slot k BC + (c ^ b_swz(k)).  float32 reads whole rows
+    // (no permutation).  A bfloat16 transposing read touches 32 bytes of rows
+    // k .. k + 3 and, by the next lanes, k + 8 .. k + 11: eight slots of 32
+    // bytes of a 256-byte bank cycle.
+    static __device__ __forceinline__ int b_swz(int k) {
+        if (F32) return 0;
+        return BC >= 16 ? ((k & 3) | ((k >> 3) & 1) << 2) << 1 : (((k >> 1) & 1) | ((k >> 3) & 1) << 1) << 1;
+    }
 
-    const bool interior = (row0 + BM <= M) && (col0 + BN <= N);
+    acc_t acc[TM][TN];
+    typedef std::conditional_t<F32, f32x4, bf16x8> a_t;
+    a_t af[2][TM];                         // a lane's k of a row: four (float32) or eight
+    float bf32[2][TN][2];                  // float32: two k of a column
+    bf16x8 bf16[2][cmax(TN / 2, 1)];       // bfloat16: eight k of a column
+    int lane, wm, wn;
+
+    __device__ __forceinline__ Tile() {
+        lane = threadIdx.x & 63;
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        wm = wave / WN;
+        wn = wave % WN;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int v = 0; v < RB * RB / 64; ++v) acc[i][j][v] = 0.0f;
+    }
+
+    // requests phase p's operands from the tiles at `as` and `bs`
+    __device__ __forceinline__ void read(const unsigned char *as, const unsigned char *bs, int p, int par) {
+        if ((p & 1) == 0) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i) read_a(as, i, p, par);
+        }
+        read_b(bs, p);
+    }
+    // block row i of A; the phase's part of B
+    __device__ __forceinline__ void read_a(const unsigned char *as, int i, int p, int par) {
+        const int r = lane % RB, h = lane / RB, g = p >> 1, row = wm * WTM + i * RB + r;
+        af[(g + par) & 1][i] =
+            *reinterpret_cast<const a_t *>(as + (row * AC + ((64 / RB * g + h) ^ a_swz(r))) * 16);
+    }
+    __device__ __forceinline__ void read_b(const unsigned char *bs, int p) {
+        const int g = p >> 1, half = p & 1;
+        if constexpr (F32) {
+            const int r = lane & 31, h = lane >> 5;
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int e = 0; e < 2; ++e)
+                    bf32[half][j][e] = *reinterpret_cast<const float *>(
+                        bs + ((8 * g + 4 * h + 2 * half + e) * BN + wn * WTN + j * 32 + r) * 4);
+        } else {
+            const int m16 = lane & 15, kq = lane >> 4;
+            const int k = 8 * kq + (m16 >> 2);  // and k + 4: both in one group of eight rows, of one b_swz
+#pragma unroll
+            for (int j = 0; j < TN / 2; ++j) {
+                const int col = wn * WTN + (half * (TN / 2) + j) * 16 + 4 * (m16 & 3);
+                const unsigned char *b = bs + ((32 * g + k) * BC + ((col >> 3) ^ b_swz(k))) * 16 + (col & 7) * 2;
+                const s16x4 lo = lds_read_tr16(b), hi = lds_read_tr16(b + 4 * BC * 16);
+                bf16[half][j] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+            }
+        }
+    }
+
+    // multiplies phase p's operands: block row i, or all
+    __device__ __forceinline__ void mul_row(int i, int p, int par) {
+        const int half = p & 1, q = ((p >> 1) + par) & 1;
+        if constexpr (F32) {
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(half ? af[q][i][2 + e] : af[q][i][e],
+                                                                     bf32[half][j][e], acc[i][j], 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int j = 0; j < TN / 2; ++j) {
+                acc_t &c = acc[i][half * (TN / 2) + j];
+                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[q][i], bf16[half][j], c, 0, 0, 0);
+            }
+        }
+    }
+    __device__ __forceinline__ void mul(int p, int par) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) mul_row(i, p, par);
+    }
+
+    // C at the tile's place: stored, added to (accumulate), or, for a share of
+    // K, added atomically (C holds zeros or the other shares' sums).  float32:
+    // value v of a block is row 8 (v / 4) + 4 (lane / 32) + v % 4, column lane %
+    // 32; bfloat16: row 4 (lane / 16) + v, column lane % 16.
+    __device__ __forceinline__ void store(const MmArgs &a, int row0, int col0) const {
+        const gmut<float> C = (gmut<float>)a.C;
+        const bool interior = (row0 + BM <= a.M) && (col0 + BN <= a.N);
+        // (the choices outside the loops: inside, every store would branch)
+        auto each = [&](auto &&put) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int v = 0; v < RB * RB / 64; ++v) {
+                    const int gr = row0 + wm * WTM + i * RB + 4 * (lane / RB) + (F32 ? 8 * (v / 4) + v % 4 : v);
+                    const gmut<float> p = C + (int64_t)gr * a.ldc + col0 + wn * WTN + lane % RB;
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+                        if (interior || (gr < a.M && col0 + wn * WTN + j * RB + lane % RB < a.N))
+                            put(p + j * RB, acc[i][j][v]);
+                }
+        };
+        if (a.splits > 1)
+            each([](gmut<float> p, float x) { unsafeAtomicAdd((float *)p, x); });
+        else if (a.accumulate)
+            each([](gmut<float> p, float x) { *p += x; });
+        else if (interior)
+            each([](gmut<float> p, float x) { *p = x; });
+        else
+            each([](gmut<float> p, float x) { *p = x; });
+    }
+
     // a wavefront whose part of an edge tile lies wholly outside C has nothing
-    // to multiply (it still loads and stores its share of the operand tiles);
-    // skipping its products frees the matrix unit for the other wavefronts
-    // (not in programs of 1024 work-items, whose registers are at the limit)
-    const bool idle = NT <= 512 && ((row0 + wm * WTM >= M) || (col0 + wn * WTN >= N));
+    // to multiply (it still loads its share of the operand tiles); skipping
+    // its products frees the matrix unit for the other wavefronts
+    __device__ __forceinline__ bool idle(const MmArgs &a, int row0, int col0) const {
+        return row0 + wm * WTM >= a.M || col0 + wn * WTN >= a.N;
+    }
+};
 
-    f32x16 acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+// ------------------------------------------------------------------ loads straight to LDS
+// 16 bytes a lane from `base` + voff to LDS, lane l's at `lds` + 16 l (`lds`
+// uniform).  In asm because the compiler, which cannot tell the buffers apart,
+// would wait for every such load before any LDS read; it has no output
+// register, and the waits are dma_tile's own (below).
+__device__ __forceinline__ void load_lds16(uint32_t voff, const unsigned char *base, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(lds)
+                 : "memory");
+}
+// waits until at most N of the wavefront's memory operations are outstanding
+// (they complete in order)
+template <int N> __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+// waits for the wavefront's LDS operations, then for the workgroup
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-    // work-item f of the workgroup's u-th load: A row f / (BK / 8), its k
-    // chunk (f % (BK / 8)) * 8; B row (k) f / (BN / 8), its column chunk
-    // (f % (BN / 8)) * 8
-    u32x4 ra[A8], rb[B8];
-    typedef typename ChunkAt<2, WIDE>::type chunk;
-    auto gload_fast = [&](int k0) {  // unguarded, as in the float32 tile
+// One BM x BN output tile at (row0, col0) over the K steps [kt0, kt1) of BK
+// each, rows 16-byte aligned and leading dimensions at most kMaxDmaRowBytes (so
+// that a tile's offsets fit 32 bits).  SBK: K extent of a buffer; a.depth of
+// them at `lds`, two to MAX_DEPTH, the last ones perhaps in LDS that the launch
+// adds (dma_depth in the host library).  The caller synchronises the workgroup
+// before the call and before using the LDS otherwise.
+//
+// A step's last phase opens the next step: its loads have arrived in this
+// wavefront's view (wait_loads) and, after the barrier, in all of them, and
+// every wavefront has read the last of this step's buffer, which the loads of
+// the step DEPTH further then fill.  What bounds it: at two buffers, the
+// memory latency that one step of products does not cover when operands come
+// from HBM (all workgroups of an XCD meet a panel's first touch together);
+// bfloat16 of order 4096 on 128 x 256 x 32, 146 us with two and 124 with three.
+template <int EB, int BM, int BN, int BK, int SBK, int WM, int WN, int MAX_DEPTH>
+__device__ __forceinline__ void dma_tile(const MmArgs &a, const int row0, const int col0, unsigned char *const lds,
+                                         const int kt0, const int kt1) {
+    using T = Tile<EB, BM, BN, SBK, WM, WN>;
+    constexpr int NT = T::NT, VE = T::VE, P = T::P;
+    constexpr int LOADS = T::AL + T::BL;  // per work-item and step
+    static_assert((MAX_DEPTH - 1) * LOADS < 64, "steps under way fit the wait's counter");
+    T t;
+    const int tid = threadIdx.x;
+    const int K = min(kt1 * BK, a.K) - kt0 * BK;        // of this tile's share
+    const int KF = K / SBK, KS = (K + SBK - 1) / SBK;   // whole steps, steps
+    const unsigned char *ab = (const unsigned char *)a.A + ((int64_t)row0 * a.lda + (int64_t)kt0 * BK) * EB;
+    const unsigned char *bb = (const unsigned char *)a.B + ((int64_t)kt0 * BK * a.ldb + col0) * EB;
+    const int64_t bstep = (int64_t)SBK * a.ldb * EB;
+    uint32_t va[T::AL], vb[T::BL];  // byte offsets of this work-item's chunks
 #pragma unroll
-        for (int u = 0; u < A8; ++u) {
-            const int f = tid + u * NT;
-            const int rr = f / (BK / 8), c8 = (f % (BK / 8)) * 8;
-            ra[u] = *reinterpret_cast<gptr<chunk>>(A + (int64_t)(row0 + rr) * a.lda + k0 + c8);
+    for (int u = 0; u < T::AL; ++u) {
+        const int f = (tid + u * NT) % (BM * T::AC), r = f / T::AC, c = (f % T::AC) ^ T::a_swz(r);
+        va[u] = (uint32_t)(min(r, a.M - 1 - row0) * (int)a.lda + c * VE) * EB;
+    }
+    const int clast = ((a.N - 1) & ~(VE - 1)) - col0;
+#pragma unroll
+    for (int u = 0; u < T::BL; ++u) {
+        const int f = (tid + u * NT) % (SBK * T::BC), r = f / T::BC, c = (f % T::BC) ^ T::b_swz(r);
+        vb[u] = (uint32_t)(r * (int)a.ldb + min(c * VE, clast)) * EB;
+    }
+    // this wavefront's part of the tiles' slots
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t lbase = __builtin_amdgcn_readfirstlane(
+        (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds);
+    auto a_slot = [&](int at, int u) { return lbase + at + ((wave * 64 + u * NT) % (BM * T::AC)) * 16; };
+    auto b_slot = [&](int at, int u) { return lbase + at + T::A_BYTES + ((wave * 64 + u * NT) % (SBK * T::BC)) * 16; };
+    // requests the next step (steps are requested in order) into the buffer
+    // at byte `at` of the LDS
+    auto load = [&](int at) {
+#pragma unroll
+        for (int u = 0; u < T::AL; ++u) load_lds16(va[u], ab, a_slot(at, u));
+#pragma unroll
+        for (int u = 0; u < T::BL; ++u) load_lds16(vb[u], bb, b_slot(at, u));
+        ab += SBK * EB;
+        bb += bstep;
+    };
+    // the same for a last step of `rest` < SBK k: chunks and rows past them
+    // read the last one in range
+    const int rest = K - KF * SBK;
+    auto load_rest = [&](int at) {
+        const int kl = (rest - 1) & ~(VE - 1);
+#pragma unroll
+        for (int u = 0; u < T::AL; ++u) {
+            const int f = (tid + u * NT) % (BM * T::AC), k = ((f % T::AC) ^ T::a_swz(f / T::AC)) * VE;
+            load_lds16(va[u] - (uint32_t)max(k - kl, 0) * EB, ab, a_slot(at, u));
         }
 #pragma unroll
-        for (int u = 0; u < B8; ++u) {
-            const int f = tid + u * NT;
-            const int rr = f / (BN / 8), c8 = (f % (BN / 8)) * 8;
-            rb[u] = *reinterpret_cast<gptr<chunk>>(B + (int64_t)(k0 + rr) * a.ldb + col0 + c8);
+        for (int u = 0; u < T::BL; ++u) {
+            const int r = (tid + u * NT) % (SBK * T::BC) / T::BC;
+            load_lds16(vb[u] - (uint32_t)(max(r - (rest - 1), 0) * (int)a.ldb) * EB, bb, b_slot(at, u));
         }
     };
-    // any K step, and the chunks of edge steps: as in the float32 tile
-    const bool tiny = !WIDE && (a.K < 8 || N < 8);
-    const int sk = WIDE ? 0 : (8 - (K & 7)) & 7, sn = WIDE ? 0 : (8 - (N & 7)) & 7;
-    const int klast = WIDE ? (K - 1) & ~7 : K - 8, nlast = WIDE ? (N - 1) & ~7 : N - 8;
+    auto load_step = [&](int kt, int at) {
+        if (kt < KF)
+            load(at);
+        else if (kt < KS)
+            load_rest(at);
+    };
+    // zeros at k >= rest in this work-item's own chunks, which have arrived
+    auto clear_rest = [&](int at) {
+        unsigned char *const la = lds + at, *const lb = la + T::A_BYTES;
+#pragma unroll
+        for (int u = 0; u < T::AL; ++u) {
+            const int f = (tid + u * NT) % (BM * T::AC), k = ((f % T::AC) ^ T::a_swz(f / T::AC)) * VE;
+            if (k + VE > rest) {
+                u32x4 v = *reinterpret_cast<const u32x4 *>(la + f * 16);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if constexpr (T::F32)
+                        v[e] = k + e < rest ? v[e] : 0u;
+                    else  // word e holds k + 2e (low half) and k + 2e + 1 (high half)
+                        v[e] &= k + 2 * e + 1 < rest ? 0xffffffffu : (k + 2 * e < rest ? 0x0000ffffu : 0u);
+                *reinterpret_cast<u32x4 *>(la + f * 16) = v;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < T::BL; ++u) {
+            const int f = (tid + u * NT) % (SBK * T::BC);
+            if (f / T::BC >= rest) *reinterpret_cast<u32x4 *>(lb + f * 16) = u32x4{0u, 0u, 0u, 0u};
+        }
+    };
+    const bool idle = t.idle(a, row0, col0);
+    // (the code of a depth's own: buffers, waits and operand sets constant)
+    auto run = [&](auto depth) {
+        constexpr int DEPTH = decltype(depth)::value;
+#pragma unroll
+        for (int s = 0; s < DEPTH; ++s) load_step(s, s * T::BYTES);
+        if (KS >= DEPTH)
+            wait_loads<(DEPTH - 1) * LOADS>();
+        else
+            wait_loads<0>();
+        if (KF == 0) clear_rest(0);
+        lds_barrier();
+        t.read(lds, lds + T::A_BYTES, 0, 0);
+        // step kt, in buffer buf, whose phase 0 is on its way.  FULL: all of
+        // its k and of the next DEPTH steps' in range
+        auto step = [&](int kt, int buf, int par, auto full) {
+            constexpr bool FULL = decltype(full)::value;
+            const int at = buf * T::BYTES, next = buf + 1 == DEPTH ? 0 : at + T::BYTES;
+            const int kn = FULL ? SBK : min(K - kt * SBK, SBK);
+#pragma unroll
+            for (int p = 0; p < P; ++p) {
+                if (p + 1 < P) {
+                    t.read(lds + at, lds + at + T::A_BYTES, p + 1, par);
+                } else if (FULL || kt + 1 < KS) {
+                    if (FULL || kt + DEPTH <= KS)
+                        wait_loads<(DEPTH - 2) * LOADS>();
+                    else
+                        wait_loads<0>();
+                    if (!FULL && kt + 1 >= KF) clear_rest(next);
+                    lds_barrier();
+                    __builtin_amdgcn_sched_barrier(0);
+                    t.read(lds + next, lds + next + T::A_BYTES, 0, par ^ T::FLIP);
+                    if (FULL)
+                        load(at);
+                    else
+                        load_step(kt + DEPTH, at);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                // (groups past the end of K are zeros: nothing to multiply)
+                if (FULL || (!idle && (p >> 1) * T::KG < kn)) t.mul(p, par);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        // a round returns to the first buffer and operand set
+        constexpr int ROUND = T::FLIP && DEPTH % 2 ? 2 * DEPTH : DEPTH;
+        int kt = 0;
+        if (!idle)
+            for (; kt + ROUND - 1 + DEPTH < KF; kt += ROUND) {
+#pragma unroll
+                for (int s = 0; s < ROUND; ++s) step(kt + s, s % DEPTH, s & T::FLIP, std::true_type{});
+            }
+        int buf = 0;
+        for (; kt < KS; kt += 2) {
+            step(kt, buf, 0, std::false_type{});
+            buf = buf + 1 == DEPTH ? 0 : buf + 1;
+            if (kt + 1 < KS) step(kt + 1, buf, T::FLIP, std::false_type{});
+            buf = buf + 1 == DEPTH ? 0 : buf + 1;
+        }
+    };
+    if (KS > 0) {
+        if (MAX_DEPTH == 2 || a.depth == 2)
+            run(std::integral_constant<int, 2>{});
+        else if (MAX_DEPTH == 3 || a.depth == 3)
+            run(std::integral_constant<int, cmin(3, MAX_DEPTH)>{});
+        else
+            run(std::integral_constant<int, MAX_DEPTH>{});
+    }
+    t.store(a, row0, col0);
+}
+
+// ------------------------------------------------------------------ loads through registers
+// The same tile with chunks through registers: STAGES buffers of BK at `lds`.
+// WIDE: rows 16-byte aligned (else chunks are read at element alignment).
+// EDGE_ADDR: edge chunks at chosen addresses; else (float32 twins whose fixups
+// would spill at their register cap) guarded loads, element by element at the
+// edges -- and everywhere in the large single-stage ones (CHUNKS false), where
+// the wide form of the guards would spill.
+template <int EB, int BM, int BN, int BK, int WM, int WN, int STAGES, bool WIDE, bool EDGE_ADDR>
+__device__ __forceinline__ void regs_tile(const MmArgs &a, const int row0, const int col0, unsigned char *const lds,
+                                          const int kt0, const int kt1) {
+    using T = Tile<EB, BM, BN, BK, WM, WN>;
+    constexpr int NT = T::NT, VE = T::VE, AC = T::AC, BC = T::BC, AL = T::AL, BL = T::BL;
+    static_assert(BM * AC % NT == 0 && BK * BC % NT == 0, "whole loads");
+    constexpr bool CHUNKS = WIDE || EDGE_ADDR || WM * WN >= 16;
+    // one block row's operands at a time, where more would spill at the
+    // register cap
+    constexpr bool LEAN = NT >= 512 || (EB == 2 && BM * BN >= 128 * 128);
+    using elem = std::conditional_t<EB == 4, uint32_t, unsigned short>;
+    typedef elem elems __attribute__((ext_vector_type(VE)));
+    typedef typename ChunkAt<EB, WIDE>::type chunk;
+    T t;
+    // the operands from this share's first K step on: its steps run from 0,
+    // and K counts what is left of the product from there
+    const gptr<elem> __restrict__ A = (gptr<elem>)a.A + kt0 * BK;
+    const gptr<elem> __restrict__ B = (gptr<elem>)a.B + (int64_t)kt0 * BK * a.ldb;
+    const int M = a.M, N = a.N, K = a.K - kt0 * BK;
+    const int tid = threadIdx.x;
+    const bool interior = (row0 + BM <= M) && (col0 + BN <= N);
+    const bool idle = NT <= 512 && t.idle(a, row0, col0);  // (1024 work-items: registers at the limit)
+
+    u32x4 ra[AL], rb[BL];
+    // row and first element of this work-item's u-th chunks
+    auto a_row = [&](int u) { return (tid + u * NT) / AC; };
+    auto a_k = [&](int u) { return (tid + u * NT) % AC * VE; };
+    auto b_row = [&](int u) { return (tid + u * NT) / BC; };
+    auto b_col = [&](int u) { return (tid + u * NT) % BC * VE; };
+    // a K step that lies wholly inside the operands: no guards, so the loads
+    // issue back to back (guarded loads branch per load, and the compiler
+    // then waits for each load before the next)
+    auto gload_fast = [&](int k0) {
+#pragma unroll
+        for (int u = 0; u < AL; ++u)
+            ra[u] = *reinterpret_cast<gptr<chunk>>(A + (int64_t)(row0 + a_row(u)) * a.lda + k0 + a_k(u));
+#pragma unroll
+        for (int u = 0; u < BL; ++u)
+            rb[u] = *reinterpret_cast<gptr<chunk>>(B + (int64_t)(k0 + b_row(u)) * a.ldb + col0 + b_col(u));
+    };
+    // Any K step.  EDGE_ADDR: rows of A past M read row M - 1 and columns of B
+    // past N a chunk inside N; rows of B at k >= K read a block of zeros.
+    // Aligned rows: a chunk across k = K or column N is read whole (it holds
+    // an element of the matrix, so it lies inside its aligned row).
+    // Unaligned rows: such a chunk is read ending at the row's last element
+    // and shifted down by sk (A) or sn (B) elements by fixup, when it goes to
+    // LDS, so that the load stays in flight during the products.  Unaligned
+    // rows shorter than a chunk (tiny): element loads.
+    const bool tiny = !WIDE && (a.K < VE || N < VE);
+    const int sk = WIDE ? 0 : (VE - (K & (VE - 1))) & (VE - 1), sn = WIDE ? 0 : (VE - (N & (VE - 1))) & (VE - 1);
+    const int klast = WIDE ? (K - 1) & ~(VE - 1) : K - VE, nlast = WIDE ? (N - 1) & ~(VE - 1) : N - VE;
     auto gload = [&](int k0) {
         if constexpr (!EDGE_ADDR) {
             const bool kfull = (k0 + BK <= K);
 #pragma unroll
-            for (int u = 0; u < A8; ++u) {
-                const int f = tid + u * NT;
-                const int rr = f / (BK / 8), c8 = (f % (BK / 8)) * 8;
-                const int gr = row0 + rr, gc = k0 + c8;
-                if (kfull && gr < M) {
+            for (int u = 0; u < AL; ++u) {
+                const int gr = row0 + a_row(u), gc = k0 + a_k(u);
+                if (CHUNKS && kfull && gr < M) {
                     ra[u] = *reinterpret_cast<gptr<chunk>>(A + (int64_t)gr * a.lda + gc);
                 } else {
-                    u16x8 v;
+                    elems v;
 #pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        v[e] = (gr < M && gc + e < K) ? A[(int64_t)gr * a.lda + gc + e] : (unsigned short)0;
+                    for (int e = 0; e < VE; ++e)
+                        v[e] = (gr < M && gc + e < K) ? A[(int64_t)gr * a.lda + gc + e] : elem(0);
                     ra[u] = __builtin_bit_cast(u32x4, v);
                 }
+                if constexpr (LEAN) __builtin_amdgcn_sched_barrier(0);  // (one chunk's addresses at a time)
             }
 #pragma unroll
-            for (int u = 0; u < B8; ++u) {
-                const int f = tid + u * NT;
-                const int rr = f / (BN / 8), c8 = (f % (BN / 8)) * 8;
-                const int gr = k0 + rr, gc = col0 + c8;
-                if (gr < K && gc + 8 <= N) {
+            for (int u = 0; u < BL; ++u) {
+                const int gr = k0 + b_row(u), gc = col0 + b_col(u);
+                if (CHUNKS && gr < K && gc + VE <= N) {
                     rb[u] = *reinterpret_cast<gptr<chunk>>(B + (int64_t)gr * a.ldb + gc);
                 } else {
-                    u16x8 v;
+                    elems v;
 #pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        v[e] = (gr < K && gc + e < N) ? B[(int64_t)gr * a.ldb + gc + e] : (unsigned short)0;
+                    for (int e = 0; e < VE; ++e)
+                        v[e] = (gr < K && gc + e < N) ? B[(int64_t)gr * a.ldb + gc + e] : elem(0);
                     rb[u] = __builtin_bit_cast(u32x4, v);
                 }
+                if constexpr (LEAN) __builtin_amdgcn_sched_barrier(0);
             }
             return;
         }
         if (!tiny) {
 #pragma unroll
-            for (int u = 0; u < A8; ++u) {
-                const int f = tid + u * NT;
-                const int rr = f / (BK / 8), c8 = (f % (BK / 8)) * 8;
-                ra[u] = *reinterpret_cast<gptr<chunk>>(A + (int64_t)min(row0 + rr, M - 1) * a.lda +
-                                                       min(k0 + c8, klast));
-            }
+            for (int u = 0; u < AL; ++u)
+                ra[u] = *reinterpret_cast<gptr<chunk>>(A + (int64_t)min(row0 + a_row(u), M - 1) * a.lda +
+                                                       min(k0 + a_k(u), klast));
 #pragma unroll
-            for (int u = 0; u < B8; ++u) {
-                const int f = tid + u * NT;
-                const int rr = f / (BN / 8), c8 = (f % (BN / 8)) * 8;
-                const int k = k0 + rr;
-                rb[u] = *(k < K ? reinterpret_cast<gptr<chunk>>(B + (int64_t)k * a.ldb + min(col0 + c8, nlast))
+            for (int u = 0; u < BL; ++u) {
+                const int k = k0 + b_row(u);
+                rb[u] = *(k < K ? reinterpret_cast<gptr<chunk>>(B + (int64_t)k * a.ldb + min(col0 + b_col(u), nlast))
                                 : (gptr<chunk>)(const void *)kZeroBlock);
             }
             return;
         }
-        const gptr<unsigned short> zero = (gptr<unsigned short>)(const void *)kZeroBlock;
+        const gptr<elem> zero = (gptr<elem>)(const void *)kZeroBlock;
 #pragma unroll
-        for (int u = 0; u < A8; ++u) {
-            const int f = tid + u * NT;
-            const int rr = f / (BK / 8), c8 = (f % (BK / 8)) * 8;
-            const gptr<unsigned short> row = A + (int64_t)min(row0 + rr, M - 1) * a.lda;
-            u16x8 v;
+        for (int u = 0; u < AL; ++u) {
+            const gptr<elem> row = A + (int64_t)min(row0 + a_row(u), M - 1) * a.lda;
+            elems v;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int k = k0 + c8 + e;
+            for (int e = 0; e < VE; ++e) {
+                const int k = k0 + a_k(u) + e;
                 v[e] = *(k < K ? row + k : zero);
             }
             ra[u] = __builtin_bit_cast(u32x4, v);
         }
 #pragma unroll
-        for (int u = 0; u < B8; ++u) {
-            const int f = tid + u * NT;
-            const int rr = f / (BN / 8), c8 = (f % (BN / 8)) * 8;
-            const int k = k0 + rr;
-            const gptr<unsigned short> row = k < K ? B + (int64_t)k * a.ldb : nullptr;
-            u16x8 v;
+        for (int u = 0; u < BL; ++u) {
+            const int k = k0 + b_row(u);
+            const gptr<elem> row = k < K ? B + (int64_t)k * a.ldb : nullptr;
+            elems v;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = *(row ? row + min(col0 + c8 + e, N - 1) : zero);
+            for (int e = 0; e < VE; ++e) v[e] = *(row ? row + min(col0 + b_col(u) + e, N - 1) : zero);
             rb[u] = __builtin_bit_cast(u32x4, v);
         }
     };
@@ -610,77 +612,73 @@ __device__ __forceinline__ void mfma_bf16_tile(const MmArgs &a, const int row0, 
         if (tiny) return;
         if (k0 + BK > K) {
 #pragma unroll
-            for (int u = 0; u < A8; ++u) {
-                const int k = k0 + ((tid + u * NT) % (BK / 8)) * 8;
-                if constexpr (WIDE) {
+            for (int u = 0; u < AL; ++u) {
+                const int k = k0 + a_k(u);
+                if constexpr (!WIDE) {
+                    const u32x4 s = chunk_from<EB>(ra[u], sk);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) ra[u][e] = k + VE <= K ? ra[u][e] : k < K ? s[e] : 0u;
+                } else if constexpr (EB == 4) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) ra[u][e] = k + e < K ? ra[u][e] : 0u;
+                } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)  // word e holds k + 2e (low half) and k + 2e + 1 (high half)
                         ra[u][e] &= k + 2 * e + 1 < K ? 0xffffffffu : (k + 2 * e < K ? 0x0000ffffu : 0u);
-                } else {
-                    const u32x4 t = chunk_from<2>(ra[u], sk);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) ra[u][e] = k + 8 <= K ? ra[u][e] : k < K ? t[e] : 0u;
                 }
             }
         }
         if (!WIDE && sn && col0 + BN > N) {
 #pragma unroll
-            for (int u = 0; u < B8; ++u) {
-                const u32x4 t = chunk_from<2>(rb[u], sn);
-                const bool whole = col0 + ((tid + u * NT) % (BN / 8)) * 8 + 8 <= N;
+            for (int u = 0; u < BL; ++u) {
+                const u32x4 s = chunk_from<EB>(rb[u], sn);
+                const bool whole = col0 + b_col(u) + VE <= N;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) rb[u][e] = whole ? rb[u][e] : t[e];
+                for (int e = 0; e < 4; ++e) rb[u][e] = whole ? rb[u][e] : s[e];
             }
         }
     };
     auto sstore = [&](int st) {
+        unsigned char *const la = lds + st * T::BYTES, *const lb = la + T::A_BYTES;
 #pragma unroll
-        for (int u = 0; u < A8; ++u) {
-            const int f = tid + u * NT;
-            const int rr = f / (BK / 8), c8 = (f % (BK / 8)) * 8;
-            *reinterpret_cast<u32x4 *>(&As0[st * L::A + rr * LD_S + c8]) = ra[u];
+        for (int u = 0; u < AL; ++u) {
+            const int r = a_row(u);
+            *reinterpret_cast<u32x4 *>(la + (r * AC + (a_k(u) / VE ^ T::a_swz(r))) * 16) = ra[u];
         }
 #pragma unroll
-        for (int u = 0; u < B8; ++u) {
-            const int f = tid + u * NT;
-            const int rr = f / (BN / 8), c8 = (f % (BN / 8)) * 8;
-            *reinterpret_cast<u32x4 *>(&Bs0[st * L::B + rr * LDB_S + c8]) = rb[u];
+        for (int u = 0; u < BL; ++u) {
+            const int r = b_row(u);
+            *reinterpret_cast<u32x4 *>(lb + (r * BC + (b_col(u) / VE ^ T::b_swz(r))) * 16) = rb[u];
         }
     };
-    // lane (r, h) multiplies A row r and B column r over k = h BK/2 + kc + t,
-    // t = 0..7, per MFMA; its B values come from two transposing reads (t =
-    // 0..3, then 4..7): lane m of its group of 16 addresses row m / 4 of the
-    // four, columns 4 (m % 4) .. + 3 of the group's 16 (groups 0 and 2 take
-    // columns 0..15 of the block, 1 and 3 columns 16..31)
-    const int grp = lane >> 4, m16 = lane & 15;
     auto compute = [&](int st) {
-        const unsigned short *as = &As0[st * L::A + (wm * WTM + r) * LD_S + h * (BK / 2)];
-        const unsigned short *bs = &Bs0[st * L::B + (h * (BK / 2) + (m16 >> 2)) * LDB_S + wn * WTN +
-                                        16 * (grp & 1) + 4 * (m16 & 3)];
+        const unsigned char *const la = lds + st * T::BYTES, *const lb = la + T::A_BYTES;
+        // (and operand addresses made anew each step, not held across it)
+        if constexpr (LEAN) asm volatile("" : "+v"(t.lane));
 #pragma unroll
-        for (int kc = 0; kc < BK / 2; kc += 8) {
-            bf16x8 af[TM], bf[TN];
+        for (int p = 0; p < T::P; ++p) {
+            if constexpr (LEAN) {
+                t.read_b(lb, p);
 #pragma unroll
-            for (int i = 0; i < TM; ++i) af[i] = *reinterpret_cast<const bf16x8 *>(as + i * 32 * LD_S + kc);
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const s16x4 lo = lds_read_tr16(bs + kc * LDB_S + j * 32);
-                const s16x4 hi = lds_read_tr16(bs + (kc + 4) * LDB_S + j * 32);
-                bf[j] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+                for (int i = 0; i < T::TM; ++i) {
+                    t.read_a(la, i, p, 0);
+                    t.mul_row(i, p, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            } else {
+                t.read(la, lb, p, 0);
+                t.mul(p, 0);
             }
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bf[j], acc[i][j], 0, 0, 0);
         }
     };
-
-    // the workgroup's KT K steps (all of K, or its share of a product split
-    // along K).  Leading steps that need no guards: all of them for an
-    // interior tile on aligned rows, except a partial last one.
+    // Left to itself, the compiler's scheduler sinks the next step's loads to
+    // the end of the step (shortening their registers' lives) and the step
+    // then waits out a whole global-memory latency: a scheduling barrier keeps
+    // them ahead of the products, except in the two-stage programs whose
+    // wavefronts hold less than 64 x 64 (enough wavefronts hide it there).
+    constexpr bool PIN = EB == 2 || STAGES == 1 || T::WTM * T::WTN >= 64 * 64;
     const int KT = kt1 - kt0;
-    const int KF = interior ? min(K / BK, KT) : 0;
+    const int KF = CHUNKS && interior ? min(K / BK, KT) : 0;  // leading steps that need no guards
     if (STAGES == 2) {
         if (KT > 0) {
             if (KF > 0) {
@@ -742,24 +740,22 @@ __device__ __forceinline__ void mfma_bf16_tile(const MmArgs &a, const int row0, 
             if (!idle) compute(0);
         }
     }
+    t.store(a, row0, col0);
+}
 
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int gc = col0 + wn * WTN + j * 32 + r;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int gr = row0 + wm * WTM + i * 32 + 8 * (v / 4) + 4 * h + (v % 4);
-                if (interior || (gr < M && gc < N)) {
-                    const gmut<float> p = C + (int64_t)gr * a.ldc + gc;
-                    if (a.splits > 1)  // a share of K: added to C, which holds the other shares' sums
-                        unsafeAtomicAdd((float *)p, acc[i][j][v]);
-                    else
-                        *p = a.accumulate ? *p + acc[i][j][v] : acc[i][j][v];
-                }
-            }
-        }
+// The tile by the way that its program and its rows' alignment take.
+template <int EB, int BM, int BN, int BK, int WM, int WN, int STAGES, bool WIDE, int MAX_DEPTH>
+__device__ __forceinline__ void mfma_tile(const MmArgs &a, int row0, int col0, unsigned char *lds, int kt0, int kt1) {
+    constexpr int SBK = STAGES == 2 ? BK : BK / 2;
+    // (programs of 1024 work-items, 128 registers a lane, have no room for
+    // the second operand set)
+    constexpr bool DMA = WIDE && WM * WN < 16 && SBK % (EB == 4 ? 8 : 32) == 0;
+    // the largest tiles' guarded loads: see regs_tile
+    constexpr bool EDGE = WM * WN < 16 && (EB == 2 || STAGES == 2 || BM * BN * BK <= 128 * 256 * 16);
+    if constexpr (DMA)
+        dma_tile<EB, BM, BN, BK, SBK, WM, WN, MAX_DEPTH>(a, row0, col0, lds, kt0, kt1);
+    else
+        regs_tile<EB, BM, BN, BK, WM, WN, STAGES, WIDE, EDGE>(a, row0, col0, lds, kt0, kt1);
 }
 
 // ------------------------------------------------------------------ single product
@@ -769,56 +765,47 @@ __device__ __forceinline__ void mfma_bf16_tile(const MmArgs &a, const int row0, 
 // 1024 work-items are never split (kSplittableThreads): their registers are
 // at the limit already.
 template <int BK>
-__device__ __forceinline__ void k_share(const MmArgs &a, int64_t tiles, int64_t *b, int *kt0, int *kt1) {
+__device__ __forceinline__ void k_share(const MmArgs &a, uint32_t tiles, uint32_t *b, int *kt0, int *kt1) {
     const int KT = (a.K + BK - 1) / BK;
     *kt0 = 0;
     *kt1 = KT;
     if (a.splits > 1) {
-        const int s = (int)(*b / tiles);
-        *b -= (int64_t)s * tiles;
-        *kt0 = (int)((int64_t)KT * s / a.splits);
-        *kt1 = (int)((int64_t)KT * (s + 1) / a.splits);
+        const uint32_t s = *b / tiles;
+        *b -= s * tiles;
+        *kt0 = (int)((uint32_t)KT * (uint64_t)s / (uint32_t)a.splits);
+        *kt1 = (int)((uint32_t)KT * (uint64_t)(s + 1) / (uint32_t)a.splits);
     }
 }
 
 // WIDE: 16-byte loads along aligned rows; the element-load twin (WIDE =
 // false: 16-byte loads at element alignment) is a kernel of its own, so
-// neither carries the other's load path.  The twins load edge chunks at chosen
-// addresses, but for float32 tiles whose fixups would spill at their register
-// cap.  SPLIT: the kernel runs shares of K
+// neither carries the other's load path.  SPLIT: the kernel runs shares of K
 // (a.splits > 1); the wide program's split form is a kernel of its own too,
-// so the whole-product kernel carries none of it (the element-load twins,
-// already off the fast path, split in place).
-template <int BM, int BN, int BK, int WM, int WN, int STAGES, bool WIDE = true, bool SPLIT = !WIDE>
-__device__ __forceinline__ void mfma_f32(const MmArgs &a0) {
+// so the whole-product kernel carries none of it (the element-load twins
+// split in place).
+template <int EB, int BM, int BN, int BK, int WM, int WN, int STAGES, bool WIDE, bool SPLIT>
+__device__ __forceinline__ void mfma_product(const MmArgs &a0, unsigned char *lds) {
     MmArgs a = a0;
     if constexpr (!SPLIT || 64 * WM * WN > kSplittableThreads) a.splits = 0;
     int tm, tn;
-    using L = F32Lds<BM, BN, BK, STAGES>;
-    __shared__ __attribute__((aligned(16))) float As[STAGES * L::A];
-    __shared__ __attribute__((aligned(16))) float Bs[STAGES * L::B];
-    int64_t b = blockIdx.x;
+    uint32_t b = blockIdx.x;
+    const uint32_t tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
     int kt0, kt1;
-    k_share<BK>(a, (int64_t)((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN), &b, &kt0, &kt1);
-    tile_of(b, (a.M + BM - 1) / BM, (a.N + BN - 1) / BN, &tm, &tn);
-    mfma_f32_tile<BM, BN, BK, WM, WN, STAGES, WIDE,
-                  !WIDE && WM * WN < 16 && (STAGES == 2 || BM * BN * BK <= 128 * 256 * 16)>(a, tm * BM, tn * BN, As, Bs, kt0,
-                                                                                            kt1);
+    k_share<BK>(a, tiles_m * tiles_n, &b, &kt0, &kt1);
+    tile_of(b, tiles_m, tiles_n, &tm, &tn);
+    mfma_tile<EB, BM, BN, BK, WM, WN, STAGES, WIDE, max_depth(EB == 4, BM, BN, WM, WN)>(a, tm * BM, tn * BN, lds, kt0, kt1);
 }
 
 template <int BM, int BN, int BK, int WM, int WN, int STAGES, bool WIDE = true, bool SPLIT = !WIDE>
-__device__ __forceinline__ void mfma_bf16(const MmArgs &a0) {
-    MmArgs a = a0;
-    if constexpr (!SPLIT || 64 * WM * WN > kSplittableThreads) a.splits = 0;
-    int tm, tn;
-    using L = Bf16Lds<BM, BN, BK, STAGES>;
-    __shared__ __attribute__((aligned(16))) unsigned short As[STAGES * L::A];
-    __shared__ __attribute__((aligned(16))) unsigned short Bs[STAGES * L::B];
-    int64_t b = blockIdx.x;
-    int kt0, kt1;
-    k_share<BK>(a, (int64_t)((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN), &b, &kt0, &kt1);
-    tile_of(b, (a.M + BM - 1) / BM, (a.N + BN - 1) / BN, &tm, &tn);
-    mfma_bf16_tile<BM, BN, BK, WM, WN, STAGES, WIDE, !WIDE>(a, tm * BM, tn * BN, As, Bs, kt0, kt1);
+__device__ __forceinline__ void mfma_f32(const MmArgs &a) {
+    __shared__ __attribute__((aligned(256))) unsigned char lds[f32_lds(BM, BN, BK, STAGES)];
+    mfma_product<4, BM, BN, BK, WM, WN, STAGES, WIDE, SPLIT>(a, lds);
+}
+
+template <int BM, int BN, int BK, int WM, int WN, int STAGES, bool WIDE = true, bool SPLIT = !WIDE>
+__device__ __forceinline__ void mfma_bf16(const MmArgs &a) {
+    __shared__ __attribute__((aligned(256))) unsigned char lds[bf16_lds(BM, BN, BK, STAGES)];
+    mfma_product<2, BM, BN, BK, WM, WN, STAGES, WIDE, SPLIT>(a, lds);
 }
 
 // ------------------------------------------------------------------ grouped (persistent)
@@ -882,7 +869,7 @@ __device__ __forceinline__ void walk_tiles(const GroupArgs &g, Tile &&tile) {
         const int64_t t2 = w.t + 2 * w.stride;
         const int gafter = t2 < w.end ? const_load(g.tile_group + t2) : gnext;
         const GroupDesc dn = const_load(g.descs + gnext);
-        __syncthreads();  // the previous tile's LDS reads are done
+        lds_barrier();  // the previous tile's LDS reads are done (its stores need not be)
         tile(d, (int)(w.t - d.tile_start));
         d = dn;
         gnext = gafter;
@@ -894,95 +881,55 @@ __device__ __forceinline__ void walk_tiles(const GroupArgs &g, Tile &&tile) {
 // element-load path -- fewer registers, one more resident wavefront per SIMD
 // for the 64 x 64 programs; the element-load twin (WIDE = false) runs the
 // products whose rows are not aligned.
+template <int EB, int BM, int BN, int BK, int WM, int WN, int STAGES, bool WIDE>
+__device__ __forceinline__ void grouped_tile(const GroupArgs &g, const GroupDesc &d, int local, unsigned char *lds) {
+    const int tm = local / d.tiles_n, tn = local % d.tiles_n;
+    const MmArgs a{d.A, d.B, d.C, d.lda, d.ldb, d.ldc, d.M, d.N, d.K, g.accumulate, WIDE, 0, 2};
+    mfma_tile<EB, BM, BN, BK, WM, WN, STAGES, WIDE, 2>(a, tm * BM, tn * BN, lds, 0, (d.K + BK - 1) / BK);
+}
+
 template <int BM, int BN, int BK, int WM, int WN, int STAGES, bool WIDE>
 __device__ __forceinline__ void grouped_f32(const GroupArgs &g) {
-    using L = F32Lds<BM, BN, BK, STAGES>;
-    __shared__ __attribute__((aligned(16))) float As[STAGES * L::A];
-    __shared__ __attribute__((aligned(16))) float Bs[STAGES * L::B];
-    walk_tiles(g, [&](const GroupDesc &d, int local) {
-        const int tm = local / d.tiles_n, tn = local % d.tiles_n;
-        const MmArgs a{d.A, d.B, d.C, d.lda, d.ldb, d.ldc, d.M, d.N, d.K, g.accumulate, WIDE};
-        mfma_f32_tile<BM, BN, BK, WM, WN, STAGES, WIDE, true>(a, tm * BM, tn * BN, As, Bs, 0, (d.K + BK - 1) / BK);
-    });
+    __shared__ __attribute__((aligned(256))) unsigned char lds[f32_lds(BM, BN, BK, STAGES)];
+    walk_tiles(g, [&](const GroupDesc &d, int local) { grouped_tile<4, BM, BN, BK, WM, WN, STAGES, WIDE>(g, d, local, lds); });
 }
 
 template <int BM, int BN, int BK, int WM, int WN, int STAGES, bool WIDE>
 __device__ __forceinline__ void grouped_bf16(const GroupArgs &g) {
-    using L = Bf16Lds<BM, BN, BK, STAGES>;
-    __shared__ __attribute__((aligned(16))) unsigned short As[STAGES * L::A];
-    __shared__ __attribute__((aligned(16))) unsigned short Bs[STAGES * L::B];
-    walk_tiles(g, [&](const GroupDesc &d, int local) {
-        const int tm = local / d.tiles_n, tn = local % d.tiles_n;
-        const MmArgs a{d.A, d.B, d.C, d.lda, d.ldb, d.ldc, d.M, d.N, d.K, g.accumulate, WIDE};
-        mfma_bf16_tile<BM, BN, BK, WM, WN, STAGES, WIDE, true>(a, tm * BM, tn * BN, As, Bs, 0, (d.K + BK - 1) / BK);
-    });
+    __shared__ __attribute__((aligned(256))) unsigned char lds[bf16_lds(BM, BN, BK, STAGES)];
+    walk_tiles(g, [&](const GroupDesc &d, int local) { grouped_tile<2, BM, BN, BK, WM, WN, STAGES, WIDE>(g, d, local, lds); });
 }
 
 // Mixed grouped kernels: each product's tiles run the program kMixedTile[prog]
 // of its descriptor; one LDS allocation, the largest program's, serves all.
-constexpr int cmax(int a, int b) { return a > b ? a : b; }
-
-template <int STAGES> struct MixedLds {
-    static constexpr int f32 =
-        cmax(cmax(F32Lds<kMixedTile[0][0], kMixedTile[0][1], kMixedBk[0], STAGES>::floats,
-                  F32Lds<kMixedTile[1][0], kMixedTile[1][1], kMixedBk[0], STAGES>::floats),
-             cmax(F32Lds<kMixedTile[2][0], kMixedTile[2][1], kMixedBk[0], STAGES>::floats,
-                  F32Lds<kMixedTile[3][0], kMixedTile[3][1], kMixedBk[0], STAGES>::floats));
-    static constexpr int bf16 =
-        cmax(cmax(Bf16Lds<kMixedTile[0][0], kMixedTile[0][1], kMixedBk[2], STAGES>::elems,
-                  Bf16Lds<kMixedTile[1][0], kMixedTile[1][1], kMixedBk[2], STAGES>::elems),
-             cmax(Bf16Lds<kMixedTile[2][0], kMixedTile[2][1], kMixedBk[2], STAGES>::elems,
-                  Bf16Lds<kMixedTile[3][0], kMixedTile[3][1], kMixedBk[2], STAGES>::elems));
-};
-
-template <int P, int STAGES, bool WIDE>
-__device__ __forceinline__ void mixed_f32_tile(const MmArgs &a, int local, int tiles_n, float *lds) {
-    constexpr int BM = kMixedTile[P][0], BN = kMixedTile[P][1];
-    const int tm = local / tiles_n, tn = local % tiles_n;
-    using L = F32Lds<BM, BN, kMixedBk[0], STAGES>;
-    mfma_f32_tile<BM, BN, kMixedBk[0], 2, 2, STAGES, WIDE, true>(a, tm * BM, tn * BN, lds,
-                                                           lds + STAGES * L::A, 0,
-                                                           (a.K + kMixedBk[0] - 1) / kMixedBk[0]);
+template <int EB, int STAGES> constexpr int mixed_lds() {
+    int n = 0;
+    for (int p = 0; p < kMixedPrograms; ++p)
+        n = cmax(n, EB == 4 ? f32_lds(kMixedTile[p][0], kMixedTile[p][1], kMixedBk[0], STAGES)
+                            : bf16_lds(kMixedTile[p][0], kMixedTile[p][1], kMixedBk[2], STAGES));
+    return n;
 }
 
-template <int P, int STAGES, bool WIDE>
-__device__ __forceinline__ void mixed_bf16_tile(const MmArgs &a, int local, int tiles_n, unsigned short *lds) {
-    constexpr int BM = kMixedTile[P][0], BN = kMixedTile[P][1];
-    const int tm = local / tiles_n, tn = local % tiles_n;
-    using L = Bf16Lds<BM, BN, kMixedBk[2], STAGES>;
-    mfma_bf16_tile<BM, BN, kMixedBk[2], 2, 2, STAGES, WIDE, true>(a, tm * BM, tn * BN, lds,
-                                                            lds + STAGES * L::A, 0,
-                                                            (a.K + kMixedBk[2] - 1) / kMixedBk[2]);
-}
-
-template <int STAGES, bool WIDE>
-__device__ __forceinline__ void grouped_mixed_f32(const GroupArgs &g) {
+template <int EB, int STAGES, bool WIDE>
+__device__ __forceinline__ void grouped_mixed(const GroupArgs &g) {
     static_assert(kMixedPrograms == 4, "one case per program");
-    __shared__ __attribute__((aligned(16))) float lds[MixedLds<STAGES>::f32];
+    constexpr int BK = kMixedBk[EB == 4 ? 0 : 2];
+    __shared__ __attribute__((aligned(256))) unsigned char lds[mixed_lds<EB, STAGES>()];
     walk_tiles(g, [&](const GroupDesc &d, int local) {
-        const MmArgs a{d.A, d.B, d.C, d.lda, d.ldb, d.ldc, d.M, d.N, d.K, g.accumulate, WIDE};
         switch (d.prog) {
-        case 0: mixed_f32_tile<0, STAGES, WIDE>(a, local, d.tiles_n, lds); break;
-        case 1: mixed_f32_tile<1, STAGES, WIDE>(a, local, d.tiles_n, lds); break;
-        case 2: mixed_f32_tile<2, STAGES, WIDE>(a, local, d.tiles_n, lds); break;
-        default: mixed_f32_tile<3, STAGES, WIDE>(a, local, d.tiles_n, lds); break;
+        case 0: grouped_tile<EB, kMixedTile[0][0], kMixedTile[0][1], BK, 2, 2, STAGES, WIDE>(g, d, local, lds); break;
+        case 1: grouped_tile<EB, kMixedTile[1][0], kMixedTile[1][1], BK, 2, 2, STAGES, WIDE>(g, d, local, lds); break;
+        case 2: grouped_tile<EB, kMixedTile[2][0], kMixedTile[2][1], BK, 2, 2, STAGES, WIDE>(g, d, local, lds); break;
+        default: grouped_tile<EB, kMixedTile[3][0], kMixedTile[3][1], BK, 2, 2, STAGES, WIDE>(g, d, local, lds); break;
         }
     });
 }
 
-template <int STAGES, bool WIDE>
-__device__ __forceinline__ void grouped_mixed_bf16(const GroupArgs &g) {
-    static_assert(kMixedPrograms == 4, "one case per program");
-    __shared__ __attribute__((aligned(16))) unsigned short lds[MixedLds<STAGES>::bf16];
-    walk_tiles(g, [&](const GroupDesc &d, int local) {
-        const MmArgs a{d.A, d.B, d.C, d.lda, d.ldb, d.ldc, d.M, d.N, d.K, g.accumulate, WIDE};
-        switch (d.prog) {
-        case 0: mixed_bf16_tile<0, STAGES, WIDE>(a, local, d.tiles_n, lds); break;
-        case 1: mixed_bf16_tile<1, STAGES, WIDE>(a, local, d.tiles_n, lds); break;
-        case 2: mixed_bf16_tile<2, STAGES, WIDE>(a, local, d.tiles_n, lds); break;
-        default: mixed_bf16_tile<3, STAGES, WIDE>(a, local, d.tiles_n, lds); break;
-        }
-    });
+template <int STAGES, bool WIDE> __device__ __forceinline__ void grouped_mixed_f32(const GroupArgs &g) {
+    grouped_mixed<4, STAGES, WIDE>(g);
+}
+template <int STAGES, bool WIDE> __device__ __forceinline__ void grouped_mixed_bf16(const GroupArgs &g) {
+    grouped_mixed<2, STAGES, WIDE>(g);
 }
 
 }  // namespace pkk

@@ -131,7 +131,11 @@ double estimate_program(const pk_machine &m, const KernelEntry &e, int64_t resid
         waves_per_simd >= 3.0 ? 1.0 : std::min(1.0, std::pow(waves_per_simd / 3.0, mfma ? 0.4 : 0.25));
     // MFMA: the tile's LDS words per output; VALU: workgroups of fewer than
     // 256 work-items lose in proportion
-    const double eff = mfma ? 0.85 / (1.0 + 6.0 * (1.0 / e.tile_m + 1.0 / e.tile_n))
+    // (wide bfloat16 wavefronts of more rows than columns have registers for
+    // two buffers of K steps only where the others have three, max_depth:
+    // 4096^3, operands from HBM, 151 us on 256 x 128 tiles and 124 on 128 x 256)
+    const bool shallow = mfma && wide && dtype == PK_BF16 && pkk::max_depth(false, e.bm, e.bn, e.wm, e.wn) < 3;
+    const double eff = mfma ? (shallow ? 0.72 : 0.85) / (1.0 + 6.0 * (1.0 / e.tile_m + 1.0 / e.tile_n))
                             : std::min(1.0, e.threads / 256.0);
     const double rate = prate * clock * eff * occupancy;
     const double latency = mfma ? ((e.variant & PK_MFMA_SINGLE) ? 0.4e-6 : 0.3e-6) : 0.1e-6;
@@ -199,7 +203,7 @@ std::vector<Candidate> feasible(const pk_table *tbl, int dtype, int64_t M, int64
     for (int family : {PK_FAMILY_VALU, PK_FAMILY_VALU2, PK_FAMILY_MFMA}) {  // the product families
         const pk_table::Part *part = tbl->part(family, dtype);
         if (!part || !part->supported) continue;
-        // MFMA programs read unaligned rows element by element: feasible, slower
+        // MFMA programs read unaligned rows at element alignment: feasible, slower
         const bool wide = !A || family != PK_FAMILY_MFMA || wide_rows(dtype, A, lda, B, ldb);
         const int64_t ncu = std::max<int32_t>(tbl->machine.cu_count, 1);
         for (size_t i = 0; i < part->programs.size(); ++i) {

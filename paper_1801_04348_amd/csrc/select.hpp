@@ -78,6 +78,7 @@ int64_t grid_of(const pk_machine &m, const KernelEntry &e, int64_t M, int64_t N)
 int64_t live_blocks_per_cu(const pk_machine &m, const KernelEntry &e);
 int64_t launch_grid(const pk_machine &m, const KernelEntry &e, int64_t M, int64_t N);
 bool wide_rows(int dtype, const void *A, int64_t lda, const void *B, int64_t ldb);
+int dma_depth(const pk_machine &m, const KernelEntry &e, int64_t resident, int64_t ksteps, int *extra);
 int launch(const pk_machine &m, const KernelEntry &e, const MmArgs &args, hipStream_t stream);
 void fill_params(const pk_table *tbl, const Candidate &c, int dtype, pk_params *out);
 int resolve(const pk_table *tbl, const pk_params *pin, int dtype, pk_params *pout, const KernelEntry **entry);
