@@ -45,6 +45,7 @@
 #include <cmath>
 #include <cstring>
 #include <map>
+#include <tuple>
 #include <memory>
 #include <numeric>
 #include <stdexcept>
@@ -126,17 +127,43 @@ bool live(const GroupedOperands &o, int g) { return o.M[g] > 0 && o.N[g] > 0; }
 // descriptor, then its first K step's operands, loads each waiting on the
 // last) and closing (its stores), which nothing in its workgroup overlaps:
 // its tiles are a few K steps long and run one after another.  Only the
-// other workgroups resident on the compute unit hide it.  Set so that the
-// estimate ranks programs as measured on 4096 uneven float32 products of
-// 16-512: the 64 x 64 programs of one and two LDS stages, which
-// tile_work_seconds rates alike, hold 5 and 4 resident workgroups, and the
-// single-stage one runs the products 15 % faster.
-constexpr double kTileOpenClose = 5e-6;
+// other workgroups resident on the compute unit hide it.
+constexpr double kTileOpenClose = 3e-6;
+
+// Work of the mixed kernels against a uniform launch of the same tiles: they
+// hold the registers of their largest program and its LDS.  Unaligned
+// bfloat16 groups of 836, 1024 and 1562 products: 37-39, 72-82 and 112-119 us
+// on the mixed kernel, 31, 70 and 105 on the best uniform one.
+constexpr double kMixedWork = 1.25;
+
+// Workgroups of a grouped launch per compute unit whose tiles run `ksteps` K
+// tiles: all that fit while tiles are short and opening them is what the
+// others hide (2000 float32 products of 16-150, two K tiles each on average:
+// 30.6 us with the 8 that the 64 x 64 single-stage program has room for, 35.7
+// with 4), at most 16 wavefronts from three K tiles up, where more only put
+// more products' panels into an XCD's L2 at once (4096 products of 16-512: 429
+// us with 8, 359 with 4, 380 with 3).
+int64_t resident_workgroups(const pk_machine &m, const KernelEntry &e, double ksteps) {
+    const int64_t live = live_blocks_per_cu(m, e);
+    return ksteps < 3.0 ? live : std::min<int64_t>(live, std::max(1, 1024 / e.threads));
+}
+
+double ksteps_of(const KernelEntry &e, int64_t K) {
+    const int64_t bk = e.bk > 0 ? e.bk : 1;
+    return (double)((std::max<int64_t>(K, 1) + bk - 1) / bk);
+}
 
 // Estimated compute-unit seconds of a product under a grouped program.
 double product_cost(const pk_machine &m, const KernelEntry &e, int dtype, int64_t M, int64_t N, int64_t K) {
     const int64_t tiles = ((M + e.tile_m - 1) / e.tile_m) * ((N + e.tile_n - 1) / e.tile_n);
-    return tile_work_seconds(m, e, dtype, M, N, K) + (double)tiles * kTileOpenClose / (double)live_blocks_per_cu(m, e);
+    const int64_t res = resident_workgroups(m, e, ksteps_of(e, K));
+    const double work = tile_work_seconds(m, e, dtype, M, N, K, res) + (double)tiles * kTileOpenClose / (double)res;
+    return (e.variant & PK_MFMA_MIXED) ? kMixedWork * work : work;
+}
+
+// Estimated seconds of one tile with a compute unit to itself.
+double lone_tile_seconds(const pk_machine &m, const KernelEntry &e, int dtype, int64_t K) {
+    return tile_work_seconds(m, e, dtype, e.tile_m, e.tile_n, K, 1) + kTileOpenClose;
 }
 
 // The grouped kernel form a product runs in: the wide kernel when its rows
@@ -273,10 +300,25 @@ bool assign_mixed(const pk_table *tbl, int dtype, const GroupedOperands &o, cons
     return true;
 }
 
-double total_cost(const std::vector<Assign> &as) {
-    double t = 0.0;
-    for (const auto &a : as) t += a.cost;
-    return t;
+// Estimated seconds of an assignment: its work spread over the compute
+// units, and no less than its longest tile.  The second term decides groups of
+// few products, which leave compute units empty under large tiles: 38 bfloat16
+// products of 16-388, unaligned, ran 13.1 us on the mixed program that their
+// work alone prefers and 8.3 on 64 x 64 tiles.
+double assignment_seconds(const pk_table *tbl, int dtype, const GroupedOperands &o, const std::vector<Assign> &as) {
+    double work = 0.0, longest = 0.0;
+    std::map<std::tuple<const KernelEntry *, int, int64_t>, double> lone;  // by program and K
+    for (int g = 0; g < o.G; ++g) {
+        const Assign &a = as[g];
+        if (!a.entry) continue;
+        work += a.cost;
+        auto it = lone.emplace(std::make_tuple(a.entry, a.prog, o.K[g]), 0.0);
+        if (it.second)
+            it.first->second = lone_tile_seconds(
+                tbl->machine, (a.entry->variant & PK_MFMA_MIXED) ? as_program(*a.entry, a.prog) : *a.entry, dtype, o.K[g]);
+        longest = std::max(longest, it.first->second);
+    }
+    return std::max(work / std::max<int32_t>(tbl->machine.cu_count, 1), longest);
 }
 
 // A mixed assignment whose products all run one program runs that program's
@@ -338,13 +380,15 @@ int build_from(const pk_table *tbl, int dtype, const GroupedOperands &o, const s
         // stores of its results.  Without that term tiles of one or two K
         // steps count as nearly free and the XCD that gets them runs last.
         std::vector<double> tile_cost(o.G, 0.0);
+        double ksteps = 0.0;
         for (int g : gs) {
             const Assign &a = as[g];
             tiles[g] = ((o.M[g] + a.tile_m - 1) / a.tile_m) * ((o.N[g] + a.tile_n - 1) / a.tile_n);
             const KernelEntry pe = (a.entry->variant & PK_MFMA_MIXED) ? as_program(*a.entry, a.prog) : *a.entry;
-            const int64_t bk = pe.bk > 0 ? pe.bk : 1;
-            const double ks = (double)((std::max<int64_t>(o.K[g], 1) + bk - 1) / bk);
-            tile_cost[g] = tile_work_seconds(tbl->machine, pe, dtype, pe.tile_m, pe.tile_n, o.K[g]) * (ks + 1.0) / ks;
+            const double ks = ksteps_of(pe, o.K[g]);
+            tile_cost[g] = tile_work_seconds(tbl->machine, pe, dtype, pe.tile_m, pe.tile_n, o.K[g],
+                                             resident_workgroups(tbl->machine, pe, ks)) * (ks + 1.0) / ks;
+            ksteps += ks * (double)tiles[g];
         }
         // most expensive tiles first
         std::stable_sort(gs.begin(), gs.end(), [&](int x, int y) { return tile_cost[x] > tile_cost[y]; });
@@ -395,8 +439,9 @@ int build_from(const pk_table *tbl, int dtype, const GroupedOperands &o, const s
         while (bin <= kXcds) L.bins[bin++] = t;
         L.ndesc = (int64_t)lay.descs.size() - L.first_desc;
         L.total_tiles = t;
-        L.grid = std::max<int64_t>(1, std::min<int64_t>(t, (int64_t)tbl->machine.cu_count *
-                                                             live_blocks_per_cu(tbl->machine, *e)));
+        L.grid = std::max<int64_t>(
+            1, std::min<int64_t>(t, (int64_t)tbl->machine.cu_count *
+                                        resident_workgroups(tbl->machine, *e, ksteps / (double)std::max<int64_t>(t, 1))));
         lay.launches.push_back(L);
     }
     *out = std::move(lay);
@@ -570,8 +615,14 @@ int grouped_layout(const pk_table *tbl, int dtype, const GroupedOperands &o, con
     rc = candidate_assignments(tbl, dtype, o, f, false, &cands);
     if (rc != PK_OK) return rc;
     size_t best = 0;
-    for (size_t i = 1; i < cands.size(); ++i)
-        if (total_cost(cands[i]) < total_cost(cands[best])) best = i;
+    double best_seconds = 0.0;
+    for (size_t i = 0; i < cands.size(); ++i) {
+        const double seconds = assignment_seconds(tbl, dtype, o, cands[i]);
+        if (i == 0 || seconds < best_seconds) {
+            best = i;
+            best_seconds = seconds;
+        }
+    }
     return build_from(tbl, dtype, o, cands[best], out);
 }
 

@@ -166,14 +166,14 @@ double estimate_seconds(const pk_machine &m, const KernelEntry &e, int dtype, in
     return estimate_program(m, e, blocks_per_cu(m, e), product_rate(m, e, dtype), dtype, M, N, K, wide, ks);
 }
 
-double tile_work_seconds(const pk_machine &m, const KernelEntry &e, int dtype, int64_t M, int64_t N, int64_t K) {
-    // compute-unit seconds of the product's tiles when the unit is kept full
-    // of this program's workgroups: a unit advances its resident tiles by one
-    // K step in max(res * flops_step / rate, latency)
+double tile_work_seconds(const pk_machine &m, const KernelEntry &e, int dtype, int64_t M, int64_t N, int64_t K,
+                         int64_t res) {
+    // compute-unit seconds of the product's tiles when the unit holds `res`
+    // of this program's workgroups at a time: it advances them by one K step
+    // in max(res * flops_step / rate, latency)
     const double clock = (m.clock_khz > 0 ? m.clock_khz : 2400000) * 1e3;
     const int wave = m.wave > 0 ? m.wave : 64;
     const int64_t tiles = ((M + e.tile_m - 1) / e.tile_m) * ((N + e.tile_n - 1) / e.tile_n);
-    const int64_t res = blocks_per_cu(m, e);
     const int bk = e.bk > 0 ? e.bk : 1;
     const double ksteps = (double)((std::max<int64_t>(K, 1) + bk - 1) / bk);
     const double flops_step = 2.0 * e.tile_m * e.tile_n * bk;

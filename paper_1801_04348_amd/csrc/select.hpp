@@ -31,9 +31,10 @@ double estimate_seconds(const pk_machine &m, const KernelEntry &e, int dtype, in
                         bool wide = true, int ks = 1);
 
 // Compute-unit seconds of a product's tiles under a program when every
-// compute unit is kept full of its workgroups (the work a persistent grouped
-// launch spends on the product).
-double tile_work_seconds(const pk_machine &m, const KernelEntry &e, int dtype, int64_t M, int64_t N, int64_t K);
+// compute unit holds `res` of its workgroups at a time (the work a persistent
+// grouped launch spends on the product).
+double tile_work_seconds(const pk_machine &m, const KernelEntry &e, int dtype, int64_t M, int64_t N, int64_t K,
+                         int64_t res);
 
 // Analytic time of one launch of a streaming (HBM-bound) kernel moving
 // `bytes`: compulsory bytes over 8 TB/s, scaled by the share one launch can
