@@ -185,13 +185,12 @@ def instances():
                 # (a translation unit of its own: compiled beside the wide kernel
                 # it changes the wide kernel's instruction schedule, measurably)
                 out.append(("mfma_%s_%d_el" % (DT_NAME[dt], bm * 1000 + bn), name + "_el", body_el, entry_el))
-    # int32 on the int8 matrix cores: a wide form (16-byte loads of A where its
-    # rows are aligned) and its element-load twin; no split form.  Wave tiles
-    # of two 32 x 32 blocks hold 128 accumulator registers (four sums per
-    # block): those programs are capped at 256 registers a lane, the block
-    # budget of 65536 over 256 work-items.
+    # int32 on the int8 matrix cores: one form, listed for aligned rows and as
+    # their element-load twin; no split form.  Capped at 256 registers a lane,
+    # the block budget of 65536 over 256 work-items (four sums per 32 x 32 block
+    # and the next digits beside the current ones).
     for (bm, bn, bk, wm, wn) in MFMA_I32:
-        cap = "__attribute__((amdgpu_waves_per_eu(2)))" if bm * bn > 64 * 64 else ""
+        cap = "__attribute__((amdgpu_waves_per_eu(2)))"
         for stages in (2, 1):
             name = "pk_mfma_i32_%dx%dx%d_w%dx%d_st%d" % (bm, bn, bk, wm, wn, stages)
             entry = dict(family=FAM_MFMA, variant=0 if stages == 2 else MFMA_SINGLE, dtype=I32,
@@ -199,7 +198,7 @@ def instances():
                          lds=mfma_lds(I32, bm, bn, bk, stages), tile_m=bm, tile_n=bn, attrs=cap)
             body = "pkk::mfma_i32<%d, %d, %d, %d, %d, %d>(a);" % (bm, bn, bk, wm, wn, stages)
             out.append(("mfma_i32", name, body, entry))
-            body_el = "pkk::mfma_i32<%d, %d, %d, %d, %d, %d, false>(a);" % (bm, bn, bk, wm, wn, stages)
+            body_el = body
             entry_el = dict(entry, variant=entry["variant"] | MFMA_ELEMENT)
             out.append(("mfma_i32_el", name + "_el", body_el, entry_el))
     # transposition: tiled and direct programs (bit copies of 4-byte elements)

@@ -113,3 +113,21 @@ def test_order_1024_every_program(table, programs):
         assert np.array_equal(run(table, params(pt, v), Ad, Bd), ref), (pt, v)
     # and whatever CASE picks there
     assert np.array_equal(run(table, None, Ad, Bd), ref)
+
+
+@pytest.mark.parametrize("r", [0, 1, 30])
+def test_steps_around_the_pipeline(table, programs, r):
+    """One to seven K steps, whole and ragged (one element over, two short),
+    in rows whose surroundings are not zero."""
+    M, N = 65, 130
+    for bk in (32, 64):
+        for K in {max(1, n * bk + r - (32 if r == 30 else 0)) for n in range(1, 8)}:
+            A = inputs.full_range_i32((M, K), seed=51 + K)
+            B = inputs.full_range_i32((K, N), seed=52 + K)
+            ref = om.matmul(A, B, "i32")
+            a = inputs.full_range_i32((M + 1, K + 5), seed=53).cuda()
+            b = inputs.full_range_i32((K + 1, N + 3), seed=54).cuda()
+            a[:M, 3:3 + K], b[:K, 1:1 + N] = A.cuda(), B.cuda()
+            for pt, v in programs:
+                C = run(table, params(pt, v), a[:M, 3:3 + K], b[:K, 1:1 + N])
+                assert np.array_equal(C, ref), (pt, v, K)
