@@ -325,7 +325,7 @@ int pk_case_table_build(int device, const pk_machine *override_or_null, pk_table
                         p.variant = (int)part.solved.leaves[part.first_leaf[i]].applied;
                         p.entry = find_instance(family, p.variant, dtype, part.fam.points[i]);
                         if (!p.entry) continue;
-                        p.resident = blocks_per_cu(m, *p.entry);
+                        p.resident = estimate_residency(m, *p.entry);
                         p.rate = product_rate(m, *p.entry, dtype);
                         if (family != PK_FAMILY_MFMA) continue;
                         p.twin = element_twin(*p.entry);

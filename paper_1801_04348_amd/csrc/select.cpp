@@ -4,23 +4,22 @@
 // CASE: the paper fixes the leaf for given parameters by the case discussion
 // and leaves the program parameters to auto-tuning (Section 1); here they are
 // chosen by an analytic estimate of the launch time:
-//   tiles     = ceil(M / tile_m) * ceil(N / tile_n)
-//   occupancy = workgroups resident per compute unit (LDS, registers, threads,
-//               workgroup slots, as the bound machine reports them)
-//   rounds    = ceil(tiles / (compute units * occupancy))
-//   per round = max(occupancy * 2 * tile_m * tile_n * K / (rate * eff * clock),
-//                   K steps * step latency)
+//   tiles     = ceil(M / tile_m) * ceil(N / tile_n) * shares of K
+//   rounds    : the busiest compute unit's tiles, by as many as it holds at a
+//               time (LDS, registers, threads, workgroup slots)
+//   per round = K steps * max(workgroups * 2 * tile_m * tile_n * bk / rate,
+//                             step latency) + opening and closing
 //               rate: per-CU throughput of the program's inner loop (matrix
 //               cores; or VALU multiply-adds limited by the LDS words read per
-//               multiply-add); eff: the share of that rate a tile sustains,
-//               falling with the LDS/L2 words moved per flop, 1/tile_m +
-//               1/tile_n; step latency: one global-load round trip plus the
-//               barriers of a K step, hidden in part by a second LDS stage
+//               multiply-add), the share of it that a tile sustains falling
+//               with the words moved per flop, 1/tile_m + 1/tile_n, and with
+//               too few wavefronts to hide latencies; step latency: one
+//               global-load round trip plus the barriers of a K step
 //   traffic   = bytes the tiles read (each tile reads its A and B panels) over
-//               an on-chip cache bandwidth, and compulsory bytes over HBM
-//   estimate  = max(rounds * per round, traffic) + a fixed launch cost
-// The constants (eff's shape, step latencies) were set from event timings of
-// these kernels on gfx950; the estimate only has to rank candidates.
+//               an on-chip cache bandwidth, and the operands' bytes over HBM
+//   estimate  = max(rounds, traffic) + a fixed launch cost
+// The constants were fitted to event timings of these kernels on gfx950; the
+// estimate only has to rank candidates.
 // EXHAUSTIVE: every candidate is launched and timed with HIP events on the
 // device (back-to-back launches, mean), the least CASE estimate first; a
 // candidate whose first three launches are already 1.5x slower than the best
@@ -30,6 +29,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <limits>
 #include <stdexcept>
 
@@ -38,7 +38,6 @@ namespace pk {
 namespace {
 constexpr double kLaunchSeconds = 4e-6;
 constexpr double kHbmBytesPerSecond = 8e12;
-constexpr double kAtomicAddsPerSecond = 4e11;  // float atomic additions to C, whole device
 
 int elem_bytes(int dtype) { return dtype == PK_BF16 ? 2 : 4; }
 
@@ -101,69 +100,128 @@ double streaming_seconds(const pk_machine &m, const KernelEntry &e, double bytes
 
 namespace {
 
+// The MFMA programs' estimate, by element type.  Fitted to the timings of
+// every candidate of 260 (float32, bfloat16) or 130 (int32) products of 64 to
+// 8192 along each dimension, packed and padded rows, three sets of operands in
+// turn, so that the least estimate is the fastest program or close to it:
+// half of the products to fit, half to check.  The choice's mean time over the
+// fastest's, before and with these: float32 1.049 and 1.021, bfloat16 1.040
+// and 1.014, int32 1.186 and 1.039.
+struct MfmaFit {
+    double waves;          // wavefronts a SIMD needs to hide latencies (fourth root below)
+    double eff, edge;      // share of the peak rate eff / (1 + edge (1 / tile_m + 1 / tile_n))
+    double lat1, lat2;     // least seconds of a K step, single-stage and two-stage programs
+    double narrow, nlat;   // factors on both where rows are not aligned
+    double shallow;        // arithmetic of wide wavefronts that have registers for two
+                           // buffers of K steps only (max_depth): bfloat16 of order 4096,
+                           // 151 us on 256 x 128 tiles and 124 on 128 x 256
+    double open;           // seconds a tile opens and closes in
+    double panels, hbm;    // bytes per second of the tiles' panels, and of the operands once
+    double split, adds;    // a split product's second launch (2 us of the device, but 4 of
+                           // the caller's thread: float32 of order 256, 9.4 us a call on
+                           // one launch, 12.9 split); atomic additions per second
+    double launch;         // seconds
+};
+constexpr MfmaFit kFit[3] = {
+    /* float32  */ {1.16, 1.03, 2.28, 2.0e-6, 0.228e-6, 1.28, 3.33, 1.0, 1.17e-6, 9.67e12, 1.79e12, 4e-6, 4.18e11, 2.4e-6},
+    /* int32    */ {5.76, 1.12, 6.9, 0.324e-6, 0.174e-6, 1.1, 1.0, 1.0, 1.95e-6, 25e12, 0.82e12, 5.5e-6, 0.55e11, 2.18e-6},
+    /* bfloat16 */ {2.1, 0.938, 14.5, 0.05e-6, 0.156e-6, 2.29, 2.92, 1.19, 2.01e-6, 11.8e12, 4.2e12, 4e-6, 4.49e11, 1.84e-6},
+};
+
+double fourth(double x) { return x * x * x * x; }
+double fourth_root(double x) { return std::sqrt(std::sqrt(x)); }
+
+// The launch's seconds under an MFMA program of which a compute unit holds
+// `resident` workgroups: the busiest unit runs its tiles in rounds of the
+// resident ones, a K step of a round taking the larger of the tiles'
+// arithmetic and one step's latency; beside that the panels' and the operands'
+// bytes, the largest of the three deciding (all three soft, as fourth powers'
+// sums).
+double estimate_mfma(const pk_machine &m, const KernelEntry &e, int64_t resident, double prate, int dtype, int64_t M,
+                     int64_t N, int64_t K, bool wide, int ks) {
+    const MfmaFit &f = kFit[dtype];
+    const double clock = (m.clock_khz > 0 ? m.clock_khz : 2400000) * 1e3;
+    const int64_t ncu = std::max<int32_t>(m.cu_count, 1);
+    const int wave = m.wave > 0 ? m.wave : 64;
+    const int64_t tiles = std::max<int64_t>(((M + e.tile_m - 1) / e.tile_m) * ((N + e.tile_n - 1) / e.tile_n), 1) * ks;
+    const int64_t per_cu = (tiles + ncu - 1) / ncu;
+    const int64_t res = std::min(resident, per_cu), full = per_cu / res, rest = per_cu % res;
+    const int bk = e.bk > 0 ? e.bk : 1;
+    const double ksteps = std::ceil((double)((std::max<int64_t>(K, 1) + bk - 1) / bk) / ks);
+    const bool shallow = wide && dtype == PK_BF16 && pkk::max_depth(false, e.bm, e.bn, e.wm, e.wn) < 3;
+    const double flops = 2.0 * e.tile_m * e.tile_n * bk * (wide ? 1.0 : f.narrow) * (shallow ? f.shallow : 1.0);
+    const double rate = prate * clock * f.eff / (1.0 + f.edge * (1.0 / e.tile_m + 1.0 / e.tile_n));
+    const double latency = ((e.variant & PK_MFMA_SINGLE) ? f.lat1 : f.lat2) * (wide ? 1.0 : f.nlat) *
+                           (dtype == PK_I32 ? bk / 32.0 : 1.0);  // (int32: the digits of every 32 k)
+    auto round = [&](int64_t r) {
+        if (r <= 0) return 0.0;
+        const double waves = (double)r * ((e.threads + wave - 1) / wave) / 4.0;
+        const double work = (double)r * flops / (rate * fourth_root(std::min(1.0, waves / f.waves)));
+        return ksteps * fourth_root(fourth(work) + fourth(latency)) + f.open;
+    };
+    const double compute = (double)full * round(res) + round(rest);
+    const double es = elem_bytes(dtype);
+    // each workgroup reads its A and B panels over its share of K
+    const double panels = es * (double)tiles * std::ceil((double)K / ks) * (e.tile_m + e.tile_n) / f.panels;
+    const double hbm = (es * ((double)M * K + (double)K * N) + 4.0 * (double)M * N) / f.hbm;
+    // shares of K: clearing C (a second launch) and one atomic addition per
+    // output and share
+    const double split = ks > 1 ? f.split + 4.0 * (double)M * N / 5e12 + (double)ks * M * N / f.adds : 0.0;
+    return fourth_root(fourth(compute) + fourth(panels) + fourth(hbm)) + split + f.launch;
+}
+
 // estimate_seconds with the program's residency and rate given (the bound
 // table holds them per point)
 double estimate_program(const pk_machine &m, const KernelEntry &e, int64_t resident, double prate, int dtype,
                         int64_t M, int64_t N, int64_t K, bool wide, int ks) {
-    // Per compute unit: the busiest one holds ceil(tiles / NCU) tiles, `res`
-    // of them resident at once; each K step of a round costs the larger of
-    // the resident tiles' arithmetic at the unit's rate and one step's
-    // latency.  The rate falls when few wavefronts share a SIMD to hide LDS
-    // and memory latency (full at about three per SIMD), and for MFMA tiles
-    // with the LDS words each output needs (1/tile_m + 1/tile_n).
+    ks = std::max(ks, 1);
+    if (e.family == PK_FAMILY_MFMA) return estimate_mfma(m, e, resident, prate, dtype, M, N, K, wide, ks);
+    // VALU programs.  Per compute unit: the busiest one holds
+    // ceil(tiles / NCU) tiles, `res` of them resident at once; each K step of
+    // a round costs the larger of the resident tiles' arithmetic at the unit's
+    // rate and one step's latency, and two barriers per resident workgroup.
+    // The rate falls when few wavefronts share a SIMD to hide LDS and memory
+    // latency (full at about three per SIMD), and where workgroups have fewer
+    // than 256 work-items, in proportion.
     const double clock = (m.clock_khz > 0 ? m.clock_khz : 2400000) * 1e3;
     const int64_t ncu = std::max<int32_t>(m.cu_count, 1);
     const int wave = m.wave > 0 ? m.wave : 64;
     const int64_t tm = (M + e.tile_m - 1) / e.tile_m, tn = (N + e.tile_n - 1) / e.tile_n;
-    ks = std::max(ks, 1);
-    // a product split along K runs ks workgroups per tile, each over its share
-    const int64_t tiles = std::max<int64_t>(tm * tn, 1) * ks;
+    const int64_t tiles = std::max<int64_t>(tm * tn, 1);
     const int64_t per_cu = (tiles + ncu - 1) / ncu;
     const int64_t res = std::min(resident, per_cu);
     const int64_t rounds = (per_cu + res - 1) / res;
     const int bk = e.bk > 0 ? e.bk : 1;
-    const double ksteps = std::ceil((double)((std::max<int64_t>(K, 1) + bk - 1) / bk) / ks);
+    const double ksteps = (double)((std::max<int64_t>(K, 1) + bk - 1) / bk);
     const double flops_step = 2.0 * e.tile_m * e.tile_n * bk;
     const double waves_per_simd = (double)res * ((e.threads + wave - 1) / wave) / 4.0;
-    const bool mfma = e.family == PK_FAMILY_MFMA;
-    const bool vi32 = !mfma && dtype == PK_I32;  // int32 VALU: its own fitted barrier cost
-    const double occupancy =
-        waves_per_simd >= 3.0 ? 1.0 : std::min(1.0, std::pow(waves_per_simd / 3.0, mfma ? 0.4 : 0.25));
-    // MFMA: the tile's LDS words per output; VALU: workgroups of fewer than
-    // 256 work-items lose in proportion
-    // (wide bfloat16 wavefronts of more rows than columns have registers for
-    // two buffers of K steps only where the others have three, max_depth:
-    // 4096^3, operands from HBM, 151 us on 256 x 128 tiles and 124 on 128 x 256)
-    const bool shallow = mfma && wide && dtype == PK_BF16 && pkk::max_depth(false, e.bm, e.bn, e.wm, e.wn) < 3;
-    const double eff = mfma ? (shallow ? 0.72 : 0.85) / (1.0 + 6.0 * (1.0 / e.tile_m + 1.0 / e.tile_n))
-                            : std::min(1.0, e.threads / 256.0);
-    const double rate = prate * clock * eff * occupancy;
-    const double latency = mfma ? ((e.variant & PK_MFMA_SINGLE) ? 0.4e-6 : 0.3e-6) : 0.1e-6;
-    // VALU K steps also pay their two barriers per resident workgroup
-    const double overhead = mfma ? 0.0 : (vi32 ? 0.1e-6 : 0.4e-6) * (double)res;
-    // element loads instead of 16-byte loads (rows not aligned): measured
-    // about 1.4x (f32) and 3.5x (bf16) slower per step, measured with the
-    // same programs both ways at 2048^3 and 4096^3
-    const double narrow = (mfma && !wide) ? (dtype == PK_BF16 ? 3.5 : dtype == PK_I32 ? 1.2 : 1.4) : 1.0;
-    const double compute =
-        narrow * (double)rounds * ksteps * (std::max((double)res * flops_step / rate, latency) + overhead);
+    const double occupancy = waves_per_simd >= 3.0 ? 1.0 : fourth_root(waves_per_simd / 3.0);
+    const double rate = prate * clock * std::min(1.0, e.threads / 256.0) * occupancy;
+    const double latency = 0.1e-6;
+    const double overhead = (dtype == PK_I32 ? 0.1e-6 : 0.4e-6) * (double)res;  // (each type's fitted)
+    const double compute = (double)rounds * ksteps * (std::max((double)res * flops_step / rate, latency) + overhead);
     const double es = elem_bytes(dtype);
-    // each workgroup reads its A and B panels over its share of K
-    const double tile_bytes = es * (double)tiles * std::ceil((double)K / ks) * (e.tile_m + e.tile_n);
+    const double tile_bytes = es * (double)tiles * (double)K * (e.tile_m + e.tile_n);
     const double hbm = (es * ((double)M * K + (double)K * N) + 4.0 * (double)M * N) / kHbmBytesPerSecond;
-    // shares of K: clearing C (a second launch) and one atomic addition per
-    // output and share
-    const double split = ks > 1 ? kLaunchSeconds + 4.0 * (double)M * N / kHbmBytesPerSecond +
-                                      (double)ks * M * N / kAtomicAddsPerSecond
-                                : 0.0;
-    return std::max(compute, std::max(tile_bytes / kHbmBytesPerSecond, hbm)) + split + kLaunchSeconds;
+    return std::max(compute, std::max(tile_bytes / kHbmBytesPerSecond, hbm)) + kLaunchSeconds;
 }
 
 }  // namespace
 
+// The workgroups the estimate takes a compute unit to hold.  MFMA programs:
+// what gfx950's registers (512 a lane and SIMD), LDS and wave slots admit; the
+// runtime's register figure, which the case table takes as reported, may be
+// half of that.  Others: the model's count, to which their estimate is fitted.
+int64_t estimate_residency(const pk_machine &m, const KernelEntry &e) {
+    if (e.family != PK_FAMILY_MFMA || std::strncmp(m.arch, "gfx950", 6) != 0) return blocks_per_cu(m, e);
+    pk_machine hw = m;
+    hw.regs_cu = std::max<int64_t>(m.regs_cu, 131072);
+    return blocks_per_cu(hw, e);
+}
+
 double estimate_seconds(const pk_machine &m, const KernelEntry &e, int dtype, int64_t M, int64_t N, int64_t K,
                         bool wide, int ks) {
-    return estimate_program(m, e, blocks_per_cu(m, e), product_rate(m, e, dtype), dtype, M, N, K, wide, ks);
+    return estimate_program(m, e, estimate_residency(m, e), product_rate(m, e, dtype), dtype, M, N, K, wide, ks);
 }
 
 double tile_work_seconds(const pk_machine &m, const KernelEntry &e, int dtype, int64_t M, int64_t N, int64_t K,

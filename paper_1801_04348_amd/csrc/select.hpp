@@ -30,6 +30,9 @@ std::vector<Candidate> feasible(const pk_table *tbl, int dtype, int64_t M, int64
 double estimate_seconds(const pk_machine &m, const KernelEntry &e, int dtype, int64_t M, int64_t N, int64_t K,
                         bool wide = true, int ks = 1);
 
+// Workgroups of a program a compute unit holds, for its estimate.
+int64_t estimate_residency(const pk_machine &m, const KernelEntry &e);
+
 // Compute-unit seconds of a product's tiles under a program when every
 // compute unit holds `res` of its workgroups at a time (the work a persistent
 // grouped launch spends on the product).
