@@ -510,22 +510,34 @@ __device__ __forceinline__ void regs_tile(const MmArgs &a, const int row0, const
     const bool interior = (row0 + BM <= M) && (col0 + BN <= N);
     const bool idle = NT <= 512 && t.idle(a, row0, col0);  // (1024 work-items: registers at the limit)
 
-    u32x4 ra[AL], rb[BL];
+    // the chunks of one K step
+    struct Set {
+        u32x4 a[AL], b[BL];
+    };
+    constexpr int SETS = STAGES == 1 || NT >= 512 ? 1 : AL + BL <= 4 ? (EB == 2 ? 4 : 2) : AL + BL <= 8 && EB == 2 ? 2 : 1;
     // row and first element of this work-item's u-th chunks
     auto a_row = [&](int u) { return (tid + u * NT) / AC; };
     auto a_k = [&](int u) { return (tid + u * NT) % AC * VE; };
     auto b_row = [&](int u) { return (tid + u * NT) / BC; };
     auto b_col = [&](int u) { return (tid + u * NT) % BC * VE; };
-    // a K step that lies wholly inside the operands: no guards, so the loads
-    // issue back to back (guarded loads branch per load, and the compiler
-    // then waits for each load before the next)
-    auto gload_fast = [&](int k0) {
+    const bool tiny = !WIDE && (a.K < VE || N < VE);
+    const int sk = WIDE ? 0 : (VE - (K & (VE - 1))) & (VE - 1), sn = WIDE ? 0 : (VE - (N & (VE - 1))) & (VE - 1);
+    const int klast = WIDE ? (K - 1) & ~(VE - 1) : K - VE, nlast = WIDE ? (N - 1) & ~(VE - 1) : N - VE;
+    // A step all of whose k are in range, in a tile that lies inside the
+    // operands or whose edge chunks are read at chosen addresses (see below):
+    // no guards, so the loads issue back to back (guarded loads branch per
+    // load, and the compiler then waits for each load before the next).
+    auto gload_fast = [&](Set &set, int k0) {
 #pragma unroll
-        for (int u = 0; u < AL; ++u)
-            ra[u] = *reinterpret_cast<gptr<chunk>>(A + (int64_t)(row0 + a_row(u)) * a.lda + k0 + a_k(u));
+        for (int u = 0; u < AL; ++u) {
+            const int gr = row0 + a_row(u);
+            set.a[u] = *reinterpret_cast<gptr<chunk>>(A + (int64_t)(EDGE_ADDR ? min(gr, M - 1) : gr) * a.lda + k0 + a_k(u));
+        }
 #pragma unroll
-        for (int u = 0; u < BL; ++u)
-            rb[u] = *reinterpret_cast<gptr<chunk>>(B + (int64_t)(k0 + b_row(u)) * a.ldb + col0 + b_col(u));
+        for (int u = 0; u < BL; ++u) {
+            const int gc = col0 + b_col(u);
+            set.b[u] = *reinterpret_cast<gptr<chunk>>(B + (int64_t)(k0 + b_row(u)) * a.ldb + (EDGE_ADDR ? min(gc, nlast) : gc));
+        }
     };
     // Any K step.  EDGE_ADDR: rows of A past M read row M - 1 and columns of B
     // past N a chunk inside N; rows of B at k >= K read a block of zeros.
@@ -535,23 +547,20 @@ __device__ __forceinline__ void regs_tile(const MmArgs &a, const int row0, const
     // and shifted down by sk (A) or sn (B) elements by fixup, when it goes to
     // LDS, so that the load stays in flight during the products.  Unaligned
     // rows shorter than a chunk (tiny): element loads.
-    const bool tiny = !WIDE && (a.K < VE || N < VE);
-    const int sk = WIDE ? 0 : (VE - (K & (VE - 1))) & (VE - 1), sn = WIDE ? 0 : (VE - (N & (VE - 1))) & (VE - 1);
-    const int klast = WIDE ? (K - 1) & ~(VE - 1) : K - VE, nlast = WIDE ? (N - 1) & ~(VE - 1) : N - VE;
-    auto gload = [&](int k0) {
+    auto gload = [&](Set &set, int k0) {
         if constexpr (!EDGE_ADDR) {
             const bool kfull = (k0 + BK <= K);
 #pragma unroll
             for (int u = 0; u < AL; ++u) {
                 const int gr = row0 + a_row(u), gc = k0 + a_k(u);
                 if (CHUNKS && kfull && gr < M) {
-                    ra[u] = *reinterpret_cast<gptr<chunk>>(A + (int64_t)gr * a.lda + gc);
+                    set.a[u] = *reinterpret_cast<gptr<chunk>>(A + (int64_t)gr * a.lda + gc);
                 } else {
                     elems v;
 #pragma unroll
                     for (int e = 0; e < VE; ++e)
                         v[e] = (gr < M && gc + e < K) ? A[(int64_t)gr * a.lda + gc + e] : elem(0);
-                    ra[u] = __builtin_bit_cast(u32x4, v);
+                    set.a[u] = __builtin_bit_cast(u32x4, v);
                 }
                 if constexpr (LEAN) __builtin_amdgcn_sched_barrier(0);  // (one chunk's addresses at a time)
             }
@@ -559,13 +568,13 @@ __device__ __forceinline__ void regs_tile(const MmArgs &a, const int row0, const
             for (int u = 0; u < BL; ++u) {
                 const int gr = k0 + b_row(u), gc = col0 + b_col(u);
                 if (CHUNKS && gr < K && gc + VE <= N) {
-                    rb[u] = *reinterpret_cast<gptr<chunk>>(B + (int64_t)gr * a.ldb + gc);
+                    set.b[u] = *reinterpret_cast<gptr<chunk>>(B + (int64_t)gr * a.ldb + gc);
                 } else {
                     elems v;
 #pragma unroll
                     for (int e = 0; e < VE; ++e)
                         v[e] = (gr < K && gc + e < N) ? B[(int64_t)gr * a.ldb + gc + e] : elem(0);
-                    rb[u] = __builtin_bit_cast(u32x4, v);
+                    set.b[u] = __builtin_bit_cast(u32x4, v);
                 }
                 if constexpr (LEAN) __builtin_amdgcn_sched_barrier(0);
             }
@@ -574,12 +583,12 @@ __device__ __forceinline__ void regs_tile(const MmArgs &a, const int row0, const
         if (!tiny) {
 #pragma unroll
             for (int u = 0; u < AL; ++u)
-                ra[u] = *reinterpret_cast<gptr<chunk>>(A + (int64_t)min(row0 + a_row(u), M - 1) * a.lda +
+                set.a[u] = *reinterpret_cast<gptr<chunk>>(A + (int64_t)min(row0 + a_row(u), M - 1) * a.lda +
                                                        min(k0 + a_k(u), klast));
 #pragma unroll
             for (int u = 0; u < BL; ++u) {
                 const int k = k0 + b_row(u);
-                rb[u] = *(k < K ? reinterpret_cast<gptr<chunk>>(B + (int64_t)k * a.ldb + min(col0 + b_col(u), nlast))
+                set.b[u] = *(k < K ? reinterpret_cast<gptr<chunk>>(B + (int64_t)k * a.ldb + min(col0 + b_col(u), nlast))
                                 : (gptr<chunk>)(const void *)kZeroBlock);
             }
             return;
@@ -594,7 +603,7 @@ __device__ __forceinline__ void regs_tile(const MmArgs &a, const int row0, const
                 const int k = k0 + a_k(u) + e;
                 v[e] = *(k < K ? row + k : zero);
             }
-            ra[u] = __builtin_bit_cast(u32x4, v);
+            set.a[u] = __builtin_bit_cast(u32x4, v);
         }
 #pragma unroll
         for (int u = 0; u < BL; ++u) {
@@ -603,11 +612,11 @@ __device__ __forceinline__ void regs_tile(const MmArgs &a, const int row0, const
             elems v;
 #pragma unroll
             for (int e = 0; e < VE; ++e) v[e] = *(row ? row + min(col0 + b_col(u) + e, N - 1) : zero);
-            rb[u] = __builtin_bit_cast(u32x4, v);
+            set.b[u] = __builtin_bit_cast(u32x4, v);
         }
     };
     // what the chunks of an edge step at k0 become before they go to LDS
-    auto fixup = [&](int k0) {
+    auto fixup = [&](Set &set, int k0) {
         if constexpr (!EDGE_ADDR) return;
         if (tiny) return;
         if (k0 + BK > K) {
@@ -615,40 +624,40 @@ __device__ __forceinline__ void regs_tile(const MmArgs &a, const int row0, const
             for (int u = 0; u < AL; ++u) {
                 const int k = k0 + a_k(u);
                 if constexpr (!WIDE) {
-                    const u32x4 s = chunk_from<EB>(ra[u], sk);
+                    const u32x4 s = chunk_from<EB>(set.a[u], sk);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) ra[u][e] = k + VE <= K ? ra[u][e] : k < K ? s[e] : 0u;
+                    for (int e = 0; e < 4; ++e) set.a[u][e] = k + VE <= K ? set.a[u][e] : k < K ? s[e] : 0u;
                 } else if constexpr (EB == 4) {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) ra[u][e] = k + e < K ? ra[u][e] : 0u;
+                    for (int e = 0; e < 4; ++e) set.a[u][e] = k + e < K ? set.a[u][e] : 0u;
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)  // word e holds k + 2e (low half) and k + 2e + 1 (high half)
-                        ra[u][e] &= k + 2 * e + 1 < K ? 0xffffffffu : (k + 2 * e < K ? 0x0000ffffu : 0u);
+                        set.a[u][e] &= k + 2 * e + 1 < K ? 0xffffffffu : (k + 2 * e < K ? 0x0000ffffu : 0u);
                 }
             }
         }
         if (!WIDE && sn && col0 + BN > N) {
 #pragma unroll
             for (int u = 0; u < BL; ++u) {
-                const u32x4 s = chunk_from<EB>(rb[u], sn);
+                const u32x4 s = chunk_from<EB>(set.b[u], sn);
                 const bool whole = col0 + b_col(u) + VE <= N;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) rb[u][e] = whole ? rb[u][e] : s[e];
+                for (int e = 0; e < 4; ++e) set.b[u][e] = whole ? set.b[u][e] : s[e];
             }
         }
     };
-    auto sstore = [&](int st) {
+    auto sstore = [&](const Set &set, int st) {
         unsigned char *const la = lds + st * T::BYTES, *const lb = la + T::A_BYTES;
 #pragma unroll
         for (int u = 0; u < AL; ++u) {
             const int r = a_row(u);
-            *reinterpret_cast<u32x4 *>(la + (r * AC + (a_k(u) / VE ^ T::a_swz(r))) * 16) = ra[u];
+            *reinterpret_cast<u32x4 *>(la + (r * AC + (a_k(u) / VE ^ T::a_swz(r))) * 16) = set.a[u];
         }
 #pragma unroll
         for (int u = 0; u < BL; ++u) {
             const int r = b_row(u);
-            *reinterpret_cast<u32x4 *>(lb + (r * BC + (b_col(u) / VE ^ T::b_swz(r))) * 16) = rb[u];
+            *reinterpret_cast<u32x4 *>(lb + (r * BC + (b_col(u) / VE ^ T::b_swz(r))) * 16) = set.b[u];
         }
     };
     auto compute = [&](int st) {
@@ -671,71 +680,112 @@ __device__ __forceinline__ void regs_tile(const MmArgs &a, const int row0, const
             }
         }
     };
-    // Left to itself, the compiler's scheduler sinks the next step's loads to
-    // the end of the step (shortening their registers' lives) and the step
-    // then waits out a whole global-memory latency: a scheduling barrier keeps
-    // them ahead of the products, except in the two-stage programs whose
-    // wavefronts hold less than 64 x 64 (enough wavefronts hide it there).
-    constexpr bool PIN = EB == 2 || STAGES == 1 || T::WTM * T::WTN >= 64 * 64;
     const int KT = kt1 - kt0;
-    const int KF = CHUNKS && interior ? min(K / BK, KT) : 0;  // leading steps that need no guards
-    if (STAGES == 2) {
+    const int KF = (EDGE_ADDR ? !tiny : CHUNKS && interior) ? min(K / BK, KT) : 0;  // leading steps without guards
+    auto load = [&](Set &set, int kt) {
+        if (kt < KF)
+            gload_fast(set, kt * BK);
+        else if (kt < KT)
+            gload(set, kt * BK);
+    };
+    if constexpr (STAGES == 2 && NT >= 1024) {
+        // at the register limit: step kt + 1's loads in flight while step kt
+        // multiplies, no further ahead
+        Set s0;
+        load(s0, 0);
         if (KT > 0) {
-            if (KF > 0) {
-                gload_fast(0);
-            } else {
-                gload(0);
-                fixup(0);
-            }
-            sstore(0);
+            fixup(s0, 0);
+            sstore(s0, 0);
         }
-        __syncthreads();
+        lds_barrier();
         int kt = 0;
-        // steps whose successor is unguarded too: a loop without branches, so
-        // the next step's loads stay in flight while this step multiplies
         for (; kt + 1 < KF; ++kt) {
-            const int cur = kt & 1;
-            gload_fast((kt + 1) * BK);
-            if constexpr (PIN) __builtin_amdgcn_sched_barrier(0);
-            compute(cur);
-            sstore(cur ^ 1);
-            __syncthreads();
+            gload_fast(s0, (kt + 1) * BK);
+            __builtin_amdgcn_sched_barrier(0);
+            compute(kt & 1);
+            sstore(s0, (kt + 1) & 1);
+            lds_barrier();
         }
         for (; kt < KT; ++kt) {
-            const int cur = kt & 1;
-            if (kt + 1 < KT) gload((kt + 1) * BK);
-            if constexpr (PIN) __builtin_amdgcn_sched_barrier(0);
-            if (!idle) compute(cur);
+            load(s0, kt + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            compute(kt & 1);
             if (kt + 1 < KT) {
-                fixup((kt + 1) * BK);
-                sstore(cur ^ 1);
+                fixup(s0, (kt + 1) * BK);
+                sstore(s0, (kt + 1) & 1);
             }
-            __syncthreads();
+            lds_barrier();
         }
+    } else if constexpr (STAGES == 2) {
+        // Step k's chunks are in set k mod SETS.  A step multiplies out of one
+        // buffer, then stores the next step's chunks to the other and sends
+        // out the loads of the step SETS further into their registers: with
+        // one set a step's products do not cover the memory latency (packed
+        // rows: float32 1531 x 777 x 1201 43.1 us with one set, 41.2 with two;
+        // bfloat16 1021 x 3001 x 2047 39.6 with one, 36.9 with four).
+        constexpr int U = SETS > 2 ? SETS : 2;  // steps of a round: static sets and buffers
+        Set s0, s1, s2, s3;
+        auto step = [&](Set &set, int kt, int cur, auto full_) {
+            constexpr bool full = decltype(full_)::value;
+            if (full || !idle) compute(cur);
+            if (full || kt + 1 < KT) {
+                fixup(set, (kt + 1) * BK);
+                sstore(set, cur ^ 1);
+                if constexpr (full)
+                    gload_fast(set, (kt + 1 + SETS) * BK);
+                else
+                    load(set, kt + 1 + SETS);
+            }
+            lds_barrier();
+        };
+        auto round = [&](int kt, auto full_) {
+            constexpr bool full = decltype(full_)::value;
+            step(SETS > 1 ? s1 : s0, kt, 0, full_);
+            if (full || kt + 1 < KT) step(SETS > 2 ? s2 : s0, kt + 1, 1, full_);
+            if constexpr (U == 4) {
+                if (full || kt + 2 < KT) step(s3, kt + 2, 0, full_);
+                if (full || kt + 3 < KT) step(s0, kt + 3, 1, full_);
+            }
+        };
+        if (KT > 0) {
+            load(s0, 0);
+            if constexpr (SETS > 1) load(s1, 1);
+            if constexpr (SETS > 2) {
+                load(s2, 2);
+                load(s3, 3);
+            }
+            fixup(s0, 0);
+            sstore(s0, 0);
+            load(s0, SETS);
+        }
+        lds_barrier();
+        int kt = 0;
+        for (; kt + U + SETS < KF; kt += U) round(kt, std::true_type{});
+        for (; kt < KT; kt += U) round(kt, std::false_type{});
     } else {
         // one LDS buffer: step kt + 1's loads are in flight (in registers)
-        // while step kt multiplies out of LDS
-        if (KT > 0) {
-            if (KF > 0)
-                gload_fast(0);
-            else
-                gload(0);
-        }
+        // while step kt multiplies out of LDS.  Left to itself, the compiler's
+        // scheduler sinks them to the end of the step (shortening their
+        // registers' lives) and the step then waits out a whole memory
+        // latency: a scheduling barrier keeps them ahead of the products.
+        Set s0;
+        load(s0, 0);
         int kt = 0;
         for (; kt + 1 < KF; ++kt) {
+            if constexpr (!WIDE) fixup(s0, kt * BK);
             __syncthreads();  // the previous step's LDS reads are done
-            sstore(0);
+            sstore(s0, 0);
             __syncthreads();
-            gload_fast((kt + 1) * BK);
+            gload_fast(s0, (kt + 1) * BK);
             __builtin_amdgcn_sched_barrier(0);
             compute(0);
         }
         for (; kt < KT; ++kt) {
-            if (kt >= KF) fixup(kt * BK);
+            fixup(s0, kt * BK);
             __syncthreads();
-            sstore(0);
+            sstore(s0, 0);
             __syncthreads();
-            if (kt + 1 < KT) gload((kt + 1) * BK);
+            load(s0, kt + 1);
             __builtin_amdgcn_sched_barrier(0);
             if (!idle) compute(0);
         }

@@ -102,3 +102,20 @@ def test_choice_of_one_size_on_both_alignments(table, dtype):
         pk.pk_matmul(table, None, dtype, views[0], views[1], C)
         torch.cuda.synchronize()
         assert np.array_equal(C.cpu().numpy().astype(np.float64), ref), lead
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("steps", range(1, 14))
+def test_steps_around_the_pipeline(table, dtype, steps):
+    """One to thirteen K steps, whole and ragged, in edge tiles: loads run up
+    to four steps ahead through registers."""
+    for bk in sorted({p[2] for p in POINTS[dtype]}):
+        for K in (steps * bk, steps * bk - 3, steps * bk + 1):
+            M, N = 67, 131
+            (ah, a), (bh, b) = operand((M, K), dtype, steps), operand((K, N), dtype, 40 + steps)
+            ref = om.matmul(ah, bh, dtype)
+            for (bm, bn, pbk, wm, wn) in POINTS[dtype]:
+                for stage in (0, pk.PK_MFMA_SINGLE):
+                    for ks in (0, 2) if steps in (9, 13) else (0,):
+                        p = pk.params(family=pk.PK_FAMILY_MFMA, variant=stage, bm=bm, bn=bn, bk=pbk, wm=wm, wn=wn, ks=ks)
+                        check(table, dtype, p, a, b, ref, (M, N, K, bm, bn, pbk, stage, ks))
