@@ -17,7 +17,7 @@ cycles -- checked against kernel-trace durations at the 2.4 GHz clock):
                    SIMDs): the fraction of the matrix units' cycles spent on
                    MFMAs, at the clock the kernel ran at
   cycles_per_mfma  SQ_VALU_MFMA_BUSY_CYCLES / SQ_INSTS_MFMA (64 for
-                   v_mfma_f32_32x32x2_f32, 32 for v_mfma_f32_32x32x16_bf16)
+                   v_mfma_f32_32x32x2_f32, 16 for v_mfma_f32_16x16x32_bf16)
   lds_active       SQ_LDS_IDX_ACTIVE / (GRBM_GUI_ACTIVE / 8 x 256 CUs): the
                    fraction of cycles a CU's LDS spent on indexed accesses
   lds_conflict_per_active  SQ_LDS_BANK_CONFLICT / SQ_LDS_IDX_ACTIVE (cycles

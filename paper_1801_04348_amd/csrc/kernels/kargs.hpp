@@ -15,7 +15,7 @@ struct MmArgs {
     int64_t lda, ldb, ldc;
     int32_t M, N, K;
     int32_t accumulate;
-    int32_t vec;     // MFMA programs: rows aligned for 16-byte loads (else element loads)
+    int32_t vec;     // MFMA programs: rows aligned for the wide loads (else the twin runs)
     int32_t splits;  // MFMA programs: shares of K (> 1: each adds its sum to C atomically), else 0
     int32_t depth;   // MFMA programs that load straight to LDS: buffers of K steps (2 .. max_depth)
 };

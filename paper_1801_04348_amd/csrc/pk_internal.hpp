@@ -163,7 +163,7 @@ bool variant_fits(const Family &fam, uint32_t variant, const std::vector<int64_t
                   const std::vector<int64_t> &machine_vals);
 const KernelEntry *find_instance(int family, int variant, int dtype, const std::vector<int64_t> &pt);
 // The element-load twin of a single-launch MFMA instance (same program,
-// rows read element by element), or null.
+// rows read at element alignment), or null.
 const KernelEntry *element_twin(const KernelEntry &e);
 // The split-along-K form of a single-launch MFMA instance's wide program, or
 // null (programs that are never split).

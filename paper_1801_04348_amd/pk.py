@@ -275,7 +275,7 @@ def pk_select(tbl: Table, dtype, M: int, N: int, K: int, policy: int = PK_POLICY
 
 def pk_select_operands(tbl: Table, dtype, A, B, policy: int = PK_POLICY_CASE, allow_fallback: bool = False):
     """pk_select for these device operands (A: (M, K), B: (K, N)): MFMA
-    candidates as they would run on them (element loads on unaligned rows)."""
+    candidates as they would run on them (their twins on unaligned rows)."""
     M, K = A.shape
     K2, N = B.shape
     if K2 != K:
