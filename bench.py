@@ -17,7 +17,7 @@ Prints one JSON line (rank 0, the only rank):
              TFLOP/s float32 matrix-core peak
   cpu_baseline  the CPU oracle on a bounded sample of the same sweep
   exhaustive    when a tuning store for this device exists, the per-shape best
-             branch timed in the same run (untimed for `value`; in-sample)
+             branch timed in the same run (untimed for `value`)
   heldout    the cost model on 40 held-out shapes, every candidate timed live
   grouped    4096 uneven products in one persistent launch (a tile program
              per product), CASE and EXHAUSTIVE plans (graph replay), against
@@ -499,8 +499,8 @@ def main():
                 ratios["learned"].append(tb / tl)
         geo = lambda r: round(math.exp(sum(map(math.log, r)) / len(r)), 4)
         exhaustive = {"shapes": len(ratios["case"]),
-                      "sample": "in-sample: the sweep shapes' candidates are in the float32 model's training "
-                                "data; best = the fastest of the tuner's stored pick, CASE and LEARNED, timed "
+                      "sample": "the float32 model was trained on random shapes of the same range, not on these "
+                                "shapes; best = the fastest of the tuner's stored pick, CASE and LEARNED, timed "
                                 "interleaved in this run",
                       "best_gflops": round(fl / tot["best"] / 1e6, 1),
                       "case_gflops": round(fl / tot["case"] / 1e6, 1),
