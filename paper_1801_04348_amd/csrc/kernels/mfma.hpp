@@ -297,12 +297,23 @@ template <int EB, int BM, int BN, int BK, int WM, int WN> struct Tile {
 // ------------------------------------------------------------------ loads straight to LDS
 // 16 bytes a lane from `base` + voff to LDS, lane l's at `lds` + 16 l (`lds`
 // uniform).  In asm because the compiler, which cannot tell the buffers apart,
-// would wait for every such load before any LDS read; it has no output
-// register, and the waits are dma_tile's own (below).
+// would wait for every such load before any LDS read; its one output is a
+// scalar copy, and the waits are dma_tile's own (below).  A scalar pair that a
+// vector instruction wrote must rest five states before a load may read it as
+// its base, which the compiler sees to for its own loads but not in here: the
+// load reads a copy by the scalar unit, which also is the state between the
+// writing of m0 and its use.  (m0 is no register that the compiler allocates,
+// hence its warning; the clobber tells it that a value of its own there is gone.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void load_lds16(uint32_t voff, const unsigned char *base, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "s"(lds)
-                 : "memory");
+    uint64_t at;
+    asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %2\n\tglobal_load_lds_dwordx4 %1, %0"
+                 : "=&s"(at)
+                 : "v"(voff), "s"(base), "s"(lds)
+                 : "memory", "m0");
 }
+#pragma clang diagnostic pop
 // waits until at most N of the wavefront's memory operations are outstanding
 // (they complete in order)
 template <int N> __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
