@@ -314,6 +314,16 @@ __device__ __forceinline__ void load_lds16(uint32_t voff, const unsigned char *b
                  : "memory", "m0");
 }
 #pragma clang diagnostic pop
+// The LDS from `p` on, as memory of an extent the compiler does not know: an
+// address past the end of the object at `p`, in the LDS that a launch adds
+// behind it, is then as defined as one inside.  (Taken from the object itself,
+// such addresses are out of bounds, and the compiler may drop or reorder what
+// reads there.)  The kernel has no other LDS object, so the added part follows.
+__device__ __forceinline__ unsigned char *lds_pool(unsigned char *p) {
+    uint32_t at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)p;
+    asm("" : "+s"(at));
+    return (unsigned char *)(__attribute__((address_space(3))) unsigned char *)(uintptr_t)at;
+}
 // waits until at most N of the wavefront's memory operations are outstanding
 // (they complete in order)
 template <int N> __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
@@ -323,8 +333,8 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // One BM x BN output tile at (row0, col0) over the K steps [kt0, kt1) of BK
 // each, rows 16-byte aligned and leading dimensions at most kMaxDmaRowBytes (so
 // that a tile's offsets fit 32 bits).  SBK: K extent of a buffer; a.depth of
-// them at `lds`, two to MAX_DEPTH, the last ones perhaps in LDS that the launch
-// adds (dma_depth in the host library).  The caller synchronises the workgroup
+// them from `object` on, two to MAX_DEPTH, the last ones perhaps in LDS that the
+// launch adds (dma_depth in the host library).  The caller synchronises the workgroup
 // before the call and before using the LDS otherwise.
 //
 // A step's last phase opens the next step: its loads have arrived in this
@@ -335,8 +345,9 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // from HBM (all workgroups of an XCD meet a panel's first touch together);
 // bfloat16 of order 4096 on 128 x 256 x 32, 146 us with two and 124 with three.
 template <int EB, int BM, int BN, int BK, int SBK, int WM, int WN, int MAX_DEPTH>
-__device__ __forceinline__ void dma_tile(const MmArgs &a, const int row0, const int col0, unsigned char *const lds,
+__device__ __forceinline__ void dma_tile(const MmArgs &a, const int row0, const int col0, unsigned char *const object,
                                          const int kt0, const int kt1) {
+    unsigned char *const lds = MAX_DEPTH > 2 ? lds_pool(object) : object;
     using T = Tile<EB, BM, BN, SBK, WM, WN>;
     constexpr int NT = T::NT, VE = T::VE, P = T::P;
     constexpr int LOADS = T::AL + T::BL;  // per work-item and step

@@ -47,3 +47,14 @@ def test_direct_loads_say_that_they_write_m0(tmp_path):
     asm = re.findall(r'asm sideeffect "[^"]*global_load_lds_dwordx4[^"]*", "([^"]*)"',
                      device_code(tmp_path, "-emit-llvm"))
     assert asm and all("~{m0}" in c for c in asm)
+
+
+def test_no_address_past_the_end_of_an_lds_object(tmp_path):
+    """The third and fourth buffers of K steps lie in LDS that the launch adds
+    behind the kernel's own array: not addressed from that array, of which
+    they are out of bounds."""
+    ir = device_code(tmp_path, "-emit-llvm")
+    size = {n: int(b) for n, b in re.findall(r"^(@\S+) = .*addrspace\(3\) global \[(\d+) x i8\]", ir, re.M)}
+    assert len(size) == 2
+    reached = [(n, int(off)) for n, off in re.findall(r"addrspace\(3\) (@\w+), i32 (\d+)", ir) if n in size]
+    assert reached and all(off < size[n] for n, off in reached), max(off for _, off in reached)
