@@ -169,15 +169,16 @@ bool wide_rows(int dtype, const void *A, int64_t lda, const void *B, int64_t ldb
 // program, its counters and its residency stay what the case table says.
 int dma_depth(const pk_machine &m, const KernelEntry &e, int64_t resident, int64_t ksteps, int *extra) {
     *extra = 0;
-    if (e.family != PK_FAMILY_MFMA || e.dtype == PK_I32 || (e.variant & PK_MFMA_ELEMENT) || e.threads >= 1024) return 2;
-    const int es = e.dtype == PK_BF16 ? 2 : 4;
-    const int sbk = (e.variant & PK_MFMA_SINGLE) ? e.bk / 2 : e.bk;
-    const int64_t bytes = (int64_t)(e.tile_m + e.tile_n) * sbk * es;
-    if (2 * bytes > e.lds_bytes) return 2;  // (the single-stage programs that load through registers)
+    const bool f32 = e.dtype == PK_F32, single = e.variant & PK_MFMA_SINGLE;
+    if (e.family != PK_FAMILY_MFMA || e.dtype == PK_I32 || (e.variant & PK_MFMA_ELEMENT) ||
+        !pkk::loads_directly(f32, e.bk, single, e.wm, e.wn))
+        return 2;
+    const int64_t bytes = (int64_t)(e.tile_m + e.tile_n) * pkk::buffer_k(e.bk, single) * (f32 ? 4 : 2);
     // LDS is allocated in units of up to 1280 bytes
     const int64_t room = std::min<int64_t>(m.lds_cu / std::max<int64_t>(resident, 1), m.lds_block) / 1280 * 1280;
-    const int64_t steps = std::max<int64_t>(2, (e.variant & PK_MFMA_SINGLE) ? 2 * ksteps : ksteps);
-    const int64_t depth = std::min<int64_t>({pkk::max_depth(es == 4, e.bm, e.bn, e.wm, e.wn), steps, std::max(room, (int64_t)e.lds_bytes) / bytes});
+    const int64_t steps = std::max<int64_t>(2, single ? 2 * ksteps : ksteps);
+    const int64_t depth = std::min<int64_t>({pkk::max_depth(f32, e.bm, e.bn, e.wm, e.wn), steps,
+                                             std::max(room, (int64_t)e.lds_bytes) / bytes});
     *extra = (int)std::max<int64_t>(0, depth * bytes - e.lds_bytes);
     return (int)depth;
 }

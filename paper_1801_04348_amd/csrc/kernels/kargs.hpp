@@ -20,6 +20,16 @@ struct MmArgs {
     int32_t depth;   // MFMA programs that load straight to LDS: buffers of K steps (2 .. max_depth)
 };
 
+// K extent of a wide MFMA kernel's buffer (a single-stage program's one stage
+// is cut into two), and whether the kernel copies rows straight to it: not the
+// programs of 1024 work-items, whose 128 registers a lane have no room for the
+// second operand set, nor those whose buffer is shorter than one group of
+// products.
+constexpr int buffer_k(int bk, bool single) { return single ? bk / 2 : bk; }
+constexpr bool loads_directly(bool f32, int bk, bool single, int wm, int wn) {
+    return wm * wn < 16 && buffer_k(bk, single) % (f32 ? 8 : 32) == 0;
+}
+
 // Most buffers of K steps a wide MFMA kernel cycles through (grouped kernels:
 // two).  float32 steps multiply for thousands of cycles, more than memory
 // latency: two.  bfloat16: the wavefronts of the largest tiles have registers

@@ -818,10 +818,8 @@ __device__ __forceinline__ void regs_tile(const MmArgs &a, const int row0, const
 // The tile by the way that its program and its rows' alignment take.
 template <int EB, int BM, int BN, int BK, int WM, int WN, int STAGES, bool WIDE, int MAX_DEPTH>
 __device__ __forceinline__ void mfma_tile(const MmArgs &a, int row0, int col0, unsigned char *lds, int kt0, int kt1) {
-    constexpr int SBK = STAGES == 2 ? BK : BK / 2;
-    // (programs of 1024 work-items, 128 registers a lane, have no room for
-    // the second operand set)
-    constexpr bool DMA = WIDE && WM * WN < 16 && SBK % (EB == 4 ? 8 : 32) == 0;
+    constexpr int SBK = buffer_k(BK, STAGES == 1);
+    constexpr bool DMA = WIDE && loads_directly(EB == 4, BK, STAGES == 1, WM, WN);
     // the largest tiles' guarded loads: see regs_tile
     constexpr bool EDGE = WM * WN < 16 && (EB == 2 || STAGES == 2 || BM * BN * BK <= 128 * 256 * 16);
     if constexpr (DMA)
