@@ -174,8 +174,11 @@ int dma_depth(const pk_machine &m, const KernelEntry &e, int64_t resident, int64
         !pkk::loads_directly(f32, e.bk, single, e.wm, e.wn))
         return 2;
     const int64_t bytes = (int64_t)(e.tile_m + e.tile_n) * pkk::buffer_k(e.bk, single) * (f32 ? 4 : 2);
-    // LDS is allocated in units of up to 1280 bytes
-    const int64_t room = std::min<int64_t>(m.lds_cu / std::max<int64_t>(resident, 1), m.lds_block) / 1280 * 1280;
+    // LDS is allocated in units of up to 1280 bytes; never more than gfx950
+    // has, whatever machine the table is bound to: the programs fit without
+    constexpr int64_t kLds = 160 * 1024;
+    const int64_t room =
+        std::min<int64_t>({m.lds_cu / std::max<int64_t>(resident, 1), m.lds_block, kLds}) / 1280 * 1280;
     const int64_t steps = std::max<int64_t>(2, single ? 2 * ksteps : ksteps);
     const int64_t depth = std::min<int64_t>({pkk::max_depth(f32, e.bm, e.bn, e.wm, e.wn), steps,
                                              std::max(room, (int64_t)e.lds_bytes) / bytes});

@@ -59,3 +59,11 @@ def test_no_lds_is_added_to_programs_that_load_through_registers(tmp_path):
     direct = [r for r in rows if r not in registers]
     assert len(registers) >= 6 and any(int(r[1]) == 4 for r in direct)
     assert all(r[1:3] == ["2", "0"] for r in registers), registers
+
+
+def test_added_lds_fits_the_hardware_whatever_the_descriptor_says(tmp_path):
+    """A table may be bound to the descriptor of a machine with more LDS than
+    gfx950's 160 KiB a workgroup: every program's launch stays within those."""
+    rows = run(tmp_path, DEPTHS, machines.variant(lds_block=1 << 20, lds_cu=1 << 20))
+    assert any(int(r[2]) > 0 for r in rows)
+    assert all(int(r[2]) + int(r[3]) <= 160 * 1024 for r in rows), [r for r in rows if int(r[2]) + int(r[3]) > 160 * 1024]
