@@ -279,11 +279,15 @@ int pk_measure(const pk_table *tbl, pk_dtype dtype, const void *A, int64_t lda, 
  * when accumulating).  MFMA programs load 16 bytes at a time along rows that
  * are aligned for it (A and B 16-byte aligned; lda and ldb multiples of 4
  * for f32, of 8 for bf16), and at element alignment or element by element
- * otherwise -- the same arithmetic in the same order, so the result does not depend on the
- * alignment.  One program
- * has no element-load form (the bfloat16 256 x 256 x 64 tile, whose
- * element-load kernel would spill); given it with operands whose rows are not
- * aligned, the call runs the CASE choice for those operands instead.
+ * otherwise -- the same arithmetic in the same order, so the result does not
+ * depend on the alignment.  The f32 and bf16 programs of fewer than 1024
+ * work-items (but the single-stage bf16 ones of K tile 32) also take aligned
+ * rows that way where those a workgroup reads at a time, up to bm rows of A
+ * or up to bk of B (bk / 2 for single-stage programs), span 4 GiB - 4 KiB or
+ * more: row strides of 16 MiB and up.  Some bfloat16 programs have no
+ * element-load form, which would spill (256 x 256 x 64, and 128 x 256 x 64
+ * and 256 x 128 x 64 of four wavefronts); given one with operands whose rows
+ * need it, the call runs the CASE choice for those operands instead.
  * Errors: PK_ERR_INVALID_ARG, PK_ERR_NO_FEASIBLE_BRANCH,
  * PK_ERR_UNSUPPORTED_DTYPE, PK_ERR_NOT_INSTANTIATED, PK_ERR_HIP. */
 int pk_matmul(const pk_table *tbl, const pk_params *params_or_null, pk_dtype dtype,

@@ -152,13 +152,31 @@ static bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 
 // Rows aligned for the MFMA programs' wide loads: 16-byte loads along the
 // rows of A and B (leading dimensions multiples of 4 f32 / 8 bf16 elements,
-// 16-byte aligned bases), short enough for a tile's offsets to fit the loads'
-// 32 bits.  Otherwise the programs read at element alignment (same arithmetic,
-// same summation order).
-bool wide_rows(int dtype, const void *A, int64_t lda, const void *B, int64_t ldb) {
+// 16-byte aligned bases).
+bool aligned_rows(int dtype, const void *A, int64_t lda, const void *B, int64_t ldb) {
     const int64_t vec = dtype == PK_BF16 ? 8 : 4;
-    if (dtype != PK_I32 && std::max(lda, ldb) * (16 / vec) > pkk::kMaxDmaRowBytes) return false;
     return aligned16(A) && lda % vec == 0 && aligned16(B) && ldb % vec == 0;
+}
+
+// The rows of a tile that loads straight to LDS, `rows_a` of A and `rows_b` of
+// B in a buffer, lie within what its offsets reach.
+bool direct_reach(int dtype, int64_t rows_a, int64_t lda, int64_t rows_b, int64_t ldb) {
+    const int64_t es = dtype == PK_BF16 ? 2 : 4;
+    auto within = [&](int64_t rows, int64_t ld) { return rows <= 1 || ld <= pkk::kMaxDmaReach / es / (rows - 1); };
+    return within(rows_a, lda) && within(rows_b, ldb);
+}
+
+// A product's program runs in its wide form on these operands: rows aligned,
+// and near enough to each other for the programs that load straight to LDS.
+// Otherwise the program's twin reads at element alignment (same arithmetic,
+// same summation order).
+bool wide_rows(const KernelEntry &e, int64_t M, int64_t K, const void *A, int64_t lda, const void *B, int64_t ldb) {
+    if (!aligned_rows(e.dtype, A, lda, B, ldb)) return false;
+    const bool single = e.variant & PK_MFMA_SINGLE;
+    if (e.family != PK_FAMILY_MFMA || e.dtype == PK_I32 ||
+        !pkk::loads_directly(e.dtype == PK_F32, e.bk, single, e.wm, e.wn))
+        return true;
+    return direct_reach(e.dtype, std::min<int64_t>(M, e.tile_m), lda, std::min<int64_t>(K, pkk::buffer_k(e.bk, single)), ldb);
 }
 
 // Buffers of K steps a wide MFMA kernel cycles through, and the LDS the
@@ -190,7 +208,7 @@ int launch(const pk_machine &m, const KernelEntry &e0, const MmArgs &args, hipSt
     const KernelEntry *pe = &e0;
     MmArgs a = args;
     if (e0.family != PK_FAMILY_MFMA || a.K <= 0 || a.splits < 2) a.splits = 0;
-    if (e0.family == PK_FAMILY_MFMA && !args.vec) {  // rows not aligned: the element-load twin (it splits in place)
+    if (e0.family == PK_FAMILY_MFMA && !args.vec) {  // not wide_rows: the element-load twin (it splits in place)
         pe = element_twin(e0);
         if (!pe) return fail(PK_ERR_NOT_INSTANTIATED, std::string("no element-load twin of ") + e0.name);
     } else if (a.splits > 1) {  // shares of K: the wide program's split form
@@ -542,15 +560,18 @@ int pk_matmul(const pk_table *tbl, const pk_params *params_or_null, pk_dtype dty
         pk_params sel;
         if (!params_or_null) {
             // the CASE choice for these operands (it depends on their sizes
-            // and on whether their rows are aligned): cached like pk_select's
-            const bool wide = K > 0 && wide_rows((int)dtype, A, lda, B, ldb);
+            // and on which programs run in their wide form): cached like
+            // pk_select's where that is all or none of them
+            const bool wide = K > 0 && aligned_rows((int)dtype, A, lda, B, ldb);
+            const bool kept = !wide || direct_reach((int)dtype, std::min<int64_t>(M, pkk::kLargestTile), lda,
+                                                    std::min<int64_t>(K, pkk::kLargestBuffer), ldb);
             const auto key = std::make_tuple(wide ? (int)dtype + kCaseWide : (int)dtype + kCaseNarrow, M, N, K,
                                              (int)PK_POLICY_CASE);
-            if (!tbl->cached(key, &sel)) {
+            if (!kept || !tbl->cached(key, &sel)) {
                 int rc = select_params(tbl, (int)dtype, M, N, K, PK_POLICY_CASE, false, &sel, A, lda, B, ldb);
                 if (rc != PK_OK) return rc;
                 std::lock_guard<std::mutex> g(tbl->cache_mu);
-                if (tbl->cache.size() < kMaxCachedCase) tbl->cache[key] = sel;
+                if (kept && tbl->cache.size() < kMaxCachedCase) tbl->cache[key] = sel;
             }
             params_or_null = &sel;
         }
@@ -561,16 +582,17 @@ int pk_matmul(const pk_table *tbl, const pk_params *params_or_null, pk_dtype dty
         const KernelEntry *e = nullptr;
         int rc = resolve(tbl, params_or_null, (int)dtype, &q, &e);
         if (rc != PK_OK) return rc;
-        const bool wide = wide_rows((int)dtype, A, lda, B, ldb);
+        bool wide = wide_rows(*e, M, K, A, lda, B, ldb);
         if (e->family == PK_FAMILY_MFMA && !wide && !element_twin(*e)) {
             // a program with no element-load form (it would spill) on rows
-            // not aligned for its wide loads: the CASE choice for these
+            // that its wide loads cannot read: the CASE choice for these
             // operands runs instead (pk_select, which sees no operands, may
             // return such a program)
             rc = select_params(tbl, (int)dtype, M, N, K, PK_POLICY_CASE, false, &sel, A, lda, B, ldb);
             if (rc != PK_OK) return rc;
             rc = resolve(tbl, &sel, (int)dtype, &q, &e);
             if (rc != PK_OK) return rc;
+            wide = wide_rows(*e, M, K, A, lda, B, ldb);
         }
         MmArgs args{A, B, C, lda, ldb, ldc, (int32_t)M, (int32_t)N, (int32_t)K, accumulate ? 1 : 0, wide ? 1 : 0,
                     q.ks, 0};

@@ -108,8 +108,12 @@ KernelEntry as_program(const KernelEntry &e, int prog) {
     return x;
 }
 
-bool aligned_rows(int dtype, const void *A, int64_t lda, const void *B, int64_t ldb) {
-    return wide_rows(dtype, A, lda, B, ldb);
+// A product runs in the wide grouped kernels: its rows are aligned, and those
+// of the largest tile and K step (128 rows of A, 64 of B) within direct loads'
+// reach -- one rule for all of them.
+bool grouped_wide(int dtype, const GroupedOperands &o, int g) {
+    return o.K[g] > 0 && aligned_rows(dtype, o.A[g], o.lda[g], o.B[g], o.ldb[g]) &&
+           direct_reach(dtype, std::min<int64_t>(o.M[g], 128), o.lda[g], std::min<int64_t>(o.K[g], 64), o.ldb[g]);
 }
 
 // One product's place in a layout.
@@ -166,10 +170,10 @@ double lone_tile_seconds(const pk_machine &m, const KernelEntry &e, int dtype, i
     return tile_work_seconds(m, e, dtype, e.tile_m, e.tile_n, K, 1) + kTileOpenClose;
 }
 
-// The grouped kernel form a product runs in: the wide kernel when its rows
-// are aligned for 16-byte loads, else the element-load twin (PK_MFMA_ELEMENT).
+// The grouped kernel form a product runs in: the wide kernel, or its
+// element-load twin (PK_MFMA_ELEMENT).
 int form_of(int dtype, const GroupedOperands &o, int g) {
-    return o.K[g] > 0 && aligned_rows(dtype, o.A[g], o.lda[g], o.B[g], o.ldb[g]) ? 0 : (int)PK_MFMA_ELEMENT;
+    return grouped_wide(dtype, o, g) ? 0 : (int)PK_MFMA_ELEMENT;
 }
 
 int check_operands(const GroupedOperands &o) {
@@ -420,7 +424,7 @@ int build_from(const pk_table *tbl, int dtype, const GroupedOperands &o, const s
             d.M = (int32_t)o.M[g];
             d.N = (int32_t)o.N[g];
             d.K = (int32_t)o.K[g];
-            d.vec = o.K[g] > 0 && aligned_rows(dtype, o.A[g], o.lda[g], o.B[g], o.ldb[g]) ? 1 : 0;
+            d.vec = grouped_wide(dtype, o, g) ? 1 : 0;
             d.tile_start = t;
             d.tiles_n = (int32_t)((o.N[g] + a.tile_n - 1) / a.tile_n);
             d.prog = a.prog;

@@ -41,9 +41,11 @@ constexpr int max_depth(bool f32, int bm, int bn, int wm, int wn) {
 // Largest workgroup of an MFMA program that runs a product split along K.
 constexpr int kSplittableThreads = 512;
 
-// Longest row (leading dimension in bytes) the wide MFMA kernels read: the
-// offsets of a tile's up to 256 rows stay below 2^31.
-constexpr int64_t kMaxDmaRowBytes = (int64_t(1) << 23) - 1024;
+// Bytes from a tile's first row to its last that the kernels that load straight
+// to LDS reach: a chunk's offset is 32-bit, its row's distance and its place in
+// the row (below 4 KiB) together.
+constexpr int64_t kMaxDmaReach = (int64_t(1) << 32) - 4096;
+constexpr int kLargestTile = 256, kLargestBuffer = 64;  // rows of A and of B in one buffer, at most
 
 // One product of a grouped launch.
 struct GroupDesc {

@@ -331,8 +331,8 @@ template <int N> __device__ __forceinline__ void wait_loads() { asm volatile("s_
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // One BM x BN output tile at (row0, col0) over the K steps [kt0, kt1) of BK
-// each, rows 16-byte aligned and leading dimensions at most kMaxDmaRowBytes (so
-// that a tile's offsets fit 32 bits).  SBK: K extent of a buffer; a.depth of
+// each, rows 16-byte aligned and a buffer's rows within kMaxDmaReach of its
+// first (so that chunks' offsets fit 32 bits).  SBK: K extent of a buffer; a.depth of
 // them from `object` on, two to MAX_DEPTH, the last ones perhaps in LDS that the
 // launch adds (dma_depth in the host library).  The caller synchronises the workgroup
 // before the call and before using the LDS otherwise.
@@ -352,6 +352,7 @@ __device__ __forceinline__ void dma_tile(const MmArgs &a, const int row0, const 
     constexpr int NT = T::NT, VE = T::VE, P = T::P;
     constexpr int LOADS = T::AL + T::BL;  // per work-item and step
     static_assert((MAX_DEPTH - 1) * LOADS < 64, "steps under way fit the wait's counter");
+    static_assert(BM <= kLargestTile && SBK <= kLargestBuffer, "the host's rule for every program at once");
     T t;
     const int tid = threadIdx.x;
     const int K = min(kt1 * BK, a.K) - kt0 * BK;        // of this tile's share
@@ -363,13 +364,13 @@ __device__ __forceinline__ void dma_tile(const MmArgs &a, const int row0, const 
 #pragma unroll
     for (int u = 0; u < T::AL; ++u) {
         const int f = (tid + u * NT) % (BM * T::AC), r = f / T::AC, c = (f % T::AC) ^ T::a_swz(r);
-        va[u] = (uint32_t)(min(r, a.M - 1 - row0) * (int)a.lda + c * VE) * EB;
+        va[u] = ((uint32_t)min(r, a.M - 1 - row0) * (uint32_t)a.lda + c * VE) * EB;
     }
     const int clast = ((a.N - 1) & ~(VE - 1)) - col0;
 #pragma unroll
     for (int u = 0; u < T::BL; ++u) {
         const int f = (tid + u * NT) % (SBK * T::BC), r = f / T::BC, c = (f % T::BC) ^ T::b_swz(r);
-        vb[u] = (uint32_t)(r * (int)a.ldb + min(c * VE, clast)) * EB;
+        vb[u] = ((uint32_t)r * (uint32_t)a.ldb + min(c * VE, clast)) * EB;
     }
     // this wavefront's part of the tiles' slots
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -388,7 +389,8 @@ __device__ __forceinline__ void dma_tile(const MmArgs &a, const int row0, const 
         bb += bstep;
     };
     // the same for a last step of `rest` < SBK k: chunks and rows past them
-    // read the last one in range
+    // read the last one in range (its offset fits where theirs may not have:
+    // all of this is modulo 2^32)
     const int rest = K - KF * SBK;
     auto load_rest = [&](int at) {
         const int kl = (rest - 1) & ~(VE - 1);
@@ -400,7 +402,7 @@ __device__ __forceinline__ void dma_tile(const MmArgs &a, const int row0, const 
 #pragma unroll
         for (int u = 0; u < T::BL; ++u) {
             const int r = (tid + u * NT) % (SBK * T::BC) / T::BC;
-            load_lds16(vb[u] - (uint32_t)(max(r - (rest - 1), 0) * (int)a.ldb) * EB, bb, b_slot(at, u));
+            load_lds16(vb[u] - (uint32_t)max(r - (rest - 1), 0) * (uint32_t)a.ldb * EB, bb, b_slot(at, u));
         }
     };
     auto load_step = [&](int kt, int at) {

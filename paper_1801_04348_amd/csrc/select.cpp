@@ -261,12 +261,13 @@ std::vector<Candidate> feasible(const pk_table *tbl, int dtype, int64_t M, int64
     for (int family : {PK_FAMILY_VALU, PK_FAMILY_VALU2, PK_FAMILY_MFMA}) {  // the product families
         const pk_table::Part *part = tbl->part(family, dtype);
         if (!part || !part->supported) continue;
-        // MFMA programs read unaligned rows at element alignment: feasible, slower
-        const bool wide = !A || family != PK_FAMILY_MFMA || wide_rows(dtype, A, lda, B, ldb);
         const int64_t ncu = std::max<int32_t>(tbl->machine.cu_count, 1);
         for (size_t i = 0; i < part->programs.size(); ++i) {
             const auto &p = part->programs[i];
-            if (!p.entry || (!wide && !p.twin)) continue;
+            if (!p.entry) continue;
+            // MFMA programs read unaligned rows at element alignment: feasible, slower
+            const bool wide = !A || family != PK_FAMILY_MFMA || wide_rows(*p.entry, M, K, A, lda, B, ldb);
+            if (!wide && !p.twin) continue;
             Candidate c;
             c.family = family;
             c.point = (int)i;
@@ -342,7 +343,6 @@ int time_candidates(const pk_table *tbl, int dtype, int64_t M, int64_t N, int64_
         args.B = sB;
         args.C = sC;
     }
-    args.vec = wide_rows(dtype, args.A, args.lda, args.B, args.ldb) ? 1 : 0;
     if ((err = hipStreamCreate(&s)) != hipSuccess) return setup_failed("hipStreamCreate", err);
     if ((err = hipEventCreate(&e0)) != hipSuccess) return setup_failed("hipEventCreate", err);
     if ((err = hipEventCreate(&e1)) != hipSuccess) return setup_failed("hipEventCreate", err);
@@ -357,6 +357,7 @@ int time_candidates(const pk_table *tbl, int dtype, int64_t M, int64_t N, int64_
     for (size_t i : order) {
         const KernelEntry &e = *cands[i].entry;
         MmArgs ca = args;
+        ca.vec = wide_rows(e, M, K, args.A, args.lda, args.B, args.ldb) ? 1 : 0;
         ca.splits = cands[i].ks > 1 ? cands[i].ks : 0;
         // warm-up launch, itself timed: a candidate whose one launch already
         // takes over a millisecond (launch latency is then negligible) and
@@ -424,9 +425,9 @@ int select_params(const pk_table *tbl, int dtype, int64_t M, int64_t N, int64_t 
     if (policy == PK_POLICY_LEARNED && model) {
         // order by predicted time; near-ties are settled by measurement
         std::vector<float> X(cands.size() * PK_NFEATURES), pred(cands.size());
-        const bool wide = !A || wide_rows(dtype, A, lda, B, ldb);
         for (size_t i = 0; i < cands.size(); ++i)
-            features(tbl->machine, *cands[i].entry, dtype, M, N, K, wide, cands[i].ks, &X[i * PK_NFEATURES]);
+            features(tbl->machine, *cands[i].entry, dtype, M, N, K,
+                     !A || wide_rows(*cands[i].entry, M, K, A, lda, B, ldb), cands[i].ks, &X[i * PK_NFEATURES]);
         costmodel_predict(*model, tbl->device, X.data(), (int64_t)cands.size(), pred.data());
         std::vector<int> order(cands.size());
         for (size_t i = 0; i < order.size(); ++i) order[i] = (int)i;

@@ -81,7 +81,9 @@ int64_t grid_of(const pk_machine &m, const KernelEntry &e, int64_t M, int64_t N)
 // the same for a launch: residency from the runtime's occupancy calculator
 int64_t live_blocks_per_cu(const pk_machine &m, const KernelEntry &e);
 int64_t launch_grid(const pk_machine &m, const KernelEntry &e, int64_t M, int64_t N);
-bool wide_rows(int dtype, const void *A, int64_t lda, const void *B, int64_t ldb);
+bool aligned_rows(int dtype, const void *A, int64_t lda, const void *B, int64_t ldb);
+bool direct_reach(int dtype, int64_t rows_a, int64_t lda, int64_t rows_b, int64_t ldb);
+bool wide_rows(const KernelEntry &e, int64_t M, int64_t K, const void *A, int64_t lda, const void *B, int64_t ldb);
 int dma_depth(const pk_machine &m, const KernelEntry &e, int64_t resident, int64_t ksteps, int *extra);
 int launch(const pk_machine &m, const KernelEntry &e, const MmArgs &args, hipStream_t stream);
 void fill_params(const pk_table *tbl, const Candidate &c, int dtype, pk_params *out);

@@ -67,3 +67,60 @@ def test_added_lds_fits_the_hardware_whatever_the_descriptor_says(tmp_path):
     rows = run(tmp_path, DEPTHS, machines.variant(lds_block=1 << 20, lds_cu=1 << 20))
     assert any(int(r[2]) > 0 for r in rows)
     assert all(int(r[2]) + int(r[3]) <= 160 * 1024 for r in rows), [r for r in rows if int(r[2]) + int(r[3]) > 160 * 1024]
+
+
+WIDE = r"""
+int main() {
+    // reads "M K lda ldb" lines' worth of a fixed list; operands at aligned addresses
+    const int64_t cases[][4] = {%s};
+    for (const auto &e : registry()) {
+        if (e.family != PK_FAMILY_MFMA || (e.variant & (PK_MFMA_GROUPED | PK_MFMA_ELEMENT | PK_MFMA_SPLIT)) || e.dtype == PK_I32)
+            continue;
+        std::printf("%%s %%d %%d %%d", e.name, e.tile_m, e.bk, e.dtype == PK_BF16 ? 2 : 4);
+        for (const auto &c : cases)
+            std::printf(" %%d", (int)wide_rows(e, c[0], c[1], (void *)4096, c[2], (void *)8192, c[3]));
+        std::printf("\n");
+    }
+}
+"""
+
+
+def test_row_strides_that_direct_loads_reach(tmp_path):
+    """A program that loads straight to LDS is wide while the last byte of a
+    tile's rows lies within 32 bits of its first, whatever the matrix's other
+    rows; one that loads through registers, on any stride."""
+    cases = [(M, K, lda, ldb) for M in (1, 2, 64, 100, 256, 5000) for K in (1, 20, 64, 5000)
+             for lda, ldb in ((8192, 8192), (1 << 40, 64), (64, 1 << 40), (4000000, 4000000), (17000000, 64),
+                              (34000000, 64), (64, 34000000), (64, 69000000), (128000000, 128000000))]
+    body = WIDE % ", ".join("{%dLL, %dLL, %dLL, %dLL}" % c for c in cases)
+    rows = run(tmp_path, body, machines.gfx950())
+    assert len(rows) >= 40
+    for name, bm, bk, es, *wide in rows:
+        bm, bk, es = int(bm), int(bk), int(es)
+        buffer = bk // 2 if name.endswith("_st1") else bk
+        registers = "_w4x4" in name or (es == 2 and bk == 32 and name.endswith("_st1"))
+        for (M, K, lda, ldb), w in zip(cases, wide):
+            span = max((min(M, bm) - 1) * lda, (min(K, buffer) - 1) * ldb) * es
+            assert int(w) == (registers or span + 4096 <= 2 ** 32), (name, M, K, lda, ldb)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_choice_on_long_aligned_rows(dtype):
+    """Rows of 9 to 30 MB that direct loads reach change nothing in the choice
+    (operand addresses are not read): it is that of short ones."""
+    from paper_1801_04348_amd import pk
+    import ctypes
+    tbl = pk.pk_case_table_build(-1, machines.gfx950())
+    es = 2 if dtype == "bf16" else 4
+
+    def pick(M, N, K, lda, ldb):
+        out = pk.pk_params()
+        pk._check(pk.lib().pk_select_operands(tbl.handle, pk._dt(dtype), ctypes.c_void_p(4096), lda,
+                                              ctypes.c_void_p(8192), ldb, M, N, K, pk.PK_POLICY_CASE,
+                                              ctypes.byref(out)))
+        return out.as_dict() if hasattr(out, "as_dict") else bytes(out)
+
+    for M, N, K in [(1, 64, 512), (64, 64, 4096), (100, 1000, 300), (1000, 256, 512), (2048, 2048, 1024), (4096, 640, 2048)]:
+        for mb in (9, 16):
+            ld = mb * 1000000 // es // 8 * 8
+            assert pick(M, N, K, ld, ld) == pick(M, N, K, max(K, 8) // 8 * 8 + 8, N // 8 * 8 + 8), (M, N, K, mb)
