@@ -120,8 +120,9 @@ namespace pkk {
 // Divisions modulo 2^31 - 1, M = 2^15: K = 100 33 -> 10.5 us (two launches'
 // worth), K = 1000 71 us with 1024 work-items.
 // Phase 2: each workgroup stages the b window of its tile of S * B remainder
-// coefficients and reads the quotient from LDS.  Needs K <= 1024 and B >= 64.  LDS bytes: 4 * (2 * 1024 + S * B + 1024).  a[M .. n-1] are left
-// for the host to clear.
+// coefficients and reads the quotient from LDS.  Needs K <= 1024 and B >= 64.
+// LDS bytes: 4 * (2 * 1024 + S * B + 1024).  a[M .. n-1] are left for the host
+// to clear.
 constexpr int kPdMaxK = 1024;
 constexpr int kPdBlock = 64;  // quotient coefficients per block: one per lane
 
@@ -159,18 +160,17 @@ __device__ __forceinline__ void polydiv_fused(const PdArgs &g) {
     constexpr int TW = S * B;
     __shared__ uint32_t qs[kPdMaxK];              // top[j], turning into q_j
     __shared__ __attribute__((aligned(16))) uint32_t work[2 * kPdMaxK + TW];   // phase 1: divisor coefficients; phase 2: the b window
-    // phase 1: bt[d - 1] = b[M - d] (zeros past the divisor's end and, 64 of
-    // them, before d = 1), and the first 64 of them as (w, w') pairs, with 64
-    // zero pairs before
-    uint32_t *const bt = work + kPdBlock;
-    uint2 *const pairs = reinterpret_cast<uint2 *>(work + 2 * kPdBlock + kPdMaxK);
-    static_assert(2 * kPdBlock + kPdMaxK + 4 * kPdBlock <= 2 * kPdMaxK, "phase 1 fits the window's space");
+    // phase 1: bt[d - 1] = b[M - d] (zeros past the divisor's end), and the
+    // first 64 of them as (w, w') pairs, with 64 zero pairs before
+    uint32_t *const bt = work;
+    uint2 *const pairs = reinterpret_cast<uint2 *>(work + kPdMaxK);
+    static_assert(kPdMaxK + 4 * kPdBlock <= 2 * kPdMaxK, "phase 1 fits the window's space");
     const int M = g.M, n = g.n, K = n - M;
     const uint32_t P = g.P;
     const uint64_t mu = g.mu;
     const int t = threadIdx.x;
     for (int i = t; i < K; i += B) qs[i] = g.a[n - 1 - i];
-    for (int i = t - kPdBlock; i < K; i += B) bt[i] = i >= 0 && i < M ? g.b[M - 1 - i] : 0u;
+    for (int i = t; i < K; i += B) bt[i] = i < M ? g.b[M - 1 - i] : 0u;
     for (int i = t; i < 2 * kPdBlock; i += B) {
         const int d = i - kPdBlock;
         uint32_t w = 0, ws = 0;
@@ -191,7 +191,10 @@ __device__ __forceinline__ void polydiv_fused(const PdArgs &g) {
             const uint2 *const pl = pairs + t;  // step i: d = t - i, pair d - 1 + 64
 #pragma unroll
             for (int i0 = 0; i0 < kPdBlock; i0 += 16) {
-                if (i0 >= kn) break;  // (lanes past kn hold zeros: steps past kn - 1 subtract nothing)
+                // (a step past kn - 1 within the 16 takes its q from a lane past
+                // kn, which it subtracts from lanes further on only: none of
+                // them is stored)
+                if (i0 >= kn) break;
                 uint2 w[16];
 #pragma unroll
                 for (int i = 0; i < 16; ++i) w[i] = pl[kPdBlock - 1 - i0 - i];
