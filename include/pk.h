@@ -313,7 +313,8 @@ int pk_matmul(const pk_table *tbl, const pk_params *params_or_null, pk_dtype dty
  *   PK_POLICY_CASE        per product, the program of least estimated
  *     compute-unit time at the residency of the kernel it runs in; the
  *     kernel (each uniform program fitting every product, each mixed kernel)
- *     of least summed estimate;
+ *     of least estimated time, the larger of its summed compute-unit time
+ *     over the compute units and its longest tile's;
  *   PK_POLICY_EXHAUSTIVE  the auto-tuning of Section 1 at plan level: a plan
  *     of every uniform program and stage count, and of each mixed kernel
  *     under three per-product rules (the CASE estimate, the largest tile
