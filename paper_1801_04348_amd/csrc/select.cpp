@@ -128,6 +128,26 @@ constexpr MfmaFit kFit[3] = {
     /* bfloat16 */ {2.1, 0.938, 14.5, 0.05e-6, 0.156e-6, 2.29, 2.92, 1.19, 2.01e-6, 11.8e12, 4.2e12, 4e-6, 4.49e11, 1.84e-6},
 };
 
+// The VALU programs' estimate, float32 and int32.  Products with a dimension
+// below 64 decide between them and the MFMA programs, and were not among those
+// that the constants above were fitted to: a K step that few workgroups share
+// takes the latency of its loads and barriers (int32: 0.3 us and up to 0.8 more
+// with its K extent), and the operands' bytes cost what they cost the MFMA
+// programs (kFit's hbm).  Fitted to half of 570 int32 and 470 float32 products
+// of 1 to 8192 along each dimension, two thirds of them with one below 64; mean time
+// of the choice over the fastest program's on all, before and with these:
+// int32 1.22 and 1.05 (37 x 4544 x 3168: 317 us chosen, 50 now), float32 1.10
+// and 1.05 (7692 x 6808 x 18: 206 and 49).
+struct ValuFit {
+    double launch;              // seconds
+    double latency, latency_k;  // least seconds of a K step, and per k of a tiled program's
+    double barriers;            // seconds of a step's barriers per resident workgroup
+};
+constexpr ValuFit kValuFit[2] = {
+    /* float32 */ {kLaunchSeconds, 0.1e-6, 0.0, 0.4e-6},
+    /* int32   */ {2.6e-6, 0.28e-6, 0.024e-6, 0.065e-6},
+};
+
 double fourth(double x) { return x * x * x * x; }
 double fourth_root(double x) { return std::sqrt(std::sqrt(x)); }
 
@@ -179,7 +199,8 @@ double estimate_program(const pk_machine &m, const KernelEntry &e, int64_t resid
     // VALU programs.  Per compute unit: the busiest one holds
     // ceil(tiles / NCU) tiles, `res` of them resident at once; each K step of
     // a round costs the larger of the resident tiles' arithmetic at the unit's
-    // rate and one step's latency, and two barriers per resident workgroup.
+    // rate and one step's latency, and two barriers per resident workgroup;
+    // beside that the tiles' and the operands' bytes.
     // The rate falls when few wavefronts share a SIMD to hide LDS and memory
     // latency (full at about three per SIMD), and where workgroups have fewer
     // than 256 work-items, in proportion.
@@ -197,13 +218,14 @@ double estimate_program(const pk_machine &m, const KernelEntry &e, int64_t resid
     const double waves_per_simd = (double)res * ((e.threads + wave - 1) / wave) / 4.0;
     const double occupancy = waves_per_simd >= 3.0 ? 1.0 : fourth_root(waves_per_simd / 3.0);
     const double rate = prate * clock * std::min(1.0, e.threads / 256.0) * occupancy;
-    const double latency = 0.1e-6;
-    const double overhead = (dtype == PK_I32 ? 0.1e-6 : 0.4e-6) * (double)res;  // (each type's fitted)
+    const ValuFit &f = kValuFit[dtype];
+    const double latency = f.latency + ((e.variant & PK_VALU_NOLDS) ? 0.0 : f.latency_k * bk);
+    const double overhead = f.barriers * (double)res;
     const double compute = (double)rounds * ksteps * (std::max((double)res * flops_step / rate, latency) + overhead);
     const double es = elem_bytes(dtype);
     const double tile_bytes = es * (double)tiles * (double)K * (e.tile_m + e.tile_n);
-    const double hbm = (es * ((double)M * K + (double)K * N) + 4.0 * (double)M * N) / kHbmBytesPerSecond;
-    return std::max(compute, std::max(tile_bytes / kHbmBytesPerSecond, hbm)) + kLaunchSeconds;
+    const double hbm = (es * ((double)M * K + (double)K * N) + 4.0 * (double)M * N) / kFit[dtype].hbm;
+    return std::max(compute, std::max(tile_bytes / kHbmBytesPerSecond, hbm)) + f.launch;
 }
 
 }  // namespace

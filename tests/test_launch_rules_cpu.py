@@ -124,3 +124,15 @@ def test_choice_on_long_aligned_rows(dtype):
         for mb in (9, 16):
             ld = mb * 1000000 // es // 8 * 8
             assert pick(M, N, K, ld, ld) == pick(M, N, K, max(K, 8) // 8 * 8 + 8, N // 8 * 8 + 8), (M, N, K, mb)
+
+
+@pytest.mark.parametrize("dtype,M,N,K", [
+    ("i32", 59, 8140, 2164), ("i32", 6, 4744, 5632), ("i32", 25, 4256, 2640), ("i32", 23, 2336, 7816),
+    ("i32", 3, 2936, 4336), ("i32", 6943, 27, 6782), ("i32", 3213, 9, 6520), ("i32", 53, 1008, 4614),
+    ("f32", 8141, 6355, 15), ("f32", 7692, 6808, 18), ("f32", 3616, 3576, 4), ("f32", 1224, 6884, 21)])
+def test_thin_products_run_on_the_matrix_cores(dtype, M, N, K):
+    """Products with a dimension below 64 whose fastest VALU program takes 1.3
+    to 4 times the fastest MFMA program's time (timed on gfx950)."""
+    from paper_1801_04348_amd import pk
+    tbl = pk.pk_case_table_build(-1, machines.variant(regs_block=65536, regs_cu=65536, max_blocks_cu=2))
+    assert pk.pk_select(tbl, dtype, M, N, K).family == pk.PK_FAMILY_MFMA
