@@ -104,6 +104,7 @@ typedef struct {
 #define PK_MFMA_ELEMENT 4 /* internal: the twin of a program that reads rows at element alignment */
 #define PK_MFMA_MIXED 8   /* internal: a grouped kernel running a different tile program per product */
 #define PK_MFMA_SPLIT 16  /* internal: the form of a program that runs shares of K (pk_params.ks > 1) */
+#define PK_MFMA_STREAM 32 /* internal: the form of a grouped kernel for groups that come from HBM */
 
 /* A leaf choice together with its program parameters E.
  *   family  - PK_FAMILY_*

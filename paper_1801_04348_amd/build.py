@@ -51,6 +51,7 @@ MFMA_GROUPED = 2
 MFMA_ELEMENT = 4
 MFMA_MIXED = 8
 MFMA_SPLIT = 16
+MFMA_STREAM = 32
 # the mixed grouped kernels' tile programs (csrc/kernels/kargs.hpp kMixedTile,
 # in the same order) and K tiles
 MIXED_TILES = [(64, 64), (128, 64), (64, 128), (128, 128)]
@@ -289,6 +290,16 @@ def instances():
                                  tile_n=bn, args="pkk::GroupArgs g",
                                  attrs=mfma_reg_cap(dt, 64 * wm * wn, stages, "grouped"))
                     out.append(("grouped_%s%s" % (DT_NAME[dt], "" if wide else "_el"), name, body, entry))
+                    # the form for groups that come from HBM (aligned rows through
+                    # registers); the 64 x 64 program at 96 registers, five
+                    # workgroups a compute unit, the others as the compiler needs
+                    # (at four a unit they spill)
+                    if dt == BF16 and stages == 1 and wide:
+                        body_hb = body.replace(", true>(g)", ", true, true>(g)")
+                        entry_hb = dict(entry, variant=entry["variant"] | MFMA_STREAM)
+                        if bm * bn == 64 * 64:
+                            entry_hb["attrs"] = "__attribute__((amdgpu_waves_per_eu(5)))"
+                        out.append(("grouped_bf16_hb", name + "_hb", body_hb, entry_hb))
     # mixed grouped kernels: a tile program per product (kMixedTile), 2 x 2
     # wavefronts, LDS sized for the largest program
     for dt, fn in ((F32, "grouped_mixed_f32"), (BF16, "grouped_mixed_bf16")):
@@ -304,6 +315,9 @@ def instances():
                              wn=2, threads=256, lds=lds, tile_m=bm, tile_n=bn, args="pkk::GroupArgs g",
                              attrs=mfma_reg_cap(dt, 256, stages, "grouped"))
                 out.append(("grouped_mixed_%s%s" % (DT_NAME[dt], "" if wide else "_el"), name, body, entry))
+                if dt == BF16 and wide:
+                    out.append(("grouped_mixed_bf16_hb", name + "_hb", body.replace(", true>(g)", ", true, true>(g)"),
+                                dict(entry, variant=entry["variant"] | MFMA_STREAM)))
     return out
 
 

@@ -459,8 +459,10 @@ const KernelEntry *find_instance(int family, int variant, int dtype, const std::
         if (variant & PK_VALU_GRAN) q[2] = 1;
         kind = variant & PK_VALU_NOLDS;
     } else {
-        // grouped instances come as a wide kernel and its element-load twin
-        kind = variant & (PK_MFMA_SINGLE | PK_MFMA_GROUPED | ((variant & PK_MFMA_GROUPED) ? PK_MFMA_ELEMENT : 0));
+        // grouped instances come as a wide kernel, its element-load twin and,
+        // some, the form for groups that come from HBM
+        kind = variant & (PK_MFMA_SINGLE | PK_MFMA_GROUPED |
+                          ((variant & PK_MFMA_GROUPED) ? PK_MFMA_ELEMENT | PK_MFMA_STREAM : 0));
     }
     for (const auto &e : registry()) {
         if (e.family != family || e.dtype != dtype || e.variant != kind) continue;

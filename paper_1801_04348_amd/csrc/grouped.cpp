@@ -131,8 +131,16 @@ bool live(const GroupedOperands &o, int g) { return o.M[g] > 0 && o.N[g] > 0; }
 // descriptor, then its first K step's operands, loads each waiting on the
 // last) and closing (its stores), which nothing in its workgroup overlaps:
 // its tiles are a few K steps long and run one after another.  Only the
-// other workgroups resident on the compute unit hide it.
-constexpr double kTileOpenClose = 3e-6;
+// other workgroups resident on the compute unit hide it.  The second figure,
+// and the factor on programs with tiles of 64 columns (whose rows of B and C
+// are the shortest pieces of HBM's pages), are for aligned rows of groups that
+// come from HBM (from_hbm): over 14 groups of 62-683 MB the chosen single-stage
+// program took 1.010 times the fastest one's time, 1.041 with the first figure.
+constexpr double kTileOpenClose = 3e-6, kTileOpenCloseHbm = 5e-6, kNarrowHbm = 1.15;
+
+double tile_open_close(const KernelEntry &e, bool hbm) {
+    return hbm && !(e.variant & PK_MFMA_ELEMENT) ? kTileOpenCloseHbm : kTileOpenClose;
+}
 
 // Work of the mixed kernels against a uniform launch of the same tiles: they
 // hold the registers of their largest program and its LDS.  Unaligned
@@ -158,23 +166,45 @@ double ksteps_of(const KernelEntry &e, int64_t K) {
 }
 
 // Estimated compute-unit seconds of a product under a grouped program.
-double product_cost(const pk_machine &m, const KernelEntry &e, int dtype, int64_t M, int64_t N, int64_t K) {
+double product_cost(const pk_machine &m, const KernelEntry &e, int dtype, int64_t M, int64_t N, int64_t K, bool hbm) {
     const int64_t tiles = ((M + e.tile_m - 1) / e.tile_m) * ((N + e.tile_n - 1) / e.tile_n);
     const int64_t res = resident_workgroups(m, e, ksteps_of(e, K));
-    const double work = tile_work_seconds(m, e, dtype, M, N, K, res) + (double)tiles * kTileOpenClose / (double)res;
+    double work = tile_work_seconds(m, e, dtype, M, N, K, res) + (double)tiles * tile_open_close(e, hbm) / (double)res;
+    if (hbm && !(e.variant & PK_MFMA_ELEMENT) && e.tile_n <= 64) work *= kNarrowHbm;
     return (e.variant & PK_MFMA_MIXED) ? kMixedWork * work : work;
 }
 
 // Estimated seconds of one tile with a compute unit to itself.
-double lone_tile_seconds(const pk_machine &m, const KernelEntry &e, int dtype, int64_t K) {
-    return tile_work_seconds(m, e, dtype, e.tile_m, e.tile_n, K, 1) + kTileOpenClose;
+double lone_tile_seconds(const pk_machine &m, const KernelEntry &e, int dtype, int64_t K, bool hbm) {
+    return tile_work_seconds(m, e, dtype, e.tile_m, e.tile_n, K, 1) + tile_open_close(e, hbm);
 }
 
-// The grouped kernel form a product runs in: the wide kernel, or its
-// element-load twin (PK_MFMA_ELEMENT).
-int form_of(int dtype, const GroupedOperands &o, int g) {
-    return grouped_wide(dtype, o, g) ? 0 : (int)PK_MFMA_ELEMENT;
+// A group too large to stay in the memory-side cache (256 MB) from one run to
+// the next beside as much other data: its aligned bfloat16 products run the
+// single-stage kernels' form for operands that come from HBM.  Fresh operands
+// each run and the same ones, direct and through registers: 3000 products of
+// 16-200 (133 MB) 49.0, 45.6 and 31.6, 32.4 us; 1000 of 16-512 (164 MB) 56.8,
+// 50.9 and 46.2, 45.2; 300 of 16-512 (46 MB) 20.3, 18.6 and 12.4, 13.5.
+// (float32 multiplies longer than it loads: direct everywhere.)
+constexpr double kCachedBytes = 128.0 * (1 << 20);
+
+bool from_hbm(int dtype, const GroupedOperands &o) {
+    if (dtype != PK_BF16) return false;
+    double bytes = 0.0;
+    for (int g = 0; g < o.G; ++g)
+        if (live(o, g))
+            bytes += 2.0 * ((double)o.M[g] * o.K[g] + (double)o.K[g] * o.N[g]) + 4.0 * (double)o.M[g] * o.N[g];
+    return bytes > kCachedBytes;
 }
+
+// The grouped kernel form a product runs in, an index of kForms: the wide
+// kernel, its element-load twin, or its form for operands that come from HBM.
+constexpr int kForms[3] = {0, PK_MFMA_ELEMENT, PK_MFMA_STREAM};
+int form_of(int dtype, const GroupedOperands &o, int g, int stage, bool hbm) {
+    if (!grouped_wide(dtype, o, g)) return 1;
+    return hbm && (stage & PK_MFMA_SINGLE) ? 2 : 0;
+}
+int form_index(const KernelEntry &e) { return (e.variant & PK_MFMA_ELEMENT) ? 1 : (e.variant & PK_MFMA_STREAM) ? 2 : 0; }
 
 int check_operands(const GroupedOperands &o) {
     for (int g = 0; g < o.G; ++g) {
@@ -204,9 +234,11 @@ struct Feasibility {
     const pk_table::Part *part = nullptr;
     std::vector<char> ok;                               // per point index
     int prog_point[kMixedPrograms] = {-1, -1, -1, -1};  // point index of each mixed program
+    bool hbm = false;                                   // from_hbm of the group
 };
 
-int feasibility(const pk_table *tbl, int dtype, Feasibility *f) {
+int feasibility(const pk_table *tbl, int dtype, const GroupedOperands &o, Feasibility *f) {
+    f->hbm = from_hbm(dtype, o);
     f->part = tbl->part(PK_FAMILY_MFMA, dtype);
     if (!f->part || !f->part->supported) return fail(PK_ERR_UNSUPPORTED_DTYPE, "no MFMA family for the dtype");
     const auto &pts = f->part->fam.points;
@@ -232,18 +264,18 @@ bool assign_uniform(const pk_table *tbl, int dtype, const GroupedOperands &o, co
                     int stage, std::vector<Assign> *out) {
     if (!f.ok[pi]) return false;
     const auto &pt = f.part->fam.points[pi];
-    const KernelEntry *forms[2] = {find_instance(PK_FAMILY_MFMA, stage | PK_MFMA_GROUPED, dtype, pt),
-                                   find_instance(PK_FAMILY_MFMA, stage | PK_MFMA_GROUPED | PK_MFMA_ELEMENT, dtype, pt)};
+    const KernelEntry *forms[3];
+    for (int w = 0; w < 3; ++w) forms[w] = find_instance(PK_FAMILY_MFMA, stage | PK_MFMA_GROUPED | kForms[w], dtype, pt);
     out->assign(o.G, Assign{});
     for (int g = 0; g < o.G; ++g) {
         if (!live(o, g)) continue;
-        const KernelEntry *e = forms[form_of(dtype, o, g) ? 1 : 0];
+        const KernelEntry *e = forms[form_of(dtype, o, g, stage, f.hbm)];
         if (!e || !entry_fits(tbl->machine, *e)) return false;
         Assign &a = (*out)[g];
         a.entry = e;
         a.tile_m = e->tile_m;
         a.tile_n = e->tile_n;
-        a.cost = product_cost(tbl->machine, *e, dtype, o.M[g], o.N[g], o.K[g]);
+        a.cost = product_cost(tbl->machine, *e, dtype, o.M[g], o.N[g], o.K[g], f.hbm);
         a.params = program_params(pt, stage);
     }
     return true;
@@ -254,15 +286,17 @@ enum MixedRule { RULE_ESTIMATE = 0, RULE_WASTE_15, RULE_WASTE_35 };
 
 bool assign_mixed(const pk_table *tbl, int dtype, const GroupedOperands &o, const Feasibility &f, int stage,
                   int rule, std::vector<Assign> *out) {
-    const KernelEntry *forms[2] = {mixed_entry(dtype, stage), mixed_entry(dtype, stage | PK_MFMA_ELEMENT)};
-    KernelEntry progs_of[2][kMixedPrograms];
-    for (int w = 0; w < 2; ++w)
+    const KernelEntry *forms[3];
+    KernelEntry progs_of[3][kMixedPrograms];
+    for (int w = 0; w < 3; ++w) {
+        forms[w] = mixed_entry(dtype, stage | kForms[w]);
         if (forms[w])
             for (int p = 0; p < kMixedPrograms; ++p) progs_of[w][p] = as_program(*forms[w], p);
+    }
     out->assign(o.G, Assign{});
     for (int g = 0; g < o.G; ++g) {
         if (!live(o, g)) continue;
-        const int w = form_of(dtype, o, g) ? 1 : 0;
+        const int w = form_of(dtype, o, g, stage, f.hbm);
         const KernelEntry *e = forms[w];
         if (!e || !entry_fits(tbl->machine, *e)) return false;
         const KernelEntry *progs = progs_of[w];
@@ -271,7 +305,7 @@ bool assign_mixed(const pk_table *tbl, int dtype, const GroupedOperands &o, cons
         for (int p = 0; p < kMixedPrograms; ++p) {
             cost[p] = -1.0;
             if (f.prog_point[p] < 0 || !f.ok[f.prog_point[p]]) continue;
-            cost[p] = product_cost(tbl->machine, progs[p], dtype, o.M[g], o.N[g], o.K[g]);
+            cost[p] = product_cost(tbl->machine, progs[p], dtype, o.M[g], o.N[g], o.K[g], f.hbm);
             if (best < 0 || cost[p] < best_cost) {
                 best = p;
                 best_cost = cost[p];
@@ -309,7 +343,8 @@ bool assign_mixed(const pk_table *tbl, int dtype, const GroupedOperands &o, cons
 // few products, which leave compute units empty under large tiles: 38 bfloat16
 // products of 16-388, unaligned, ran 13.1 us on the mixed program that their
 // work alone prefers and 8.3 on 64 x 64 tiles.
-double assignment_seconds(const pk_table *tbl, int dtype, const GroupedOperands &o, const std::vector<Assign> &as) {
+double assignment_seconds(const pk_table *tbl, int dtype, const GroupedOperands &o, bool hbm,
+                          const std::vector<Assign> &as) {
     double work = 0.0, longest = 0.0;
     std::map<std::tuple<const KernelEntry *, int, int64_t>, double> lone;  // by program and K
     for (int g = 0; g < o.G; ++g) {
@@ -319,7 +354,7 @@ double assignment_seconds(const pk_table *tbl, int dtype, const GroupedOperands 
         auto it = lone.emplace(std::make_tuple(a.entry, a.prog, o.K[g]), 0.0);
         if (it.second)
             it.first->second = lone_tile_seconds(
-                tbl->machine, (a.entry->variant & PK_MFMA_MIXED) ? as_program(*a.entry, a.prog) : *a.entry, dtype, o.K[g]);
+                tbl->machine, (a.entry->variant & PK_MFMA_MIXED) ? as_program(*a.entry, a.prog) : *a.entry, dtype, o.K[g], hbm);
         longest = std::max(longest, it.first->second);
     }
     return std::max(work / std::max<int32_t>(tbl->machine.cu_count, 1), longest);
@@ -328,7 +363,7 @@ double assignment_seconds(const pk_table *tbl, int dtype, const GroupedOperands 
 // A mixed assignment whose products all run one program runs that program's
 // uniform instance instead (fewer registers, the same arithmetic), when it
 // fits.
-void prefer_uniform(const pk_table *tbl, int dtype, const GroupedOperands &o, std::vector<Assign> *as) {
+void prefer_uniform(const pk_table *tbl, int dtype, const GroupedOperands &o, bool hbm, std::vector<Assign> *as) {
     const KernelEntry *mixed = nullptr;
     int prog = -1;
     for (int g = 0; g < o.G; ++g) {
@@ -342,21 +377,21 @@ void prefer_uniform(const pk_table *tbl, int dtype, const GroupedOperands &o, st
     if (!mixed) return;
     const int stage = mixed->variant & PK_MFMA_SINGLE;
     const std::vector<int64_t> pt = {kMixedTile[prog][0], kMixedTile[prog][1], pkk::kMixedBk[dtype], 2, 2};
-    const KernelEntry *forms[2] = {find_instance(PK_FAMILY_MFMA, stage | PK_MFMA_GROUPED, dtype, pt),
-                                   find_instance(PK_FAMILY_MFMA, stage | PK_MFMA_GROUPED | PK_MFMA_ELEMENT, dtype, pt)};
+    const KernelEntry *forms[3];
+    for (int w = 0; w < 3; ++w) forms[w] = find_instance(PK_FAMILY_MFMA, stage | PK_MFMA_GROUPED | kForms[w], dtype, pt);
     for (int g = 0; g < o.G; ++g) {
         const Assign &a = (*as)[g];
         if (!a.entry) continue;
-        const KernelEntry *e = forms[(a.entry->variant & PK_MFMA_ELEMENT) ? 1 : 0];
+        const KernelEntry *e = forms[form_index(*a.entry)];
         if (!e || !entry_fits(tbl->machine, *e)) return;
     }
     for (int g = 0; g < o.G; ++g) {
         Assign &a = (*as)[g];
         if (!a.entry) continue;
-        const KernelEntry *e = forms[(a.entry->variant & PK_MFMA_ELEMENT) ? 1 : 0];
+        const KernelEntry *e = forms[form_index(*a.entry)];
         a.entry = e;
         a.prog = 0;
-        a.cost = product_cost(tbl->machine, *e, dtype, o.M[g], o.N[g], o.K[g]);
+        a.cost = product_cost(tbl->machine, *e, dtype, o.M[g], o.N[g], o.K[g], hbm);
     }
 }
 
@@ -484,36 +519,37 @@ int assign_given(const pk_table *tbl, int dtype, const GroupedOperands &o, const
         if (!in_mixed) all_mixed = false;
     }
     if (first < 0) return PK_OK;
-    const KernelEntry *mixed_forms[2] = {nullptr, nullptr};
+    const bool hbm = from_hbm(dtype, o);
+    const KernelEntry *mixed_forms[3] = {nullptr, nullptr, nullptr};
     bool use_mixed = !one_program && all_mixed;
     if (use_mixed)
         for (int g = 0; g < o.G; ++g) {
             if (!live(o, g)) continue;
-            const int w = form_of(dtype, o, g) ? 1 : 0;
-            if (!mixed_forms[w]) mixed_forms[w] = mixed_entry(dtype, stage[first] | (w ? PK_MFMA_ELEMENT : 0));
+            const int w = form_of(dtype, o, g, stage[first], hbm);
+            if (!mixed_forms[w]) mixed_forms[w] = mixed_entry(dtype, stage[first] | kForms[w]);
             if (!mixed_forms[w] || !entry_fits(tbl->machine, *mixed_forms[w])) use_mixed = false;
         }
     for (int g = 0; g < o.G; ++g) {
         if (!live(o, g)) continue;
         Assign &a = (*out)[g];
-        const int w = form_of(dtype, o, g) ? 1 : 0;
+        const int w = form_of(dtype, o, g, stage[g], hbm);
         if (use_mixed) {
             const KernelEntry *mixed = mixed_forms[w];
             a.entry = mixed;
             const KernelEntry x = as_program(*mixed, a.prog);
             a.tile_m = x.tile_m;
             a.tile_n = x.tile_n;
-            a.cost = product_cost(tbl->machine, x, dtype, o.M[g], o.N[g], o.K[g]);
+            a.cost = product_cost(tbl->machine, x, dtype, o.M[g], o.N[g], o.K[g], hbm);
             continue;
         }
         const KernelEntry *e =
-            find_instance(PK_FAMILY_MFMA, stage[g] | PK_MFMA_GROUPED | (w ? PK_MFMA_ELEMENT : 0), dtype, pts[g]);
+            find_instance(PK_FAMILY_MFMA, stage[g] | PK_MFMA_GROUPED | kForms[w], dtype, pts[g]);
         if (!e) return fail(PK_ERR_NOT_INSTANTIATED, "no grouped instance for product " + std::to_string(g));
         a.entry = e;
         a.prog = 0;
         a.tile_m = e->tile_m;
         a.tile_n = e->tile_n;
-        a.cost = product_cost(tbl->machine, *e, dtype, o.M[g], o.N[g], o.K[g]);
+        a.cost = product_cost(tbl->machine, *e, dtype, o.M[g], o.N[g], o.K[g], hbm);
     }
     return PK_OK;
 }
@@ -533,7 +569,7 @@ int candidate_assignments(const pk_table *tbl, int dtype, const GroupedOperands 
             if (!all_rules && rule != RULE_ESTIMATE) continue;
             std::vector<Assign> as;
             if (!assign_mixed(tbl, dtype, o, f, stage, rule, &as)) continue;
-            prefer_uniform(tbl, dtype, o, &as);
+            prefer_uniform(tbl, dtype, o, f.hbm, &as);
             out->push_back(std::move(as));
         }
     if (out->empty()) return fail(PK_ERR_NO_FEASIBLE_BRANCH, "no grouped kernel fits every product");
@@ -613,7 +649,7 @@ int grouped_layout(const pk_table *tbl, int dtype, const GroupedOperands &o, con
         return build_from(tbl, dtype, o, as, out);
     }
     Feasibility f;
-    rc = feasibility(tbl, dtype, &f);
+    rc = feasibility(tbl, dtype, o, &f);
     if (rc != PK_OK) return rc;
     std::vector<std::vector<Assign>> cands;
     rc = candidate_assignments(tbl, dtype, o, f, false, &cands);
@@ -621,7 +657,7 @@ int grouped_layout(const pk_table *tbl, int dtype, const GroupedOperands &o, con
     size_t best = 0;
     double best_seconds = 0.0;
     for (size_t i = 0; i < cands.size(); ++i) {
-        const double seconds = assignment_seconds(tbl, dtype, o, cands[i]);
+        const double seconds = assignment_seconds(tbl, dtype, o, f.hbm, cands[i]);
         if (i == 0 || seconds < best_seconds) {
             best = i;
             best_seconds = seconds;
@@ -688,7 +724,7 @@ int pk_grouped_plan_create(const pk_table *tbl, pk_dtype dtype, int32_t G, const
             rc = check_operands(o);
             if (rc != PK_OK) return rc;
             Feasibility f;
-            rc = feasibility(tbl, (int)dtype, &f);
+            rc = feasibility(tbl, (int)dtype, o, &f);
             if (rc != PK_OK) return rc;
             std::vector<std::vector<Assign>> cands;
             rc = candidate_assignments(tbl, (int)dtype, o, f, true, &cands);

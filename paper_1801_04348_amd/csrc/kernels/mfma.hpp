@@ -953,11 +953,26 @@ __device__ __forceinline__ void walk_tiles(const GroupArgs &g, Tile &&tile) {
 // element-load path -- fewer registers, one more resident wavefront per SIMD
 // for the 64 x 64 programs; the element-load twin (WIDE = false) runs the
 // products whose rows are not aligned.
-template <int EB, int BM, int BN, int BK, int WM, int WN, int STAGES, bool WIDE>
+// STREAM (bfloat16, single-stage, aligned rows): through registers all the
+// same, for groups too large to stay in the memory-side cache.  What bounds
+// those is HBM's latency and how its lines are used: direct loads fetch a row
+// of A in pieces of half a K step, 64 bytes of a 128-byte line, and wait for
+// each half; through registers a whole step's line is one request.  Fresh
+// operands each run, 64 x 128 tiles, rows padded to 8: 2500 products of 16-400
+// (295 MB) 97.7 us direct and 86.9 so, 4096 of 16-512 (683 MB) 220 and 203, 300
+// of 300-512 (376 MB) 151 and 139; held in the cache, 300 products of 16-512
+// (46 MB), 12.4 and 13.5.  Both halves of A's lines requested at once, in four
+// half-step buffers, gave half of it (2500 products: 91); whole steps through
+// two buffers as much as registers where operands come from HBM (90), but cost
+// workgroups, and 10-25 % where they do not.
+template <int EB, int BM, int BN, int BK, int WM, int WN, int STAGES, bool WIDE, bool STREAM = false>
 __device__ __forceinline__ void grouped_tile(const GroupArgs &g, const GroupDesc &d, int local, unsigned char *lds) {
     const int tm = local / d.tiles_n, tn = local % d.tiles_n;
     const MmArgs a{d.A, d.B, d.C, d.lda, d.ldb, d.ldc, d.M, d.N, d.K, g.accumulate, WIDE, 0, 2};
-    mfma_tile<EB, BM, BN, BK, WM, WN, STAGES, WIDE, 2>(a, tm * BM, tn * BN, lds, 0, (d.K + BK - 1) / BK);
+    if constexpr (STREAM)
+        regs_tile<EB, BM, BN, BK, WM, WN, STAGES, WIDE, true>(a, tm * BM, tn * BN, lds, 0, (d.K + BK - 1) / BK);
+    else
+        mfma_tile<EB, BM, BN, BK, WM, WN, STAGES, WIDE, 2>(a, tm * BM, tn * BN, lds, 0, (d.K + BK - 1) / BK);
 }
 
 template <int BM, int BN, int BK, int WM, int WN, int STAGES, bool WIDE>
@@ -966,10 +981,12 @@ __device__ __forceinline__ void grouped_f32(const GroupArgs &g) {
     walk_tiles(g, [&](const GroupDesc &d, int local) { grouped_tile<4, BM, BN, BK, WM, WN, STAGES, WIDE>(g, d, local, lds); });
 }
 
-template <int BM, int BN, int BK, int WM, int WN, int STAGES, bool WIDE>
+template <int BM, int BN, int BK, int WM, int WN, int STAGES, bool WIDE, bool STREAM = false>
 __device__ __forceinline__ void grouped_bf16(const GroupArgs &g) {
     __shared__ __attribute__((aligned(256))) unsigned char lds[bf16_lds(BM, BN, BK, STAGES)];
-    walk_tiles(g, [&](const GroupDesc &d, int local) { grouped_tile<2, BM, BN, BK, WM, WN, STAGES, WIDE>(g, d, local, lds); });
+    walk_tiles(g, [&](const GroupDesc &d, int local) {
+        grouped_tile<2, BM, BN, BK, WM, WN, STAGES, WIDE, STREAM>(g, d, local, lds);
+    });
 }
 
 // Mixed grouped kernels: each product's tiles run the program kMixedTile[prog]
@@ -982,26 +999,26 @@ template <int EB, int STAGES> constexpr int mixed_lds() {
     return n;
 }
 
-template <int EB, int STAGES, bool WIDE>
+template <int EB, int STAGES, bool WIDE, bool STREAM>
 __device__ __forceinline__ void grouped_mixed(const GroupArgs &g) {
     static_assert(kMixedPrograms == 4, "one case per program");
     constexpr int BK = kMixedBk[EB == 4 ? 0 : 2];
     __shared__ __attribute__((aligned(256))) unsigned char lds[mixed_lds<EB, STAGES>()];
     walk_tiles(g, [&](const GroupDesc &d, int local) {
         switch (d.prog) {
-        case 0: grouped_tile<EB, kMixedTile[0][0], kMixedTile[0][1], BK, 2, 2, STAGES, WIDE>(g, d, local, lds); break;
-        case 1: grouped_tile<EB, kMixedTile[1][0], kMixedTile[1][1], BK, 2, 2, STAGES, WIDE>(g, d, local, lds); break;
-        case 2: grouped_tile<EB, kMixedTile[2][0], kMixedTile[2][1], BK, 2, 2, STAGES, WIDE>(g, d, local, lds); break;
-        default: grouped_tile<EB, kMixedTile[3][0], kMixedTile[3][1], BK, 2, 2, STAGES, WIDE>(g, d, local, lds); break;
+        case 0: grouped_tile<EB, kMixedTile[0][0], kMixedTile[0][1], BK, 2, 2, STAGES, WIDE, STREAM>(g, d, local, lds); break;
+        case 1: grouped_tile<EB, kMixedTile[1][0], kMixedTile[1][1], BK, 2, 2, STAGES, WIDE, STREAM>(g, d, local, lds); break;
+        case 2: grouped_tile<EB, kMixedTile[2][0], kMixedTile[2][1], BK, 2, 2, STAGES, WIDE, STREAM>(g, d, local, lds); break;
+        default: grouped_tile<EB, kMixedTile[3][0], kMixedTile[3][1], BK, 2, 2, STAGES, WIDE, STREAM>(g, d, local, lds); break;
         }
     });
 }
 
 template <int STAGES, bool WIDE> __device__ __forceinline__ void grouped_mixed_f32(const GroupArgs &g) {
-    grouped_mixed<4, STAGES, WIDE>(g);
+    grouped_mixed<4, STAGES, WIDE, false>(g);
 }
-template <int STAGES, bool WIDE> __device__ __forceinline__ void grouped_mixed_bf16(const GroupArgs &g) {
-    grouped_mixed<2, STAGES, WIDE>(g);
+template <int STAGES, bool WIDE, bool STREAM = false> __device__ __forceinline__ void grouped_mixed_bf16(const GroupArgs &g) {
+    grouped_mixed<2, STAGES, WIDE, STREAM>(g);
 }
 
 }  // namespace pkk
