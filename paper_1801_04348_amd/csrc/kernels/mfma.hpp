@@ -12,7 +12,8 @@
 // LDS holds a step's tiles as they lie in memory, A row by row (k contiguous)
 // and B row by row (n contiguous), in chunks of 16 bytes without padding; the
 // chunks of a row are permuted (a_swz, b_swz) so that the reads that feed the
-// matrix unit fall in distinct banks.
+// matrix unit fall in distinct banks (counted: no conflict cycles in any of
+// them).
 //
 // Two ways bring the tiles there:
 //   dma_tile   rows aligned for 16-byte loads: global_load_lds writes each
@@ -22,14 +23,15 @@
 //              and no wait drains more than it must.  A program's LDS stage
 //              budget decides: STAGES = 2 holds two buffers of BK; STAGES = 1,
 //              the paper's one buffer, is cut into two of BK / 2.
-//   regs_tile  other rows (and the single-stage bfloat16 programs of K tile
-//              32, too small to cut): chunks at element alignment through
+//   regs_tile  other rows (and the programs of 1024 work-items, the
+//              single-stage bfloat16 ones of K tile 32, too small to cut, and
+//              large bfloat16 groups): chunks at element alignment through
 //              registers, the next step's loads in flight while the current
 //              step multiplies, STAGES buffers of BK.
 // Against loads through registers with padded LDS (the earlier form of both),
 // bfloat16 with 16 x 16 x 32 products: a float32 8192 x 3000 x 4096 product
-// 1683 -> 1444 us (64 x 64 tiles), a bfloat16 product of order 4096 150 -> 122
-// us (1.13 PFLOP/s, operands from HBM), one of order 1024 14 -> 7.
+// 1683 -> 1444 us (64 x 64 tiles), a bfloat16 product of order 4096 150 ->
+// 122-127 us (1.1 PFLOP/s, operands from HBM), one of order 1024 14 -> 7.
 // The 16 x 16 x 32 form draws less power than 32 x 32 x 16 at the same rate
 // (half the accumulator traffic): a dense 4096^3 product runs at 2.2 GHz with
 // it and 1.95 GHz without.
@@ -116,7 +118,9 @@ __device__ __forceinline__ void tile_of(uint32_t b, uint32_t tiles_m, uint32_t t
 // ------------------------------------------------------------------ tiles in LDS
 // A BM x BK tile of A and a BK x BN tile of B (EB bytes an element) for WM x WN
 // wavefronts: chunks of 16 bytes, slots in LDS, the wavefront's operands and
-// products.
+// products.  The programs allocate what rows padded by 16 bytes (bfloat16 B: 64)
+// would need, the case table's LDS symbol; the chunks need A_BYTES + B_BYTES a
+// buffer, less by a tenth to a quarter.
 constexpr int f32_lds(int bm, int bn, int bk, int stages) { return stages * 4 * (bm * (bk + 4) + bk * (bn + 4)); }
 constexpr int bf16_lds(int bm, int bn, int bk, int stages) { return stages * 2 * (bm * (bk + 8) + bk * (bn + 32)); }
 

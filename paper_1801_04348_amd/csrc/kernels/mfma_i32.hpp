@@ -25,7 +25,9 @@ namespace pkk {
 // k contiguous, rows BK + 16 bytes apart) and of the B tile stored by column
 // (BN columns of BK bytes, k contiguous): 4 (BM + BN) (BK + 16) bytes.  With
 // rows BK + 16 bytes apart (48 or 80) the sixteen 16-byte reads of a quarter
-// wavefront, one per row, cover 64 distinct banks.
+// wavefront, one per row, cover 64 distinct banks.  The stores of the digits do
+// not: a third of a conflict cycle per LDS cycle, with the LDS busy 19 % (order
+// 1024) to 46 % (order 4096) of the time.
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x16 __attribute__((ext_vector_type(16)));
 
