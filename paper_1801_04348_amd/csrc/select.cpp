@@ -36,7 +36,6 @@
 namespace pk {
 
 namespace {
-constexpr double kLaunchSeconds = 4e-6;
 constexpr double kHbmBytesPerSecond = 8e12;
 
 int elem_bytes(int dtype) { return dtype == PK_BF16 ? 2 : 4; }
@@ -134,21 +133,26 @@ constexpr MfmaFit kFit[3] = {
 // The VALU programs' estimate, float32 and int32.  Products with a dimension
 // below 64 decide between them and the MFMA programs, and were not among those
 // that the constants above were fitted to: a K step that few workgroups share
-// takes the latency of its loads and barriers (int32: 0.3 us and up to 0.8 more
-// with its K extent), and the operands' bytes cost what they cost the MFMA
-// programs (kFit's hbm).  Fitted to half of 570 int32 and 470 float32 products
-// of 1 to 8192 along each dimension, two thirds of them with one below 64; mean time
-// of the choice over the fastest program's on all, before and with these:
-// int32 1.22 and 1.05 (37 x 4544 x 3168: 317 us chosen, 50 now), float32 1.10
-// and 1.05 (7692 x 6808 x 18: 206 and 49).
+// takes the latency of its loads and of its barriers, and the operands' bytes
+// cost what they cost the MFMA programs (kFit's hbm).  The smallest products
+// are a launch and a store: on the device 2.6 to 3 us with a VALU program and 4.2
+// with an MFMA one, whose launch and open kFit counts as 3.6 to 4.1.  Fitted to half of
+// 570 int32 and 470 float32 products of 1 to 8192 along each dimension, two
+// thirds of them with one below 64, and of 160 each of up to 50 MFLOP; mean
+// time of the choice over the fastest program's on all of the former and all
+// of the latter: int32 1.04 and 1.02, float32 1.04 and 1.02.  Before the
+// operands' bytes and the latency counted: 1.22 and 1.10 on the former (int32
+// 37 x 4544 x 3168: 317 us chosen, 50 now; float32 7692 x 6808 x 18: 206 and
+// 49); with constants of the former alone: 1.08 and 1.23 on the latter (int32
+// 617 x 26 x 50, float32 63 x 527 x 3).
 struct ValuFit {
     double launch;              // seconds
     double latency, latency_k;  // least seconds of a K step, and per k of a tiled program's
     double barriers;            // seconds of a step's barriers per resident workgroup
 };
 constexpr ValuFit kValuFit[2] = {
-    /* float32 */ {kLaunchSeconds, 0.1e-6, 0.0, 0.4e-6},
-    /* int32   */ {2.6e-6, 0.28e-6, 0.024e-6, 0.065e-6},
+    /* float32 */ {3.15e-6, 0.045e-6, 0.0048e-6, 0.55e-6},
+    /* int32   */ {2.9e-6, 0.085e-6, 0.0013e-6, 0.37e-6},
 };
 
 double fourth(double x) { return x * x * x * x; }

@@ -136,3 +136,14 @@ def test_thin_products_run_on_the_matrix_cores(dtype, M, N, K):
     from paper_1801_04348_amd import pk
     tbl = pk.pk_case_table_build(-1, machines.variant(regs_block=65536, regs_cu=65536, max_blocks_cu=2))
     assert pk.pk_select(tbl, dtype, M, N, K).family == pk.PK_FAMILY_MFMA
+
+
+@pytest.mark.parametrize("dtype,M,N,K", [
+    ("f32", 179, 2, 1), ("f32", 31, 123, 1), ("f32", 5, 9, 3), ("f32", 67, 25, 8), ("f32", 2071, 4, 1),
+    ("f32", 1307, 13, 13), ("i32", 1922, 8, 48), ("i32", 434, 16, 48), ("i32", 70, 36, 43)])
+def test_smallest_products_run_on_valu_programs(dtype, M, N, K):
+    """Products of a few loads a lane, whose fastest MFMA program takes 1.3 to
+    1.6 times the fastest VALU program's time (timed on gfx950 in a graph)."""
+    from paper_1801_04348_amd import pk
+    tbl = pk.pk_case_table_build(-1, machines.variant(regs_block=65536, regs_cu=65536, max_blocks_cu=2))
+    assert pk.pk_select(tbl, dtype, M, N, K).family != pk.PK_FAMILY_MFMA
