@@ -263,31 +263,60 @@ template <int EB, int BM, int BN, int BK, int WM, int WN> struct Tile {
     // K, added atomically (C holds zeros or the other shares' sums).  float32:
     // value v of a block is row 8 (v / 4) + 4 (lane / 32) + v % 4, column lane %
     // 32; bfloat16: row 4 (lane / 16) + v, column lane % 16.
-    __device__ __forceinline__ void store(const MmArgs &a, int row0, int col0) const {
+    // BATCH: the rows that an accumulation loads at once (below)
+    template <int BATCH> __device__ __forceinline__ void store(const MmArgs &a, int row0, int col0) const {
         const gmut<float> C = (gmut<float>)a.C;
         const bool interior = (row0 + BM <= a.M) && (col0 + BN <= a.N);
         // (the choices outside the loops: inside, every store would branch)
-        auto each = [&](auto &&put) {
+        // `put` of each value of rows [first, first + count) of the wavefront's
+        // TM RB * RB / 64 of a lane, and whether it lies in C
+        auto rows = [&](int first, int count, auto &&put) {
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
+            for (int n = first; n < first + count; ++n) {
+                const int i = n / (RB * RB / 64), v = n % (RB * RB / 64);
+                const int gr = row0 + wm * WTM + i * RB + 4 * (lane / RB) + (F32 ? 8 * (v / 4) + v % 4 : v);
+                const gmut<float> p = C + (int64_t)gr * a.ldc + col0 + wn * WTN + lane % RB;
 #pragma unroll
-                for (int v = 0; v < RB * RB / 64; ++v) {
-                    const int gr = row0 + wm * WTM + i * RB + 4 * (lane / RB) + (F32 ? 8 * (v / 4) + v % 4 : v);
-                    const gmut<float> p = C + (int64_t)gr * a.ldc + col0 + wn * WTN + lane % RB;
-#pragma unroll
-                    for (int j = 0; j < TN; ++j)
-                        if (interior || (gr < a.M && col0 + wn * WTN + j * RB + lane % RB < a.N))
-                            put(p + j * RB, acc[i][j][v]);
-                }
+                for (int j = 0; j < TN; ++j)
+                    put(n - first, j, interior || (gr < a.M && col0 + wn * WTN + j * RB + lane % RB < a.N), p + j * RB,
+                        acc[i][j][v]);
+            }
         };
+        constexpr int ROWS = TM * RB * RB / 64;
         if (a.splits > 1)
-            each([](gmut<float> p, float x) { unsafeAtomicAdd((float *)p, x); });
-        else if (a.accumulate)
-            each([](gmut<float> p, float x) { *p += x; });
-        else if (interior)
-            each([](gmut<float> p, float x) { *p = x; });
+            rows(0, ROWS, [](int, int, bool in, gmut<float> p, float x) { if (in) unsafeAtomicAdd((float *)p, x); });
+        else if (a.accumulate) {
+            // A load behind the store before it waits for memory row by row,
+            // so several rows' loads go before their additions (and lanes
+            // outside C load a zero: a branch around each load would put waits
+            // between them).
+            if constexpr (BATCH == 1) {
+                rows(0, ROWS, [](int, int, bool in, gmut<float> p, float x) { if (in) *p += x; });
+            } else {
+                const gptr<float> zero = (gptr<float>)(const void *)kZeroBlock;
+#pragma unroll
+                for (int n = 0; n < ROWS; n += BATCH) {
+                    float c[BATCH][TN];
+                    rows(n, BATCH, [&](int k, int j, bool in, gmut<float> p, float) { c[k][j] = *(in ? (gptr<float>)p : zero); });
+                    rows(n, BATCH, [&](int k, int j, bool in, gmut<float> p, float x) { if (in) *p = c[k][j] + x; });
+                }
+            }
+        } else if (interior)
+            rows(0, ROWS, [](int, int, bool in, gmut<float> p, float x) { if (in) *p = x; });
         else
-            each([](gmut<float> p, float x) { *p = x; });
+            rows(0, ROWS, [](int, int, bool in, gmut<float> p, float x) { if (in) *p = x; });
+    }
+
+    // Rows an accumulation loads at once: four, or two of four blocks and more
+    // (of 32 loads, programs of 512 and 1024 work-items spill).  Row by row
+    // before, so now: bfloat16 4596 x 2027 x 40, 47 us and 27; float32 2883 x
+    // 1126 x 3, 25 and 15; groups with rows padded to 8, bfloat16 700 of
+    // 128-512, 418 and 244, 4096 of 16-512, 660 and 399, float32 798 and 626.
+    // float32 groups have registers for it on aligned tiles one block wide
+    // alone: 64 x 128 tiles would take 104 for 96, unaligned 64 x 64 142 for
+    // 128, and a workgroup less would fit.
+    static constexpr int batch(bool group, bool aligned) {
+        return group && F32 && (!aligned || TN > 1) ? 1 : TN < 4 ? 4 : 2;
     }
 
     // a wavefront whose part of an edge tile lies wholly outside C has nothing
@@ -348,7 +377,7 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // memory latency that one step of products does not cover when operands come
 // from HBM (all workgroups of an XCD meet a panel's first touch together);
 // bfloat16 of order 4096 on 128 x 256 x 32, 146 us with two and 124 with three.
-template <int EB, int BM, int BN, int BK, int SBK, int WM, int WN, int MAX_DEPTH>
+template <int EB, int BM, int BN, int BK, int SBK, int WM, int WN, int MAX_DEPTH, bool GROUP>
 __device__ __forceinline__ void dma_tile(const MmArgs &a, const int row0, const int col0, unsigned char *const object,
                                          const int kt0, const int kt1) {
     unsigned char *const lds = MAX_DEPTH > 2 ? lds_pool(object) : object;
@@ -505,7 +534,7 @@ __device__ __forceinline__ void dma_tile(const MmArgs &a, const int row0, const 
         else
             run(std::integral_constant<int, MAX_DEPTH>{});
     }
-    t.store(a, row0, col0);
+    t.template store<T::batch(GROUP, true)>(a, row0, col0);
 }
 
 // ------------------------------------------------------------------ loads through registers
@@ -515,7 +544,7 @@ __device__ __forceinline__ void dma_tile(const MmArgs &a, const int row0, const 
 // would spill at their register cap) guarded loads, element by element at the
 // edges -- and everywhere in the large single-stage ones (CHUNKS false), where
 // the wide form of the guards would spill.
-template <int EB, int BM, int BN, int BK, int WM, int WN, int STAGES, bool WIDE, bool EDGE_ADDR>
+template <int EB, int BM, int BN, int BK, int WM, int WN, int STAGES, bool WIDE, bool EDGE_ADDR, bool GROUP>
 __device__ __forceinline__ void regs_tile(const MmArgs &a, const int row0, const int col0, unsigned char *const lds,
                                           const int kt0, const int kt1) {
     using T = Tile<EB, BM, BN, BK, WM, WN>;
@@ -818,20 +847,20 @@ __device__ __forceinline__ void regs_tile(const MmArgs &a, const int row0, const
             if (!idle) compute(0);
         }
     }
-    t.store(a, row0, col0);
+    t.template store<T::batch(GROUP, false)>(a, row0, col0);
 }
 
 // The tile by the way that its program and its rows' alignment take.
-template <int EB, int BM, int BN, int BK, int WM, int WN, int STAGES, bool WIDE, int MAX_DEPTH>
+template <int EB, int BM, int BN, int BK, int WM, int WN, int STAGES, bool WIDE, int MAX_DEPTH, bool GROUP = false>
 __device__ __forceinline__ void mfma_tile(const MmArgs &a, int row0, int col0, unsigned char *lds, int kt0, int kt1) {
     constexpr int SBK = buffer_k(BK, STAGES == 1);
     constexpr bool DMA = WIDE && loads_directly(EB == 4, BK, STAGES == 1, WM, WN);
     // the largest tiles' guarded loads: see regs_tile
     constexpr bool EDGE = WM * WN < 16 && (EB == 2 || STAGES == 2 || BM * BN * BK <= 128 * 256 * 16);
     if constexpr (DMA)
-        dma_tile<EB, BM, BN, BK, SBK, WM, WN, MAX_DEPTH>(a, row0, col0, lds, kt0, kt1);
+        dma_tile<EB, BM, BN, BK, SBK, WM, WN, MAX_DEPTH, GROUP>(a, row0, col0, lds, kt0, kt1);
     else
-        regs_tile<EB, BM, BN, BK, WM, WN, STAGES, WIDE, EDGE>(a, row0, col0, lds, kt0, kt1);
+        regs_tile<EB, BM, BN, BK, WM, WN, STAGES, WIDE, EDGE, GROUP>(a, row0, col0, lds, kt0, kt1);
 }
 
 // ------------------------------------------------------------------ single product
@@ -974,9 +1003,9 @@ __device__ __forceinline__ void grouped_tile(const GroupArgs &g, const GroupDesc
     const int tm = local / d.tiles_n, tn = local % d.tiles_n;
     const MmArgs a{d.A, d.B, d.C, d.lda, d.ldb, d.ldc, d.M, d.N, d.K, g.accumulate, WIDE, 0, 2};
     if constexpr (STREAM)
-        regs_tile<EB, BM, BN, BK, WM, WN, STAGES, WIDE, true>(a, tm * BM, tn * BN, lds, 0, (d.K + BK - 1) / BK);
+        regs_tile<EB, BM, BN, BK, WM, WN, STAGES, WIDE, true, true>(a, tm * BM, tn * BN, lds, 0, (d.K + BK - 1) / BK);
     else
-        mfma_tile<EB, BM, BN, BK, WM, WN, STAGES, WIDE, 2>(a, tm * BM, tn * BN, lds, 0, (d.K + BK - 1) / BK);
+        mfma_tile<EB, BM, BN, BK, WM, WN, STAGES, WIDE, 2, true>(a, tm * BM, tn * BN, lds, 0, (d.K + BK - 1) / BK);
 }
 
 template <int BM, int BN, int BK, int WM, int WN, int STAGES, bool WIDE>

@@ -319,15 +319,29 @@ __device__ __forceinline__ void mfma_i32_tile(const MmArgs &a, const int row0, c
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
             const int gc = col0 + wn * WTN + j * 32 + r;
+            auto each = [&](int first, int count, auto &&put) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int gr = row0 + wm * WTM + i * 32 + 8 * (v / 4) + 4 * h + (v % 4);
-                if (interior || (gr < M && gc < N)) {
+                for (int v = first; v < first + count; ++v) {
+                    const int gr = row0 + wm * WTM + i * 32 + 8 * (v / 4) + 4 * h + (v % 4);
                     const uint32_t x = (uint32_t)acc[0][i][j][v] + ((uint32_t)acc[1][i][j][v] << 8) +
                                        ((uint32_t)acc[2][i][j][v] << 16) + ((uint32_t)acc[3][i][j][v] << 24);
-                    const gmut<int32_t> p = C + (int64_t)gr * a.ldc + gc;
-                    *p = (int32_t)(a.accumulate ? (uint32_t)*p + x : x);
+                    put(v - first, interior || (gr < M && gc < N), C + (int64_t)gr * a.ldc + gc, x);
                 }
+            };
+            if (a.accumulate) {
+                // four rows' loads before their additions: a load behind the
+                // store before it waits for memory row by row (lanes outside C
+                // load a zero: a branch around each load would put waits
+                // between them)
+                const gptr<int32_t> zero = (gptr<int32_t>)(const void *)kZeroBlock;
+#pragma unroll
+                for (int v = 0; v < 16; v += 4) {
+                    uint32_t c[4];
+                    each(v, 4, [&](int n, bool in, gmut<int32_t> p, uint32_t) { c[n] = (uint32_t)*(in ? (gptr<int32_t>)p : zero); });
+                    each(v, 4, [&](int n, bool in, gmut<int32_t> p, uint32_t x) { if (in) *p = (int32_t)(c[n] + x); });
+                }
+            } else {
+                each(0, 16, [](int, bool in, gmut<int32_t> p, uint32_t x) { if (in) *p = (int32_t)x; });
             }
         }
 }

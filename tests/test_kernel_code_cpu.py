@@ -16,13 +16,13 @@ extern "C" __global__ void __launch_bounds__(256) two_f32(pkk::MmArgs a) { pkk::
 """
 
 
-def device_code(tmp_path, *flags):
-    """The compiler's text output for KERNELS, with the build's own flags."""
+def device_code(tmp_path, *flags, source=KERNELS):
+    """The compiler's text output for `source`, with the build's own flags."""
     if not os.path.exists(build.HIPCC):
         pytest.skip("no hipcc")
     src, out = str(tmp_path / "kernels.hip"), str(tmp_path / "kernels.out")
     with open(src, "w") as f:
-        f.write(KERNELS)
+        f.write(source)
     cmd = [build.HIPCC] + build.COMMON + build.DEVICE + ["--cuda-device-only", "-S", *flags, src, "-o", out]
     p = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True)
     assert p.returncode == 0, p.stderr[-4000:]
@@ -58,3 +58,18 @@ def test_no_address_past_the_end_of_an_lds_object(tmp_path):
     assert len(size) == 2
     reached = [(n, int(off)) for n, off in re.findall(r"addrspace\(3\) (@\w+), i32 (\d+)", ir) if n in size]
     assert reached and all(off < size[n] for n, off in reached), max(off for _, off in reached)
+
+
+@pytest.mark.parametrize("kernel", [
+    "mfma_f32<64, 64, 32, 2, 2, 2>", "mfma_bf16<64, 64, 64, 2, 2, 2>", "mfma_bf16<256, 128, 32, 2, 2, 2>"])
+def test_accumulation_loads_several_rows_at_once(tmp_path, kernel):
+    """C += A B reads C ahead of its stores: a load per row behind the row
+    before's store would take a trip to memory for each."""
+    code = device_code(tmp_path, source="""
+#include "kernels/mfma.hpp"
+extern "C" __global__ void __launch_bounds__(256) k(pkk::MmArgs a) { pkk::%s(a); }
+""" % kernel)
+    # single words are loaded from C alone; (a batch's last may stand out of line)
+    ops = re.findall(r"^\s+(global_load_dword|global_store_dword|s_waitcnt vmcnt)\b", code, re.M)
+    runs = re.findall("L+", "".join("L" if o == "global_load_dword" else "." for o in ops))
+    assert max(map(len, runs)) >= 3
