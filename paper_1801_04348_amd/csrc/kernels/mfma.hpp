@@ -311,12 +311,13 @@ template <int EB, int BM, int BN, int BK, int WM, int WN> struct Tile {
     // (of 32 loads, programs of 512 and 1024 work-items spill).  Row by row
     // before, so now: bfloat16 4596 x 2027 x 40, 47 us and 27; float32 2883 x
     // 1126 x 3, 25 and 15; groups with rows padded to 8, bfloat16 700 of
-    // 128-512, 418 and 244, 4096 of 16-512, 660 and 399, float32 798 and 626.
-    // float32 groups have registers for it on aligned tiles one block wide
-    // alone: 64 x 128 tiles would take 104 for 96, unaligned 64 x 64 142 for
-    // 128, and a workgroup less would fit.
-    static constexpr int batch(bool group, bool aligned) {
-        return group && F32 && (!aligned || TN > 1) ? 1 : TN < 4 ? 4 : 2;
+    // 128-512, 418 and 244, 4096 of 16-512, 660 and 399, float32 798 and 626,
+    // packed 861 and 677.  Grouped float32 kernels without `room`, registers
+    // to hold the rows in, keep to one: aligned 64 x 128 tiles would take 104
+    // for 96, two-stage unaligned 64 x 64 ones 142 for 128, and a workgroup
+    // less would fit.
+    static constexpr int batch(bool group, bool room) {
+        return group && F32 && !room ? 1 : TN < 4 ? 4 : 2;
     }
 
     // a wavefront whose part of an edge tile lies wholly outside C has nothing
@@ -534,7 +535,7 @@ __device__ __forceinline__ void dma_tile(const MmArgs &a, const int row0, const 
         else
             run(std::integral_constant<int, MAX_DEPTH>{});
     }
-    t.template store<T::batch(GROUP, true)>(a, row0, col0);
+    t.template store<T::batch(GROUP, T::TN == 1 || T::TM > 1)>(a, row0, col0);
 }
 
 // ------------------------------------------------------------------ loads through registers
@@ -847,7 +848,7 @@ __device__ __forceinline__ void regs_tile(const MmArgs &a, const int row0, const
             if (!idle) compute(0);
         }
     }
-    t.template store<T::batch(GROUP, false)>(a, row0, col0);
+    t.template store<T::batch(GROUP, STAGES == 1 || T::TN > 1)>(a, row0, col0);
 }
 
 // The tile by the way that its program and its rows' alignment take.
