@@ -312,7 +312,7 @@ template <int EB, int BM, int BN, int BK, int WM, int WN> struct Tile {
     // before, so now: bfloat16 4596 x 2027 x 40, 47 us and 27; float32 2883 x
     // 1126 x 3, 25 and 15; groups with rows padded to 8, bfloat16 700 of
     // 128-512, 418 and 244, 4096 of 16-512, 660 and 399, float32 798 and 626,
-    // packed 861 and 677.  Grouped float32 kernels without `room`, registers
+    // packed 857 and 682.  Grouped float32 kernels without `room`, registers
     // to hold the rows in, keep to one: aligned 64 x 128 tiles would take 104
     // for 96, two-stage unaligned 64 x 64 ones 142 for 128, and a workgroup
     // less would fit.
